@@ -173,11 +173,11 @@ int fda_get_plan(const fda_ctx* ctx, fda_plan_info* out);
  *          sign_i(j) (w_kj - w_t0_j)   (absent without SKETCH)
  * Pointers need the alignment of their element type only (2 bytes for a bf16 slab, 4 for everything
  * fp32; anything less is FDA_EINVAL): whole-vector loads are used for any d and any row_stride.
- * Sketch cells are accumulated as integers (a drift u enters as round(u * 2^e), 2^e chosen
- * per call so that the rounding is at most 2^-18 of the mean |u|), and everything across
- * workgroups is merged in a fixed order: with the integer cells (fda_last_state_path 0 or 1) the
- * state is bit-identical from run to run; the fp64 cells of the last fallback (path 2, and path 1
- * of fda_mean_state) add in the order the lanes arrive and are not.
+ * Sketch cells are accumulated as integers (a drift u enters as round(u * 2^e); every workgroup chooses
+ * its own 2^e from a sample of its drifts, so that the rounding is at most 2^-18 of their typical
+ * magnitude), and everything across workgroups is merged in a fixed order: with the integer cells
+ * (fda_last_state_path 0 or 1) the state is bit-identical from run to run; the fp64 cells of the last
+ * fallback (path 2, and path 1 of fda_mean_state) add in the order the lanes arrive and are not.
  * The pass works on drifts scaled by that 2^e, so a single drift 2^45 times the mean magnitude or
  * more makes ||u_k||^2 overflow to infinity (reported as a non-finite estimate) where the plain
  * fp32 square would overflow only at 2^64.
@@ -220,7 +220,8 @@ int fda_estimate_variance(fda_ctx* ctx, const float* state, double theta, double
  *                 and the context keeps ||w_bar - w_t0||^2 for fda_sync_from_mean.
  * A drift enters the sketch as the integer round(u * 2^e) (2^e as in fda_local_state), the K
  * integers of a coordinate are summed and added to 64-bit cells: exact, hence bit-identical
- * from run to run; drifts beyond 2^11 times the sampled mean |u| send the call down an fp64 path.
+ * from run to run; a workgroup that meets drifts beyond 2^11 times the typical |u| of its sample redoes
+ * its share in fp64.
  * Returns FDA_ERANGE if K times the coordinates per workgroup reaches 2^33.
  */
 int fda_mean_state(fda_ctx* ctx, const void* w, const float* w_t0, const float* xi,
@@ -326,9 +327,9 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
 
 /*
  * Diagnostic: which kind of LDS sketch cell the last fda_local_state of this context ended
- * up using -- 0: 32-bit integers (the normal case), 1: 64-bit integers (a drift was too large
- * for, or a sum did not fit, the 32-bit cells), 2: fp64 (the drifts' dynamic range is beyond
- * the 64-bit cells), -1: the context has no sketch.  Waits for `stream`.  The result of
+ * up using, the widest of any workgroup -- 0: 32-bit integers (the normal case), 1: 64-bit integers (a
+ * drift was too large for, or a sum did not fit, the 32-bit cells), 2: fp64 (the drifts' dynamic range is
+ * beyond the 64-bit cells), -1: the context has no sketch.  Waits for `stream`.  The result of
  * fda_local_state is the same within the stated tolerance whichever path ran; only the time
  * differs.
  */

@@ -2,6 +2,7 @@
 // launches.  Everything the path computes runs in the kernels of fda_kernels.hpp.
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <cstdarg>
 #include <cstddef>
 #include <cstdio>
@@ -58,21 +59,20 @@ constexpr double kAtomicCost = 7.5;        // one 32-bit LDS addition and the OR
 constexpr double kPairAddCost = 13.0;      // one 64-bit LDS addition (two cells) and the OR of what it returned
 constexpr double kPlacedPairAddCost = 9.5; // ... when the table's row slots are placed against LDS collisions
 constexpr double kSharedByteCost = 0.25;   // per byte of w_t0 / xi / table read by one more workgroup
-constexpr int kMaxEstBlocksPerRow = 128;   // 32768 / 256: workgroups of estimate_kernel per sketch row
-constexpr int kScaleSamples = 16384;       // sampled coordinates per worker for the scale
-constexpr int kScaleBlocks = kScaleSamples * fda::kScaleMaxSlices / fda::kSmallThreads;   // its workgroups, at most
 constexpr int kXiBlocks = 4096;
 constexpr int kSyncNormSlices = 64;   // the synchronization kernel's partial norms are condensed to this many
 constexpr long long kSyncVectorsPerBlock = 4 * fda::kSmallThreads;   // four trips per workgroup
 constexpr long long kStreamBytes = 512ll << 20;   // slabs beyond this are synchronized with streaming hints
+constexpr int kPathWords = 64;        // the two path records, on lines of their own
 constexpr int64_t kAlign = 256;
 
 int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
-// How one state pass is spread over the chip for a given sketch-cell size.
+// How the state pass is spread over the chip.
 struct Split {
-  int G, R, kcnt_max, rcnt_max, KC, LR, P, stride;
-  int split;        // 32-bit cells: sign-split LDS rows (2 m buckets per row)
+  int G, R, kcnt_max, rcnt_max, KC, LR, P;
+  int split;        // sign-split LDS rows (2 m buckets per row)
+  int shrink;       // StateParams::shrink
   int64_t chunk, lds_bytes;
 };
 // How one mean-state pass is spread over the chip.
@@ -81,18 +81,18 @@ struct MeanSplit {
   int64_t chunk, lds_bytes;
 };
 struct Plan {
-  Split narrow;     // 32-bit cells: the pass every call runs
-  Split wide;       // 8-byte cells: the 64-bit integer and fp64 passes
+  Split narrow;     // fda_local_state
   MeanSplit mean;   // fda_mean_state
   int vec;          // elements per 16-byte slab load
   int fb;           // bits per field of the tabulated hash
-  int narrow_fb;    // ... of the table the 32-bit-cell pass streams (kPlacedFieldBits with placed rows)
+  int narrow_fb;    // ... of the table the state pass streams (kPlacedFieldBits with placed rows)
   int grp;          // rows per placement group of that table (1: rows keep their slots)
-  int words;        // 16-bit words per record of the table the 32-bit-cell pass streams
+  int words;        // 16-bit words per record of the table the state pass streams
   int mean_words;   // ... and of the mean-state pass's table
   bool shared_table;  // both passes split the rows alike and stream one table
   int64_t cells, S, dpad;
-  int64_t off_np, off_sk, off_xi, off_syncnorm, off_scale, off_smax, off_ssum, off_nmax, off_dnorm, off_est, off_ticket, off_table,
+  int tickets;        // finished-workgroup counters: [0] estimate_kernel, then those of finish_kernel
+  int64_t off_np, off_sk, off_units, off_xi, off_syncnorm, off_path, off_ticket, off_dnorm, off_est, off_table,
       off_mean_table, ws_bytes;
 };
 
@@ -122,7 +122,7 @@ int validate(const fda_desc* d) {
   return FDA_OK;
 }
 
-int make_split(const fda_desc* d, int cus, int64_t lds_cu, int cell_bytes, Split* sp) {
+int make_split(const fda_desc* d, int cus, int64_t lds_cu, Split* sp) {
   const bool sk = (d->variants & FDA_VARIANT_SKETCH) != 0;
   const int64_t cells = sk ? (int64_t)d->l * d->m : 0;
   const int vec = fda::kStateV;
@@ -135,48 +135,34 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, int cell_bytes, Split
   const int l = sk ? d->l : 1;
   double best = -1.0;
   int bestG = 0, bestR = 0, bestKC = 0, bestLR = 0, bestSplit = 0;
-  const bool narrow = cell_bytes == 4;
   for (int G = 1; G <= d->K; ++G) {
     const int kc = (d->K + G - 1) / G;
     {
       int KC = 0;                                            // the smallest kernel that holds kc workers
-      if (narrow) {
-        for (int c : fda::kKCSet)
-          if (c >= kc) { KC = c; break; }
-      } else {
-        for (int c : fda::kWideKCSet)
-          if (c >= kc) { KC = c; break; }
-      }
+      for (int c : fda::kKCSet)
+        if (c >= kc) { KC = c; break; }
       if (KC == 0) continue;
-      const int stride = (KC == 1) ? 1 : (KC | 1);
-      // sign-split rows (32-bit cells, even slot counts): no negated terms, no select per addition, twice the LDS
+      // sign-split rows (even slot counts): no negated terms, no select per addition, twice the LDS
       // (without a sketch either kind of kernel does the same)
-      for (int split = (narrow && KC % 2 == 0) ? 1 : 0; split >= 0; --split) {
-        if (narrow && !fda::narrow_kernel_exists(KC, split != 0)) continue;
+      for (int split = KC % 2 == 0 ? 1 : 0; split >= 0; --split) {
+        if (!fda::narrow_kernel_exists(KC, split != 0)) continue;
         for (int R = 1; R <= l; ++R) {
           const int rc = (l + R - 1) / R;
           int LR = 0;                                        // row slots of the kernel that would run
-          if (narrow) {
-            if (rc <= fda::kMaxLR && KC * rc <= fda::kMaxSlots) LR = rc;
-          } else {
-            for (int c : fda::kWideLRSet)
-              if (c >= rc) { LR = c; break; }
-          }
+          if (rc <= fda::kMaxLR && KC * rc <= fda::kMaxSlots) LR = rc;
           if (LR == 0) continue;
-          const int64_t need = !cells ? 0
-                               : narrow ? (int64_t)fda::cells32_words(rc, split ? 2 * d->m : d->m, KC) * 4
-                                        : ((int64_t)rc * d->m + fda::kDummyCells) * stride * cell_bytes;
+          const int64_t need = cells ? (int64_t)fda::cells32_words(rc, split ? 2 * d->m : d->m, KC) * 4 : 0;
           if (need + kLdsReserve > lds_cu) continue;
           // Estimated cost per coordinate, in vector-ALU instructions (an LDS addition counted as what it
           // keeps the compute unit from issuing): per element slot the load / drift / fixed-point work
           // (with the negated terms unless the rows are sign-split), per row slot the table field, per
           // addition the select (unless split), the overflow OR and the LDS instruction itself.
           const double wg = (double)G * R;
-          const double pairs = (KC % 2 == 0 && narrow) ? KC / 2 : KC;           // LDS instructions per row slot
+          const double pairs = KC % 2 == 0 ? KC / 2 : KC;                       // LDS instructions per row slot
           // (a table with placed rows avoids about a third of the LDS collisions)
-          const bool placed = narrow && split && cells && fda::placed_kernel_exists(KC) &&
+          const bool placed = split && cells && fda::placed_kernel_exists(KC) &&
                               !(d->flags & FDA_DESC_PLAIN_TABLE) && fda::placed_group_rows(rc, d->m, KC) >= 2;
-          const double per_add = (KC % 2 == 0 && narrow) ? (placed ? kPlacedPairAddCost
+          const double per_add = KC % 2 == 0 ? (placed ? kPlacedPairAddCost
                                                             : split ? kPairAddCost : kPairAddCost + 2.0 * kSelectCost)
                                                          : kAtomicCost + kSelectCost;
           const double cost = wg * KC * (split ? kElementCost : kElementCost + kNegateCost) +
@@ -201,10 +187,7 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, int cell_bytes, Split
   sp->rcnt_max = (l + bestR - 1) / bestR;
   sp->KC = bestKC;
   sp->LR = bestLR;
-  sp->stride = (sp->KC == 1) ? 1 : (sp->KC | 1);
-  const int64_t sk_bytes = !cells ? 0
-                           : narrow ? (int64_t)fda::cells32_words(sp->rcnt_max, sp->split ? 2 * d->m : d->m, sp->KC) * 4
-                                    : ((int64_t)sp->rcnt_max * d->m + fda::kDummyCells) * sp->stride * cell_bytes;
+  const int64_t sk_bytes = cells ? (int64_t)fda::cells32_words(sp->rcnt_max, sp->split ? 2 * d->m : d->m, sp->KC) * 4 : 0;
   sp->lds_bytes = round_up(sk_bytes, 16) + kLdsReserve;
   // one workgroup per CU: the kernels hold more registers than two resident workgroups would allow
   const int occ = 1;
@@ -213,15 +196,15 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, int cell_bytes, Split
   // slots a whole number of times; and a workgroup costs its set-up, reductions and flush on top of
   // its tiles (measured: about six tiles' worth).  Among the first few feasible numbers of rounds of
   // resident workgroups keep the cheapest: rounds x (tiles per workgroup + overhead).
-  // Feasible: 32-bit cells take up to 16384 terms (scale_kernel sends fuller ones to the 64-bit pass), so
-  // a chunk should put about 12000 into a cell at most.  The cells of sign-split rows take the terms of one
+  // Feasible: a 32-bit cell should take about 12000 terms at most (16384 of typical size, one way, fill its
+  // band).  The cells of sign-split rows take the terms of one
   // hash sign each, which do not cancel when the drifts themselves lean one way: they are kept at about
   // 3500 expected terms (a term of mean magnitude is 2^18..2^19 units: the band of 2^30 then holds unless
   // more than about half of a cell's mass leans one way -- such a call finishes on the 64-bit cells).
   const int64_t slots = (int64_t)cus * occ, gr = (int64_t)bestG * bestR;
   const int64_t tiles = (d->d + tile - 1) / tile;
   int64_t pmin = 1;
-  if (narrow && cells) {
+  if (cells) {
     const int64_t per_row = (int64_t)d->m * (bestSplit ? 2 : 1);
     const int64_t terms = bestSplit ? kMaxTermsPlannedSplit : kMaxTermsPlanned;
     pmin = (d->d + per_row * terms - 1) / (per_row * terms);
@@ -243,6 +226,13 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, int cell_bytes, Split
   }
   sp->P = (int)P;
   sp->chunk = round_up((d->d + P - 1) / P, tile);
+  // cells that may collect more than 4096 terms get a unit one bit coarser: the expected number of terms of a
+  // cell and six standard deviations
+  sp->shrink = 0;
+  if (cells) {
+    const double expect = (double)sp->chunk / ((double)d->m * (sp->split ? 2 : 1));
+    if (expect + 6.0 * std::sqrt(expect) >= 4096.0) sp->shrink = 1;
+  }
   return FDA_OK;
 }
 
@@ -285,31 +275,30 @@ int make_plan(const fda_desc* d, int cus, int64_t lds_cu, Plan* pl) {
   pl->cells = sk ? (int64_t)d->l * d->m : 0;
   pl->S = 2 + pl->cells;
   pl->vec = d->dtype == FDA_F32 ? 4 : 8;
-  int rc = make_split(d, cus, lds_cu, 8, &pl->wide);     // the stricter one first: its error message
+  int rc = make_mean_split(d, cus, lds_cu, &pl->mean);   // the stricter one first: its error message
   if (rc != FDA_OK) return rc;
-  rc = make_split(d, cus, lds_cu, 4, &pl->narrow);
-  if (rc != FDA_OK) return rc;
-  rc = make_mean_split(d, cus, lds_cu, &pl->mean);
+  rc = make_split(d, cus, lds_cu, &pl->narrow);
   if (rc != FDA_OK) return rc;
   // the per-workgroup partials of fda_local_state and of fda_mean_state share one region
-  const int64_t Pmax = pl->narrow.P > pl->wide.P ? pl->narrow.P : pl->wide.P;
-  int64_t np_bytes = (int64_t)pl->narrow.P * d->K * 2 * 8, sk_bytes = Pmax * d->K * pl->cells * 8;
+  int64_t np_bytes = (int64_t)pl->narrow.P * d->K * 2 * 8, sk_bytes = (int64_t)pl->narrow.P * d->K * pl->cells * 8;
+  int64_t unit_count = (int64_t)pl->narrow.P * pl->narrow.G * pl->narrow.R;
+  if (unit_count < (int64_t)pl->mean.P * pl->mean.R) unit_count = (int64_t)pl->mean.P * pl->mean.R;
   if (np_bytes < (int64_t)pl->mean.P * 3 * 8) np_bytes = (int64_t)pl->mean.P * 3 * 8;
   if (sk_bytes < (int64_t)pl->mean.P * pl->cells * 8) sk_bytes = (int64_t)pl->mean.P * pl->cells * 8;
   pl->off_np = 0;
   pl->off_sk = round_up(pl->off_np + np_bytes, kAlign);
-  pl->off_xi = round_up(pl->off_sk + sk_bytes, kAlign);
+  pl->off_units = round_up(pl->off_sk + sk_bytes, kAlign);
+  pl->off_xi = round_up(pl->off_units + unit_count * (int64_t)sizeof(fda::CellUnit), kAlign);
   // one partial norm per workgroup of the synchronization kernel, and their sum
   const int64_t sync_blocks = ((d->d + fda::kSyncV - 1) / fda::kSyncV + kSyncVectorsPerBlock - 1) / kSyncVectorsPerBlock;
   pl->off_syncnorm = round_up(pl->off_xi + kXiBlocks * 8, kAlign);
-  pl->off_scale = round_up(pl->off_syncnorm + (sync_blocks + kSyncNormSlices) * 8, kAlign);
-  pl->off_smax = round_up(pl->off_scale + 2 * (int64_t)sizeof(fda::ScaleInfo), kAlign);
-  pl->off_ssum = round_up(pl->off_smax + kScaleBlocks * 4, kAlign);
-  pl->off_nmax = round_up(pl->off_ssum + kScaleBlocks * 8, kAlign);
-  pl->off_dnorm = round_up(pl->off_nmax + 8, kAlign);
+  pl->off_path = round_up(pl->off_syncnorm + (sync_blocks + kSyncNormSlices) * 8, kAlign);
+  pl->off_ticket = pl->off_path + kPathWords * 4;
+  const int64_t runs = sk ? (int64_t)d->l * ((d->m + fda::kFinishCols - 1) / fda::kFinishCols) : 0;   // of 32 cells
+  pl->tickets = 2 + (int)runs;
+  pl->off_dnorm = round_up(pl->off_ticket + (int64_t)pl->tickets * 4, kAlign);
   pl->off_est = round_up(pl->off_dnorm + 8, kAlign);
-  pl->off_ticket = round_up(pl->off_est + (2 + (int64_t)FDA_MAX_SKETCH_ROWS * kMaxEstBlocksPerRow) * 8, kAlign);
-  pl->off_table = round_up(pl->off_ticket + 8, kAlign);
+  pl->off_table = round_up(pl->off_est + (2 + runs) * 8, kAlign);   // one piece of a row norm per run
   pl->dpad = round_up(d->d, fda::kRecBlockCoords);      // the table comes in whole blocks
   // the tabulated hash: per row group one record per coordinate with a field per row slot
   pl->fb = fda::field_bits_for(sk ? d->m : 1);
@@ -373,41 +362,28 @@ int device_shape(int* cus, int64_t* lds) {
 constexpr int kVecOk = 1;
 
 // Route a launch (or, with prm == nullptr, the LDS-limit setup) to the translation unit that
-// holds the kernel for this slab type, cell kind and shape.
-int dispatch_any(int dtype, int cell, const Split& sp, int FB, const fda::StateParams* prm, hipStream_t st) {
+// holds the kernel for this slab type and shape.
+int dispatch_any(int dtype, const Split& sp, int FB, const fda::StateParams* prm, hipStream_t st) {
   const int KC = sp.KC, LR = sp.LR;
   const size_t lds = (size_t)sp.lds_bytes;
   hipError_t e = hipErrorInvalidValue;
-  if (cell == fda::kCellI32) {
 #define FDA_CASE(t, kc) case kc: e = fda::launch_narrow_##t##_kc##kc(LR, FB, sp.split, prm, lds, st); break
-    if (dtype == FDA_F32) {
-      switch (KC) { FDA_CASE(f32, 1); FDA_CASE(f32, 2); FDA_CASE(f32, 4); FDA_CASE(f32, 6); FDA_CASE(f32, 8); }
-    } else {
-      switch (KC) { FDA_CASE(bf16, 1); FDA_CASE(bf16, 2); FDA_CASE(bf16, 4); FDA_CASE(bf16, 6); FDA_CASE(bf16, 8); }
-    }
-#undef FDA_CASE
-  } else if (dtype == FDA_F32) {
-    e = cell == fda::kCellI64 ? fda::launch_wide_f32_i64(KC, LR, prm, lds, st)
-                              : fda::launch_wide_f32_f64(KC, LR, prm, lds, st);
+  if (dtype == FDA_F32) {
+    switch (KC) { FDA_CASE(f32, 1); FDA_CASE(f32, 2); FDA_CASE(f32, 4); FDA_CASE(f32, 6); FDA_CASE(f32, 8); }
   } else {
-    e = cell == fda::kCellI64 ? fda::launch_wide_bf16_i64(KC, LR, prm, lds, st)
-                              : fda::launch_wide_bf16_f64(KC, LR, prm, lds, st);
+    switch (KC) { FDA_CASE(bf16, 1); FDA_CASE(bf16, 2); FDA_CASE(bf16, 4); FDA_CASE(bf16, 6); FDA_CASE(bf16, 8); }
   }
+#undef FDA_CASE
   if (e == hipErrorInvalidValue)
     return fail(FDA_EINVAL, "internal: no state kernel for %d workers x %d rows per workgroup", KC, LR);
   if (e != hipSuccess) return fail(FDA_EHIP, "state kernel launch failed: %s", hipGetErrorString(e));
   return FDA_OK;
 }
 
-int dispatch_mean(int dtype, int cell, const MeanSplit& ms, int FB, const fda::MeanParams* prm, hipStream_t st) {
+int dispatch_mean(int dtype, const MeanSplit& ms, int FB, const fda::MeanParams* prm, hipStream_t st) {
   const size_t lds = (size_t)ms.lds_bytes;
-  hipError_t e;
-  if (dtype == FDA_F32)
-    e = cell == fda::kCellI64 ? fda::launch_mean_f32_i64(ms.rcnt_max, FB, prm, lds, st)
-                              : fda::launch_mean_f32_f64(ms.rcnt_max, FB, prm, lds, st);
-  else
-    e = cell == fda::kCellI64 ? fda::launch_mean_bf16_i64(ms.rcnt_max, FB, prm, lds, st)
-                              : fda::launch_mean_bf16_f64(ms.rcnt_max, FB, prm, lds, st);
+  const hipError_t e = dtype == FDA_F32 ? fda::launch_mean_f32(ms.rcnt_max, FB, prm, lds, st)
+                                        : fda::launch_mean_bf16(ms.rcnt_max, FB, prm, lds, st);
   if (e == hipErrorInvalidValue)
     return fail(FDA_EINVAL, "internal: no mean-state kernel for %d rows per workgroup", ms.rcnt_max);
   if (e != hipSuccess) return fail(FDA_EHIP, "mean-state kernel launch failed: %s", hipGetErrorString(e));
@@ -446,8 +422,7 @@ struct fda_ctx {
   unsigned char* ws;
   int device;
   int cus;
-  bool counted = false;       // cell_count_kernel has been enqueued for this context
-  bool table_built = false;       // the hash table of the 32-bit-cell pass has been enqueued
+  bool table_built = false;       // the hash table of the state pass has been enqueued
   bool mean_table_built = false;  // ... of the mean-state pass (the same table when the plan shares it)
   bool tickets_cleared = false;
   // optional timing of the state kernel (fda_profile_enable)
@@ -460,18 +435,13 @@ struct fda_ctx {
 };
 
 namespace {
-// The finished-workgroup counters of scale_kernel and estimate_kernel start at zero and are left
+// The finished-workgroup counters of finish_kernel and estimate_kernel start at zero and are left
 // at zero by every launch; the workspace arrives uninitialised, so they are cleared once.
 int clear_tickets_once(fda_ctx* c, hipStream_t st) {
   if (c->tickets_cleared) return FDA_OK;
-  hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(1), dim3(64), 0, st,
-                     reinterpret_cast<unsigned int*>(c->ws + c->plan.off_ticket), 2);
-  FDA_HIP(hipGetLastError());
-  // ... and so are the two scale records, whose flags an estimate may report before any state pass ran
-  static_assert(2 * sizeof(fda::ScaleInfo) <= 64 * 4, "clear_u32_kernel clears at most 64 words");
-  hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(1), dim3(64), 0, st,
-                     reinterpret_cast<unsigned int*>(c->ws + c->plan.off_scale),
-                     (int)(2 * sizeof(fda::ScaleInfo) / 4));
+  // (the path records, two pairs of ints, lie in front of the counters)
+  hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(64), dim3(fda::kSmallThreads), 0, st,
+                     reinterpret_cast<unsigned int*>(c->ws + c->plan.off_path), kPathWords + c->plan.tickets);
   FDA_HIP(hipGetLastError());
   c->tickets_cleared = true;
   return FDA_OK;
@@ -509,8 +479,6 @@ int prof_end(fda_ctx* c, hipStream_t st, int slot) {
   return FDA_OK;
 }
 
-// Before the first sketch of a context: the hash table and the cell counts.  Then, per call, the
-// fixed-point units from a sample of the drifts (this also clears the flags in *scale).
 int build_table(fda_ctx* ctx, int R, int slots, int fb, int words, int grp, int KC, int64_t off, hipStream_t st) {
   const fda_desc& d = ctx->desc;
   const Plan& pl = ctx->plan;
@@ -526,32 +494,10 @@ int build_table(fda_ctx* ctx, int R, int slots, int fb, int words, int grp, int 
   return FDA_OK;
 }
 
-// for_mean: the call is fda_mean_state (else fda_local_state): which table must exist
-int prepare_sketch(fda_ctx* ctx, const void* w, const float* w_t0, fda::ScaleInfo* scale, bool for_mean,
-                   hipStream_t st) {
-  const fda_desc& d = ctx->desc;
+// Before the first sketch of a context: the hash of every (row, coordinate), tabulated for the pass that is
+// about to run (for_mean: fda_mean_state, else fda_local_state).
+int prepare_sketch(fda_ctx* ctx, bool for_mean, hipStream_t st) {
   const Plan& pl = ctx->plan;
-  int rc0 = clear_tickets_once(ctx, st);
-  if (rc0 != FDA_OK) return rc0;
-  float* smax = reinterpret_cast<float*>(ctx->ws + pl.off_smax);
-  double* ssum = reinterpret_cast<double*>(ctx->ws + pl.off_ssum);
-  unsigned int* nmax = reinterpret_cast<unsigned int*>(ctx->ws + pl.off_nmax);
-  if (!ctx->counted) {
-    // once per context: the largest number of coordinates any workgroup puts in one cell,
-    // for the partitioning of the 32-bit pass ([0]) and of the 8-byte passes ([1]) ...
-    hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(1), dim3(64), 0, st, nmax, 2);
-    FDA_HIP(hipGetLastError());
-    hipLaunchKernelGGL(fda::cell_count_kernel, dim3(pl.narrow.P * d.l), dim3(fda::kStateThreads),
-                       (size_t)d.m * 4 * (pl.narrow.split ? 2 : 1), st, ctx->coef, d.l, d.m, pl.narrow.split,
-                       (long long)d.d, (long long)pl.narrow.chunk, nmax);
-    FDA_HIP(hipGetLastError());
-    hipLaunchKernelGGL(fda::cell_count_kernel, dim3(pl.wide.P * d.l), dim3(fda::kStateThreads),
-                       (size_t)d.m * 4, st, ctx->coef, d.l, d.m, 0, (long long)d.d,
-                       (long long)pl.wide.chunk, nmax + 1);
-    FDA_HIP(hipGetLastError());
-    ctx->counted = true;
-  }
-  // ... and the hash of every (row, coordinate), tabulated for the pass that is about to run
   if (!for_mean && !ctx->table_built) {
     int rc = build_table(ctx, pl.narrow.R, pl.narrow.LR, pl.narrow_fb, pl.words, pl.grp, pl.narrow.KC, pl.off_table, st);
     if (rc != FDA_OK) return rc;
@@ -564,19 +510,38 @@ int prepare_sketch(fda_ctx* ctx, const void* w, const float* w_t0, fda::ScaleInf
     ctx->mean_table_built = true;
     if (pl.shared_table) ctx->table_built = true;
   }
-  const int samples = (int)(d.d < kScaleSamples ? d.d : kScaleSamples);
-  int slices = (d.K + 7) / 8;                 // about eight workers per thread
-  if (slices > fda::kScaleMaxSlices) slices = fda::kScaleMaxSlices;
-  const int sblocks = (samples * slices + fda::kSmallThreads - 1) / fda::kSmallThreads;
-  unsigned int* ticket = reinterpret_cast<unsigned int*>(ctx->ws + pl.off_ticket);
-  if (d.dtype == FDA_F32)
-    hipLaunchKernelGGL(fda::scale_kernel<float>, dim3(sblocks), dim3(fda::kSmallThreads), 0, st,
-                       static_cast<const float*>(w), w_t0, d.K, (long long)d.d, (long long)d.row_stride,
-                       samples, slices, smax, ssum, ticket, nmax, scale);
-  else
-    hipLaunchKernelGGL(fda::scale_kernel<fda::bf16_t>, dim3(sblocks), dim3(fda::kSmallThreads), 0, st,
-                       static_cast<const fda::bf16_t*>(w), w_t0, d.K, (long long)d.d,
-                       (long long)d.row_stride, samples, slices, smax, ssum, ticket, nmax, scale);
+  return FDA_OK;
+}
+
+fda::PathRecord* path_record(const fda_ctx* ctx, bool for_mean) {
+  return reinterpret_cast<fda::PathRecord*>(ctx->ws + ctx->plan.off_path) + (for_mean ? 1 : 0);
+}
+
+// The partials of a state pass -> state[rows][S] (rows = K), or mean_state[S] (rows = 1), with the estimate
+// `est` on it (its rows are filled in here) unless est is NULL.
+int launch_finish(fda_ctx* ctx, bool for_mean, float* state, const fda::EstimateArgs* est, hipStream_t st) {
+  const fda_desc& d = ctx->desc;
+  const Plan& pl = ctx->plan;
+  const bool sk = (d.variants & FDA_VARIANT_SKETCH) != 0;
+  fda::FinishParams f;
+  f.part_np = reinterpret_cast<const double*>(ctx->ws + pl.off_np);
+  f.part_sk = ctx->ws + pl.off_sk;
+  f.units = reinterpret_cast<const fda::CellUnit*>(ctx->ws + pl.off_units);
+  f.path = path_record(ctx, for_mean);
+  f.state = state;
+  f.dnorm = for_mean ? reinterpret_cast<double*>(ctx->ws + pl.off_dnorm) : nullptr;
+  f.ticket = reinterpret_cast<unsigned int*>(ctx->ws + pl.off_ticket) + 1;
+  f.est_part = reinterpret_cast<double*>(ctx->ws + pl.off_est);
+  f.rows = for_mean ? 1 : d.K;
+  f.K = d.K; f.l = sk ? d.l : 0; f.m = sk ? d.m : 0;
+  f.P = for_mean ? pl.mean.P : pl.narrow.P;
+  f.G = for_mean ? 1 : pl.narrow.G;
+  f.R = for_mean ? pl.mean.R : pl.narrow.R;
+  f.est = est != nullptr ? *est : fda::EstimateArgs{};
+  f.wl = fda::kFinishLanes;
+  while (f.wl > 1 && (f.wl / 2 >= f.rows || f.P * f.wl > fda::kFinishLanes * fda::kFinishLoads)) f.wl /= 2;
+  const int blocks = 1 + f.l * ((f.m + fda::kFinishCols - 1) / fda::kFinishCols) * ((f.rows + f.wl - 1) / f.wl);
+  hipLaunchKernelGGL(fda::finish_kernel, dim3(blocks), dim3(fda::kFinishThreads), 0, st, f);
   FDA_HIP(hipGetLastError());
   return FDA_OK;
 }
@@ -683,22 +648,11 @@ int fda_create(fda_ctx** ctx, const fda_desc* desc, void* workspace, size_t work
   // The dynamic-LDS limit of a kernel is one setting per process: raise it to everything the
   // device allows, so that a context created later with a smaller sketch cannot lower it under
   // what an earlier context's launches need.
-  Split narrow_max = pl.narrow, wide_max = pl.wide;
+  Split narrow_max = pl.narrow;
   MeanSplit mean_max = pl.mean;
-  narrow_max.lds_bytes = wide_max.lds_bytes = mean_max.lds_bytes = lds;
-  rc = dispatch_any(desc->dtype, fda::kCellI32, narrow_max, pl.narrow_fb, nullptr, nullptr);
-  if (rc == FDA_OK) rc = dispatch_mean(desc->dtype, fda::kCellI64, mean_max, pl.fb, nullptr, nullptr);
-  if (rc == FDA_OK && (desc->variants & FDA_VARIANT_SKETCH))
-    rc = dispatch_mean(desc->dtype, fda::kCellF64, mean_max, pl.fb, nullptr, nullptr);
-  if (rc == FDA_OK && (desc->variants & FDA_VARIANT_SKETCH)) {
-    rc = dispatch_any(desc->dtype, fda::kCellI64, wide_max, pl.fb, nullptr, nullptr);
-    if (rc == FDA_OK) rc = dispatch_any(desc->dtype, fda::kCellF64, wide_max, pl.fb, nullptr, nullptr);
-    if (rc == FDA_OK &&
-        hipFuncSetAttribute(reinterpret_cast<const void*>(fda::cell_count_kernel),
-                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)lds - 1024) != hipSuccess)   // the kernel also has a little static LDS
-      rc = fail(FDA_EHIP, "hipFuncSetAttribute(cell_count_kernel) failed");
-  }
+  narrow_max.lds_bytes = mean_max.lds_bytes = lds;
+  rc = dispatch_any(desc->dtype, narrow_max, pl.narrow_fb, nullptr, nullptr);
+  if (rc == FDA_OK) rc = dispatch_mean(desc->dtype, mean_max, pl.fb, nullptr, nullptr);
   if (rc != FDA_OK) {
     delete c;
     return rc;
@@ -721,10 +675,10 @@ int fda_last_state_path(fda_ctx* ctx, int32_t* path, void* stream) {
   if (ctx == nullptr || path == nullptr) return fail(FDA_EINVAL, "NULL argument");
   if (!(ctx->desc.variants & FDA_VARIANT_SKETCH)) { *path = -1; return FDA_OK; }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  fda::ScaleInfo info;
-  FDA_HIP(hipMemcpyAsync(&info, ctx->ws + ctx->plan.off_scale, sizeof(info), hipMemcpyDeviceToHost, st));
+  fda::PathRecord rec;
+  FDA_HIP(hipMemcpyAsync(&rec, path_record(ctx, false), sizeof(rec), hipMemcpyDeviceToHost, st));
   FDA_HIP(hipStreamSynchronize(st));
-  *path = info.overflow64 ? 2 : (info.flag32 ? 1 : 0);
+  *path = rec.last;
   return FDA_OK;
 }
 
@@ -732,11 +686,10 @@ int fda_last_mean_state_path(fda_ctx* ctx, int32_t* path, void* stream) {
   if (ctx == nullptr || path == nullptr) return fail(FDA_EINVAL, "NULL argument");
   if (!(ctx->desc.variants & FDA_VARIANT_SKETCH)) { *path = -1; return FDA_OK; }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  fda::ScaleInfo info;
-  FDA_HIP(hipMemcpyAsync(&info, ctx->ws + ctx->plan.off_scale + sizeof(fda::ScaleInfo), sizeof(info),
-                         hipMemcpyDeviceToHost, st));
+  fda::PathRecord rec;
+  FDA_HIP(hipMemcpyAsync(&rec, path_record(ctx, true), sizeof(rec), hipMemcpyDeviceToHost, st));
   FDA_HIP(hipStreamSynchronize(st));
-  *path = info.flagm ? 1 : 0;
+  *path = rec.last;
   return FDA_OK;
 }
 
@@ -779,8 +732,8 @@ int fda_get_plan(const fda_ctx* ctx, fda_plan_info* out) {
   return FDA_OK;
 }
 
-int fda_local_state(fda_ctx* ctx, const void* w, const float* w_t0, const float* xi,
-                    float* state, void* stream) {
+static int local_state(fda_ctx* ctx, const void* w, const float* w_t0, const float* xi, float* state,
+                       const fda::EstimateArgs* est, void* stream) {
   int rc = check_state_args(ctx, w, w_t0, xi, state);
   if (rc != FDA_OK) return rc;
   const fda_desc& d = ctx->desc;
@@ -789,56 +742,41 @@ int fda_local_state(fda_ctx* ctx, const void* w, const float* w_t0, const float*
   const bool sk = (d.variants & FDA_VARIANT_SKETCH) != 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
 
-  auto params_for = [&](const Split& sp) {
-    fda::StateParams prm;
-    prm.w = w; prm.w_t0 = w_t0; prm.xi = xi;
-    prm.row_stride = d.row_stride; prm.d = d.d; prm.chunk = sp.chunk;
-    prm.K = d.K; prm.l = sk ? d.l : 0; prm.m = sk ? d.m : 0;
-    prm.G = sp.G; prm.R = sp.R; prm.P = sp.P; prm.stride = sp.stride;
-    prm.do_lin = lin; prm.do_sk = sk;
-    prm.vec_ok = kVecOk;
-    prm.part_np = reinterpret_cast<double*>(ctx->ws + pl.off_np);
-    prm.part_sk = ctx->ws + pl.off_sk;
-    prm.scale = reinterpret_cast<fda::ScaleInfo*>(ctx->ws + pl.off_scale);
-    prm.table = reinterpret_cast<const uint16_t*>(ctx->ws + pl.off_table);
-    prm.dpad = pl.dpad;
-    prm.grp = &sp == &pl.narrow ? pl.grp : 1;
-    prm.coef = ctx->coef;
-    return prm;
-  };
-  const fda::StateParams prm32 = params_for(pl.narrow);
-  const fda::StateParams prm64 = params_for(pl.wide);
+  const Split& sp = pl.narrow;
+  fda::StateParams prm;
+  prm.w = w; prm.w_t0 = w_t0; prm.xi = xi;
+  prm.row_stride = d.row_stride; prm.d = d.d; prm.chunk = sp.chunk;
+  prm.K = d.K; prm.l = sk ? d.l : 0; prm.m = sk ? d.m : 0;
+  prm.G = sp.G; prm.R = sp.R; prm.P = sp.P; prm.shrink = sp.shrink;
+  prm.do_lin = lin; prm.do_sk = sk;
+  prm.vec_ok = kVecOk;
+  prm.part_np = reinterpret_cast<double*>(ctx->ws + pl.off_np);
+  prm.part_sk = ctx->ws + pl.off_sk;
+  prm.units = reinterpret_cast<fda::CellUnit*>(ctx->ws + pl.off_units);
+  prm.path = path_record(ctx, false);
+  prm.table = reinterpret_cast<const uint16_t*>(ctx->ws + pl.off_table);
+  prm.dpad = pl.dpad;
+  prm.grp = pl.grp;
 
-  if (sk) {
-    rc = prepare_sketch(ctx, w, w_t0, prm32.scale, false, st);
-    if (rc != FDA_OK) return rc;
-  }
+  rc = clear_tickets_once(ctx, st);
+  if (rc == FDA_OK && sk) rc = prepare_sketch(ctx, false, st);
+  if (rc != FDA_OK) return rc;
   int slot = -1;
   rc = prof_begin(ctx, st, &slot);
   if (rc != FDA_OK) return rc;
-  rc = dispatch_any(d.dtype, fda::kCellI32, pl.narrow, pl.narrow_fb, &prm32, st);
+  rc = dispatch_any(d.dtype, sp, pl.narrow_fb, &prm, st);
   if (rc != FDA_OK) return rc;
   rc = prof_end(ctx, st, slot);
   if (rc != FDA_OK) return rc;
-  if (sk) {
-    // these two return at once unless the pass before them could not represent the drifts
-    rc = dispatch_any(d.dtype, fda::kCellI64, pl.wide, pl.fb, &prm64, st);
-    if (rc != FDA_OK) return rc;
-    rc = dispatch_any(d.dtype, fda::kCellF64, pl.wide, pl.fb, &prm64, st);
-    if (rc != FDA_OK) return rc;
-  }
-
-  const long long total = (long long)d.K * pl.S;
-  const int blocks = (int)((total + 31) / 32);
-  hipLaunchKernelGGL(fda::merge_kernel, dim3(blocks), dim3(fda::kSmallThreads), 0, st,
-                     prm32.part_np, prm32.part_sk, prm32.scale, state, d.K, (int)pl.cells,
-                     pl.narrow.P, pl.wide.P);
-  FDA_HIP(hipGetLastError());
-  return FDA_OK;
+  return launch_finish(ctx, false, state, est, st);
 }
 
-int fda_mean_state(fda_ctx* ctx, const void* w, const float* w_t0, const float* xi,
-                   float* mean_state, float* w_bar, void* stream) {
+int fda_local_state(fda_ctx* ctx, const void* w, const float* w_t0, const float* xi, float* state, void* stream) {
+  return local_state(ctx, w, w_t0, xi, state, nullptr, stream);
+}
+
+static int mean_state_pass(fda_ctx* ctx, const void* w, const float* w_t0, const float* xi, float* mean_state,
+                           float* w_bar, const fda::EstimateArgs* est, void* stream) {
   int rc = check_state_args(ctx, w, w_t0, xi, mean_state);
   if (rc != FDA_OK) return rc;
   const fda_desc& d = ctx->desc;
@@ -863,62 +801,66 @@ int fda_mean_state(fda_ctx* ctx, const void* w, const float* w_t0, const float* 
   prm.w_bar = w_bar;
   prm.part_np = reinterpret_cast<double*>(ctx->ws + pl.off_np);
   prm.part_sk = ctx->ws + pl.off_sk;
-  prm.scale = reinterpret_cast<fda::ScaleInfo*>(ctx->ws + pl.off_scale) + 1;
+  prm.units = reinterpret_cast<fda::CellUnit*>(ctx->ws + pl.off_units);
+  prm.path = path_record(ctx, true);
   prm.table = reinterpret_cast<const uint16_t*>(ctx->ws + pl.off_mean_table);
   prm.dpad = pl.dpad;
 
-  if (sk) {
-    rc = prepare_sketch(ctx, w, w_t0, prm.scale, true, st);
-    if (rc != FDA_OK) return rc;
-  }
+  rc = clear_tickets_once(ctx, st);
+  if (rc == FDA_OK && sk) rc = prepare_sketch(ctx, true, st);
+  if (rc != FDA_OK) return rc;
   int slot = -1;
   rc = prof_begin(ctx, st, &slot);
   if (rc != FDA_OK) return rc;
-  rc = dispatch_mean(d.dtype, fda::kCellI64, ms, pl.fb, &prm, st);
+  rc = dispatch_mean(d.dtype, ms, pl.fb, &prm, st);
   if (rc != FDA_OK) return rc;
   rc = prof_end(ctx, st, slot);
   if (rc != FDA_OK) return rc;
-  if (sk) {
-    // returns at once unless a drift was too large for the integers
-    rc = dispatch_mean(d.dtype, fda::kCellF64, ms, pl.fb, &prm, st);
-    if (rc != FDA_OK) return rc;
-  }
-  const int blocks = (int)((pl.S + 1 + 31) / 32);
-  hipLaunchKernelGGL(fda::merge_mean_kernel, dim3(blocks), dim3(fda::kSmallThreads), 0, st,
-                     prm.part_np, prm.part_sk, prm.scale, mean_state,
-                     reinterpret_cast<double*>(ctx->ws + pl.off_dnorm), d.K, (int)pl.cells, ms.P);
-  FDA_HIP(hipGetLastError());
+  return launch_finish(ctx, true, mean_state, est, st);
+}
+
+int fda_mean_state(fda_ctx* ctx, const void* w, const float* w_t0, const float* xi, float* mean_state, float* w_bar,
+                   void* stream) {
+  return mean_state_pass(ctx, w, w_t0, xi, mean_state, w_bar, nullptr, stream);
+}
+
+// The argument checks of an estimate, and what its kernels take.
+static int estimate_args(const fda_ctx* ctx, int rows, double theta, double tie_tol, fda_estimate* out_dev,
+                         fda::EstimateArgs* args) {
+  if (ctx == nullptr || out_dev == nullptr) return fail(FDA_EINVAL, "NULL argument");
+  if (reinterpret_cast<uintptr_t>(out_dev) % 8 != 0) return fail(FDA_EINVAL, "out_dev must be 8-byte aligned");
+  if (!(tie_tol >= 0.0)) return fail(FDA_EINVAL, "tie_tol must be >= 0");
+  const fda_desc& d = ctx->desc;
+  const bool sk = (d.variants & FDA_VARIANT_SKETCH) != 0;
+  *args = {d.variants, sk ? d.l : 0, sk ? d.m : 1, rows, d.eps, theta, tie_tol, out_dev};
+  return FDA_OK;
+}
+
+static int copy_result(fda_estimate* out_host, const fda_estimate* out_dev, hipStream_t st) {
+  FDA_HIP(hipMemcpyAsync(out_host, out_dev, sizeof(fda_estimate), hipMemcpyDeviceToHost, st));
+  FDA_HIP(hipStreamSynchronize(st));
   return FDA_OK;
 }
 
 static int estimate_rows(fda_ctx* ctx, const float* state, int rows, int mean_mode, double theta, double tie_tol,
                          fda_estimate* out_dev, fda_estimate* out_host, void* stream) {
-  if (ctx == nullptr || state == nullptr || out_dev == nullptr)
-    return fail(FDA_EINVAL, "NULL argument");
-  if (reinterpret_cast<uintptr_t>(out_dev) % 8 != 0) return fail(FDA_EINVAL, "out_dev must be 8-byte aligned");
-  int rcd = check_device(ctx);
-  if (rcd != FDA_OK) return rcd;
-  if (!(tie_tol >= 0.0)) return fail(FDA_EINVAL, "tie_tol must be >= 0");
+  if (state == nullptr) return fail(FDA_EINVAL, "NULL argument");
+  fda::EstimateArgs args;
+  int rc = estimate_args(ctx, rows, theta, tie_tol, out_dev, &args);
+  if (rc != FDA_OK) return rc;
+  rc = check_device(ctx);
+  if (rc != FDA_OK) return rc;
   const fda_desc& d = ctx->desc;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const bool sk = (d.variants & FDA_VARIANT_SKETCH) != 0;
-  const int bpr = (d.m + fda::kEstCols - 1) / fda::kEstCols;
-  const int eblocks = sk ? d.l * bpr : 1;
-  int rc = clear_tickets_once(ctx, st);
+  const int eblocks = args.l > 0 ? args.l * ((d.m + fda::kEstCols - 1) / fda::kEstCols) : 1;
+  rc = clear_tickets_once(ctx, st);
   if (rc != FDA_OK) return rc;
-  const fda::ScaleInfo* scale =
-      reinterpret_cast<const fda::ScaleInfo*>(ctx->ws + ctx->plan.off_scale) + (mean_mode ? 1 : 0);
-  hipLaunchKernelGGL(fda::estimate_kernel, dim3(eblocks), dim3(fda::kSmallThreads), 0, st, state, rows,
-                     sk ? d.l : 0, sk ? d.m : 1, d.variants, d.eps, theta, tie_tol,
+  hipLaunchKernelGGL(fda::estimate_kernel, dim3(eblocks), dim3(fda::kSmallThreads), 0, st, state, args,
                      reinterpret_cast<double*>(ctx->ws + ctx->plan.off_est),
-                     reinterpret_cast<unsigned int*>(ctx->ws + ctx->plan.off_ticket) + 1, scale, mean_mode,
-                     out_dev);
+                     reinterpret_cast<unsigned int*>(ctx->ws + ctx->plan.off_ticket),
+                     path_record(ctx, mean_mode != 0));
   FDA_HIP(hipGetLastError());
-  if (out_host != nullptr) {
-    FDA_HIP(hipMemcpyAsync(out_host, out_dev, sizeof(fda_estimate), hipMemcpyDeviceToHost, st));
-    FDA_HIP(hipStreamSynchronize(st));
-  }
-  return FDA_OK;
+  return out_host != nullptr ? copy_result(out_host, out_dev, st) : FDA_OK;
 }
 
 int fda_estimate_variance(fda_ctx* ctx, const float* state, double theta, double tie_tol,
@@ -961,10 +903,9 @@ int fda_estimate_variance_static(const float* state, int32_t K, int32_t l, int32
   // the counter must start at zero whatever an earlier call left (a fill kernel, not a memset node)
   hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(1), dim3(64), 0, st, ticket, 1);
   FDA_HIP(hipGetLastError());
-  hipLaunchKernelGGL(fda::estimate_kernel, dim3(eblocks), dim3(fda::kSmallThreads), 0, st, state, K,
-                     sk ? l : 0, sk ? m : 1, variants, eps, theta, tie_tol,
-                     reinterpret_cast<double*>(base), ticket, static_cast<const fda::ScaleInfo*>(nullptr), 0,
-                     out_dev);
+  const fda::EstimateArgs args = {variants, sk ? l : 0, sk ? m : 1, K, eps, theta, tie_tol, out_dev};
+  hipLaunchKernelGGL(fda::estimate_kernel, dim3(eblocks), dim3(fda::kSmallThreads), 0, st, state, args,
+                     reinterpret_cast<double*>(base), ticket, static_cast<const fda::PathRecord*>(nullptr));
   FDA_HIP(hipGetLastError());
   return FDA_OK;
 }
@@ -1105,16 +1046,10 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
       reinterpret_cast<const unsigned char*>(out_dev) +
       (decide_by == FDA_VARIANT_LINEAR ? offsetof(fda_estimate, sync_linear)
                                        : offsetof(fda_estimate, sync_sketch)));
-  int rc;
-  if (mean) {
-    rc = fda_mean_state(ctx, w, w_t0, xi, state, w_bar, stream);
-    if (rc != FDA_OK) return rc;
-    rc = fda_estimate_variance_mean(ctx, state, theta, tie_tol, out_dev, nullptr, stream);
-  } else {
-    rc = fda_local_state(ctx, w, w_t0, xi, state, stream);
-    if (rc != FDA_OK) return rc;
-    rc = fda_estimate_variance(ctx, state, theta, tie_tol, out_dev, nullptr, stream);
-  }
+  int rc = mean ? fda_mean_state(ctx, w, w_t0, xi, state, w_bar, stream) : fda_local_state(ctx, w, w_t0, xi, state, stream);
+  if (rc != FDA_OK) return rc;
+  rc = mean ? fda_estimate_variance_mean(ctx, state, theta, tie_tol, out_dev, nullptr, stream)
+            : fda_estimate_variance(ctx, state, theta, tie_tol, out_dev, nullptr, stream);
   if (rc != FDA_OK) return rc;
   if (w_bar != nullptr) {
     rc = fda_sync_from_mean(ctx, w, w_t0, w_prev, xi, w_bar, pred, stream);
@@ -1123,12 +1058,7 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
                        : fda_sync(ctx, w, w_t0, w_prev, pred, stream);
   }
   if (rc != FDA_OK) return rc;
-  if (out_host != nullptr) {
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    FDA_HIP(hipMemcpyAsync(out_host, out_dev, sizeof(fda_estimate), hipMemcpyDeviceToHost, st));
-    FDA_HIP(hipStreamSynchronize(st));
-  }
-  return FDA_OK;
+  return out_host != nullptr ? copy_result(out_host, out_dev, static_cast<hipStream_t>(stream)) : FDA_OK;
 }
 
 }  // extern "C"

@@ -29,25 +29,20 @@ struct HashCoef {
   uint32_t c[FDA_MAX_SKETCH_ROWS][2][4];     // [row][bucket|sign][power of j]
 };
 
-// Which kind of LDS sketch cell a state kernel accumulates into.
+// What the sketch partials of one workgroup of a state pass are stored as.
 enum CellKind { kCellI32 = 0, kCellI64 = 1, kCellF64 = 2 };
 
-// Fixed-point scales of one fda_local_state call, chosen on the device from a sample of the
-// drifts (scale_kernel) and read by the state and merge kernels, and the flags that send a
-// call from the 32-bit integer cells to the 64-bit ones and from those to fp64 cells.
-struct ScaleInfo {
-  double S64, invS64;     // 64-bit cells: a drift u is added as the integer round(u * S64)
-  double invS32;
-  float S32;              // 32-bit cells: round(u * S32)
-  float bound32;          // every |u| must stay below this for the 32-bit cells to be valid
-  float bound64;          // ... and below this for the 64-bit cells
-  int flag32;             // set: the 32-bit result is void (range, or a cell wrapped) -> 64-bit pass
-  int overflow64;         // set: the 64-bit cells cannot hold the drifts either -> fp64 pass
-  int flagm;              // mean-state kernel: set when a drift reached boundm -> its fp64 pass
-  double invSm;
-  float Sm;               // mean-state kernel: a drift u enters as the integer round(u * Sm)
-  float boundm;           // ... and every |u| must stay below this
+// The unit of one workgroup's sketch partials: every stored value times `unit` is a sum of drifts.
+struct CellUnit {
+  double unit;
+  int kind;               // CellKind
+  int pad;
 };
+
+// Which kind of cell the state passes of a context ended up using: the largest CellKind of any
+// workgroup.  `now` collects it while a pass runs (and is zero otherwise), `last` is the result of
+// the last pass that has been merged.
+struct PathRecord { int now, last; };
 
 struct StateParams {
   const void* w;
@@ -62,17 +57,18 @@ struct StateParams {
   int G;                  // worker groups
   int R;                  // sketch-row groups (workgroups of one worker group share the data)
   int P;                  // coordinate partitions
-  int stride;             // 8-byte-cell passes: LDS cells per bucket (>= worker slots of the group, odd)
+  int shrink;             // the unit of the 32-bit cells is this many bits coarser (cells that take many terms)
   int do_lin;
   int do_sk;
   int vec_ok;             // whole-vector loads and stores may be used (pointers are element-aligned)
   double* part_np;        // [P][K][2]
-  void* part_sk;          // [P][K][l*m] 8-byte words: int64 (integer cells) or double (fp64 cells)
-  ScaleInfo* scale;
-  const uint16_t* table;  // [R][dpad] records of the tabulated hash (32-bit-cell pass only)
+  unsigned char* part_sk; // [P][K][l*m] places of 8 bytes; a row group's share starts at its first cell's place
+                          // and holds int32 values back to back, or int64 / double values (CellUnit::kind)
+  CellUnit* units;        // [P][G][R]
+  PathRecord* path;
+  const uint16_t* table;  // [R][dpad] records of the tabulated hash
   long long dpad;
   int grp;                // rows per placement group of the table (1: a field is a bucket of its own row)
-  HashCoef coef;          // the fallback passes evaluate the hash themselves
 };
 
 struct bf16_t { uint16_t bits; };
@@ -103,7 +99,7 @@ __device__ __forceinline__ VecT load_vec_hint(const void* p) {
   if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const VecT*>(p));
   else return *reinterpret_cast<const VecT*>(p);
 }
-typedef uint32_t u32x2_a8 __attribute__((ext_vector_type(2)));                // 8-byte aligned pair (table words)
+typedef uint32_t u32x4_a16 __attribute__((ext_vector_type(4)));               // 16-byte aligned (LDS)
 constexpr bool kNtSlab = FDA_NT_SLAB != 0;
 constexpr bool kNtShared = FDA_NT_SHARED != 0;
 
@@ -307,6 +303,83 @@ __device__ __forceinline__ float raw_elem(const uint32_t (&r)[2], int v) {      
   return __uint_as_float((v & 1) ? (r[v >> 1] & 0xffff0000u) : (r[v >> 1] << 16));
 }
 
+// ---- the fixed-point unit of a workgroup -------------------------------------------------------
+// A workgroup adds drifts to its sketch cells as integers round(u * 2^e).  It chooses 2^e itself, from a
+// sample of the drifts it is about to stream: 512 of its coordinates (runs of 8, which share their cache
+// lines, evenly spaced over the chunk) of up to 8 of its workers, one coordinate per thread.  The typical
+// magnitude is the mean of the sample without its largest value, so that one outlier does not coarsen the
+// unit of everything else.  (One unit per call, from a kernel of its own in front of the pass, took 8 to
+// 24 us per call -- cfg1 8, cfg4 24 -- where the workgroups' own samples take 1 to 2.)
+// A sample of nothing but zeros (frozen layers, sparse updates) is repeated over all coordinates.
+constexpr int kSampleRunsGlobal = 4;
+
+// sum and largest |u| of `rounds` * kStateThreads sampled coordinates of [beg, beg + len), NL rows each;
+// row_of(i, t): row i for sample t
+template <int NL, typename T, typename RowOf>
+__device__ __forceinline__ void sample_drifts(RowOf row_of, const float* w0, long long beg, long long len, int rounds,
+                                              float& sum, float& top) {
+  const long long n = (long long)rounds * kStateThreads;
+  for (int q = 0; q < rounds; ++q) {
+    const int t = q * kStateThreads + (int)threadIdx.x;
+    if (len <= n && t >= len) return;
+    const long long j = beg + (len <= n ? (long long)t : (long long)(t >> 3) * (len / (n >> 3)) + (t & 7));
+    const float base = w0[j];
+    float x[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i) x[i] = Slab<T>::load_one(row_of(i, t) + j);
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+      const float u = fabsf(x[i] - base);
+      const bool usable = u < 3.0e38f;                     // not NaN, not infinite
+      top = usable ? fmaxf(top, u) : top;
+      sum += usable ? u : 0.0f;
+    }
+  }
+}
+// every thread: the typical magnitude of the workgroup's sample (0: the sample saw no drift)
+__device__ __forceinline__ double sample_mean(float sum, float top, long long count, double* scratch) {
+  double s = (double)sum;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    s += __shfl_xor(s, o, 64);
+    top = fmaxf(top, __shfl_xor(top, o, 64));
+  }
+  constexpr int kWaves = kStateThreads / 64;
+  float* tops = reinterpret_cast<float*>(scratch + kWaves);
+  if ((threadIdx.x & 63) == 0) { scratch[threadIdx.x >> 6] = s; tops[threadIdx.x >> 6] = top; }
+  __syncthreads();
+  s = 0.0;
+  for (int q = 0; q < kWaves; ++q) { s += scratch[q]; top = fmaxf(top, tops[q]); }
+  __syncthreads();
+  if (count >= 256) { s = fmax(s - (double)top, 0.0); count -= 1; }
+  return s / (double)count;
+}
+// 2^e that maps a typical magnitude to [2^(18-shrink), 2^(19-shrink)): a term is then rounded by at most
+// 2^-(19-shrink) of it and single drifts may reach 2048 to 4096 times it before a term leaves 30 bits (a
+// Student-t(3) tail over 3e9 draws reaches about 1400 times).  0: no such float.
+__device__ __forceinline__ float unit_for(double mean, int shrink) {
+  if (!(mean > 0.0) || !(mean < 1.0e300)) return 0.0f;
+  const int e = 18 - shrink - ilogb(mean);
+  return (e > 120 || e < -120) ? 0.0f : ldexpf(1.0f, e);
+}
+constexpr float kTermBound = 1073741824.0f;              // 2^30: scaled drifts must stay below it
+
+// Scratch behind the cells (`red`): the doubles of the scalar sums (8 waves x kMaxKC slots x 2), then what
+// block_all_max needs beside them.
+constexpr int kRedSums = kStateThreads / 64 * kMaxKC * 2;
+
+// largest value of a float over the workgroup, in every thread
+__device__ __forceinline__ float block_all_max(float v, double* scratch) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  float* tops = reinterpret_cast<float*>(scratch);
+  if ((threadIdx.x & 63) == 0) tops[threadIdx.x >> 6] = v;
+  __syncthreads();
+  for (int q = 0; q < kStateThreads / 64; ++q) v = fmaxf(v, tops[q]);
+  __syncthreads();
+  return v;
+}
+
 // ----------------------------------------------------------------------------------------
 // Algorithm 1 line 6.  Workgroup (p, g, r) streams coordinates [p*chunk, (p+1)*chunk) of the
 // workers of group g exactly once and owns the sketch rows of row group r.  Per tile every
@@ -325,28 +398,24 @@ __device__ __forceinline__ float raw_elem(const uint32_t (&r)[2], int v) {      
 //
 // How the sketch cells accumulate is dictated by the LDS of gfx950.  Measured per CU and clock
 // on random cells: ds_add_f32 0.33 lanes, ds_add_f64 2.8, ds_add_u64 5.5, ds_add_rtn_u32 10.4.
-// So the cells are integers and a drift u is added as round(u * 2^e), with 2^e chosen per call
-// from a sample of the drifts (scale_kernel).  Integer addition is exact: the result
-// does not depend on the order in which lanes and workgroups add, run-to-run bit-identical.
-//   kCellI32  32-bit cells holding sum + 2^30; every add is below 2^30 in magnitude and returns
-//             the old value, which must lie in [0, 2^31) -- top bit clear, i.e. the sum so far in
-//             [-2^30, 2^30): then no add can have wrapped (the final values are held to the same
-//             band when they are flushed).
-//             The mean sampled |u| maps to about 2^18.  Runs on every call and also produces
-//             the scalar components.  A value outside the band, or a drift at or above
-//             ScaleInfo::bound32, raises ScaleInfo::flag32.
-//             With an even number of worker slots the cells of slots 2t and 2t+1 of a bucket are
-//             the low and the high half of one 8-byte word and receive q_lo + 2^32 * q_hi (as a
-//             64-bit two's-complement number) in ONE ds_add_rtn_u64: half the LDS instructions,
-//             measured 1.07 to 1.15 times faster.  While the low half stays inside its band it
-//             neither borrows from nor carries into the high half, so both halves hold exactly
-//             what two 32-bit additions would have left; once it leaves the band its top bit is
-//             seen (by the next addition to the word or by the flush) and the pass is void anyway.
-//   kCellI64  64-bit cells, sketch only, runs only when flag32 is set.  The sampled maximum
-//             maps to qbits - 13 bits, qbits chosen from the exact largest number of terms
-//             of a cell so that no cell can overflow.  A drift at or above bound64 raises
-//             ScaleInfo::overflow64 (noticed by the first pass, which sees every drift).
-//   kCellF64  fp64 cells (ds_add_f64), sketch only, runs only when overflow64 is set.
+// So the cells are integers and a drift u is added as round(u * 2^e), with 2^e chosen by the workgroup
+// from a sample of its drifts (above).  Integer addition is exact: a workgroup's result does not depend
+// on the order in which its lanes add, and the state is run-to-run bit-identical.
+//   32-bit cells holding sum + 2^30; every add is below 2^30 in magnitude and returns
+//   the old value, which must lie in [0, 2^31) -- top bit clear, i.e. the sum so far in
+//   [-2^30, 2^30): then no add can have wrapped (the final values are held to the same
+//   band when they are flushed).
+//   With an even number of worker slots the cells of slots 2t and 2t+1 of a bucket are
+//   the low and the high half of one 8-byte word and receive q_lo + 2^32 * q_hi (as a
+//   64-bit two's-complement number) in ONE ds_add_rtn_u64: half the LDS instructions,
+//   measured 1.07 to 1.15 times faster.  While the low half stays inside its band it
+//   neither borrows from nor carries into the high half, so both halves hold exactly
+//   what two 32-bit additions would have left; once it leaves the band its top bit is
+//   seen (by the next addition to the word or by the flush) and the pass is void anyway.
+// A workgroup that saw a value outside the band, or a drift its terms cannot hold, does its own sketch
+// once more, one worker at a time, into 8-byte cells (redo, below): 64-bit integers whose unit follows from
+// the largest drift of the chunk, or fp64 (ds_add_f64) where the drifts' range is too wide for those.  The
+// other workgroups are not concerned.
 // ----------------------------------------------------------------------------------------
 constexpr uint32_t kCellBias = 0x40000000u;   // a 32-bit cell holds its sum plus 2^30
 
@@ -396,24 +465,14 @@ __device__ __forceinline__ int round_half_up(float x) {
   return q;
 }
 
-template <typename T, int KC, int LR, int CELL, int FB, bool SPLIT = false>
+template <typename T, int KC, int LR, int FB, bool SPLIT = false>
 __global__ void __launch_bounds__(kStateThreads)
 state_kernel(const StateParams prm) {
-  static_assert(!SPLIT || CELL == kCellI32, "sign-split rows: 32-bit cells only");
   constexpr int V = kStateV;
   constexpr long long kTile = (long long)kStateThreads * V;
-  // only the 32-bit-cell pass streams the table; the fallback passes evaluate the hash
-  constexpr bool kTabulated = CELL == kCellI32;
   using Geom = RecGeom<LR, FB>;
-  using Tile = TileRaw<T, KC, LR, FB>;        // the fallback passes leave its records unloaded
+  using Tile = TileRaw<T, KC, LR, FB>;
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  constexpr int kCellBytes = (CELL == kCellI32) ? 4 : 8;
-  if constexpr (CELL == kCellI64) {
-    if (prm.scale->flag32 == 0 || prm.scale->overflow64 != 0) return;
-  }
-  if constexpr (CELL == kCellF64) {
-    if (prm.scale->overflow64 == 0) return;
-  }
 
   // XCD-aware placement: consecutive workgroup ids go round-robin over the 8 XCDs, so the
   // G*R workgroups that read the same coordinates (and share w_t0 / xi / slab rows / table
@@ -437,45 +496,32 @@ state_kernel(const StateParams prm) {
   int kstart, kcnt, rstart = 0, rcnt = 0;
   group_range(prm.K, prm.G, g, &kstart, &kcnt);
   if (prm.do_sk) group_range(prm.l, prm.R, r, &rstart, &rcnt);
-  const bool scalars = (CELL == kCellI32) && (r == 0);
-  bool sketch = prm.do_sk != 0;
-  if constexpr (CELL == kCellI32) {
-    // a later pass will redo every sketch partial: only the scalar components are left to do
-    if (sketch && prm.scale->flag32 != 0) {
-      if (!scalars) return;
-      sketch = false;
-    }
-  }
+  const bool scalars = r == 0;
 
-  // 32-bit cells: cells32_* layout, KC words per bucket; 8-byte cells: prm.stride cells per bucket
-  constexpr bool kPaired = CELL == kCellI32 && KC % 2 == 0;
-  constexpr bool kSkewed = CELL == kCellI32 && cells32_skewed(KC);
-  const uint32_t stride_bytes = CELL == kCellI32 ? 4u * KC : (uint32_t)prm.stride * kCellBytes;
+  // cells32_* layout, KC words per bucket
+  constexpr bool kPaired = KC % 2 == 0;
+  constexpr bool kSkewed = cells32_skewed(KC);
+  constexpr uint32_t stride_bytes = 4u * KC;
   const int cells = rcnt * prm.m;                      // cells this workgroup owns
   const int mrow = SPLIT ? 2 * prm.m : prm.m;          // buckets of one LDS row
   const uint32_t row_words32 = cells32_row_words(mrow, KC);
-  const uint32_t dummy_base = CELL == kCellI32 ? (uint32_t)rcnt * row_words32 * 4u : (uint32_t)cells * stride_bytes;
-  const int lds_cells = !sketch ? 0
-                        : CELL == kCellI32 ? (int)cells32_words(rcnt, mrow, KC) : (cells + kDummyCells) * prm.stride;
-  double* red = reinterpret_cast<double*>(lds_raw + (((size_t)lds_cells * kCellBytes + 15) & ~(size_t)15));
+  const uint32_t dummy_base = (uint32_t)rcnt * row_words32 * 4u;
+  const int lds_quads = prm.do_sk ? ((int)cells32_words(rcnt, mrow, KC) + 3) / 4 : 0;       // 16 bytes each
+  double* red = reinterpret_cast<double*>(lds_raw + (size_t)lds_quads * 16);
 
   const int tid = threadIdx.x;
-  if constexpr (CELL == kCellI32) {
-    uint32_t* c32 = reinterpret_cast<uint32_t*>(lds_raw);
-    for (int t = tid; t < lds_cells; t += kStateThreads) c32[t] = kCellBias;     // sum 0
-  } else {
-    unsigned long long* c64 = reinterpret_cast<unsigned long long*>(lds_raw);
-    for (int t = tid; t < lds_cells; t += kStateThreads) c64[t] = 0ull;         // integer 0 and 0.0
+  {
+    u32x4_a16* c = reinterpret_cast<u32x4_a16*>(lds_raw);
+    const u32x4_a16 zero = {kCellBias, kCellBias, kCellBias, kCellBias};      // sum 0
+    for (int t = tid; t < lds_quads; t += kStateThreads) c[t] = zero;
   }
-  __syncthreads();
 
   double dn[KC], dp[KC];
 #pragma unroll
   for (int k = 0; k < KC; ++k) { dn[k] = 0.0; dp[k] = 0.0; }
 
   // per worker slot: its slab row (spare slots repeat the last worker);
-  // per row slot: its LDS base (spare slots: the dummy region, whose table fields -- and, in the
-  // fallback passes, masked buckets -- stay below kDummyCells)
+  // per row slot: its LDS base (spare slots: the dummy region, whose table fields stay below kDummyCells)
   const T* wrow[KC];
 #pragma unroll
   for (int k = 0; k < KC; ++k)
@@ -485,8 +531,7 @@ state_kernel(const StateParams prm) {
 #pragma unroll
   for (int i = 0; i < LR; ++i) {
     // (placed rows: the base of the slot's group, the field counts buckets from there)
-    if constexpr (CELL == kCellI32) rowbase[i] = i < rcnt ? (uint32_t)(i / prm.grp * prm.grp) * row_words32 * 4u : dummy_base;
-    else rowbase[i] = i < rcnt ? (uint32_t)(i * prm.m) * stride_bytes : dummy_base;
+    rowbase[i] = i < rcnt ? (uint32_t)(i / prm.grp * prm.grp) * row_words32 * 4u : dummy_base;
   }
   // this row group's records: [r][dpad] records of Geom::kWords 16-bit words
   const uint32_t* const recs =
@@ -500,15 +545,36 @@ state_kernel(const StateParams prm) {
   const float* const w0p = prm.w_t0;
   const float* const xip = lin ? prm.xi : prm.w_t0;   // without LinearFDA: any readable vector
 
-  double S64 = 1.0;
+  // the unit of this workgroup's sketch terms
   float S32 = 1.0f, amax = 0.0f;
-  uint32_t seen_or = 0u;            // OR of every 32-bit cell value this lane's adds returned
-  if (prm.do_sk) { S64 = prm.scale->S64; S32 = prm.scale->S32; }
+  uint32_t seen_or = 0u;            // OR of every cell value this lane's adds returned
+  double typical = 0.0;             // mean sampled |u|
+  bool sketch = false;
+  if (prm.do_sk) {
+    const long long len = cend - cbeg;
+    if (len > 0) {
+      auto row_of = [&](int i, int) { return wrow[i]; };
+      float sum = 0.0f, top = 0.0f;
+      sample_drifts<KC, T>(row_of, w0p, cbeg, len, 1, sum, top);
+      typical = sample_mean(sum, top, (len < kStateThreads ? len : kStateThreads) * KC, red);
+      if (typical == 0.0) {
+        sum = top = 0.0f;
+        sample_drifts<KC, T>(row_of, w0p, 0, dlim, kSampleRunsGlobal, sum, top);
+        typical = sample_mean(sum, top, (dlim < kSampleRunsGlobal * kStateThreads ? dlim : kSampleRunsGlobal * kStateThreads) * KC, red);
+      }
+    }
+    const float unit = unit_for(typical, prm.shrink);
+    sketch = unit != 0.0f;          // otherwise the pass only notes whether there is any drift at all
+    if (sketch) S32 = unit;
+  }
+  __syncthreads();                  // (the cells are clear)
 
-  // SC: this workgroup also produces the scalar components; SK: it accumulates sketch rows.
-  auto run = [&](auto sc_tag, auto sk_tag) {
+  // SC: this workgroup also produces the scalar components; SK: it accumulates sketch rows; MX: it notes the
+  // largest scaled drift.
+  auto run = [&](auto sc_tag, auto sk_tag, auto mx_tag) {
     constexpr bool SC = decltype(sc_tag)::value;
     constexpr bool SK = decltype(sk_tag)::value;
+    constexpr bool MX = decltype(mx_tag)::value;
 
     // whole vectors, no tests: for tiles that lie entirely inside the chunk
     auto load_fast = [&](Tile& t, long long j0) {
@@ -524,7 +590,7 @@ state_kernel(const StateParams prm) {
           t.w[k][0] = q.x; t.w[k][1] = q.y;
         }
       }
-      if constexpr (SK && kTabulated)
+      if constexpr (SK)
         load_rec_block<Geom::kDwords, kNtShared>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, t.rec);
     };
     // element by element, every access tested: ragged tails and slabs without dword alignment
@@ -553,7 +619,7 @@ state_kernel(const StateParams prm) {
         }
       }
       // the table is padded to dpad (whole blocks of 256 coordinates): always whole records
-      if constexpr (SK && kTabulated)
+      if constexpr (SK)
         load_rec_block<Geom::kDwords, false>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, t.rec);
     };
 
@@ -577,27 +643,26 @@ state_kernel(const StateParams prm) {
     };
 
     auto consume = [&](const Tile& t, long long j0) {
-      uint32_t pend_old[KC];                  // 32-bit cells: the last batch not yet examined
+      uint32_t pend_old[KC];                  // the last batch of returned values, not yet examined
       bool have_pending = false;
 #pragma unroll
       for (int v = 0; v < V; ++v) {
-        // The 32-bit-cell pass works on u * S32 throughout: S32 is a power of two, so
+        // The pass works on u * S32 throughout: S32 is a power of two, so
         // fma(w, S32, -w_t0 * S32) is exactly (w - w_t0 as fp32 rounds it) * S32, the scalar
         // sums come out multiplied by S32^2 and S32 (undone exactly at the end), and the
-        // fixed-point term is one conversion away.  (The fallback passes keep the plain drift.)
+        // fixed-point term is one conversion away.
         float u[KC];
-        const float w0s = (CELL == kCellI32) ? t.w0[v] * S32 : t.w0[v];
+        const float w0s = t.w0[v] * S32;
 #pragma unroll
         for (int k = 0; k < KC; ++k) {
-          if constexpr (CELL == kCellI32) u[k] = fmaf(raw_elem(t.w[k], v), S32, -w0s);
-          else u[k] = raw_elem(t.w[k], v) - w0s;
+          u[k] = fmaf(raw_elem(t.w[k], v), S32, -w0s);
           if constexpr (SC) {
             sn[k] = fmaf(u[k], u[k], sn[k]);
             sp[k] = fmaf(t.x[v], u[k], sp[k]);
-            amax = fmaxf(amax, fabsf(u[k]));
           }
+          if constexpr (MX) amax = fmaxf(amax, fabsf(u[k]));
         }
-        if constexpr (SK && CELL == kCellI32) {
+        if constexpr (SK) {
           uint32_t q[KC], nq[KC];
 #pragma unroll
           for (int k = 0; k < KC; ++k) {
@@ -638,7 +703,7 @@ state_kernel(const StateParams prm) {
 #pragma unroll
               for (int k = 0; k < KC; ++k) old[k] = atomicAdd(cell + k, neg ? nq[k] : q[k]);
             }
-            // Every add is below 2^30 in magnitude (ScaleInfo::bound32) and a cell holds its sum
+            // Every add is below 2^30 in magnitude (kTermBound) and a cell holds its sum
             // plus 2^30, so a cell cannot wrap in an add that found it below 2^31 (sum so far in
             // [-2^30, 2^30)): if the top bit of every value ever returned was clear, no cell
             // wrapped.  The returned values are OR-ed together (a three-operand OR takes two of
@@ -654,39 +719,8 @@ state_kernel(const StateParams prm) {
             have_pending = true;
           }
         }
-        if constexpr (SK && CELL != kCellI32) {
-          // fallback passes: the hash is evaluated here (two cubics mod p per row and coordinate)
-          unsigned long long q[KC], nq[KC];
-          if constexpr (CELL == kCellI64) {
-#pragma unroll
-            for (int k = 0; k < KC; ++k) {
-              const double y = fma((double)u[k], S64, kRoundMagic);           // round to integer
-              q[k] = (unsigned long long)(__double_as_longlong(y) - __double_as_longlong(kRoundMagic));
-              nq[k] = 0ull - q[k];
-            }
-          }
-          const long long j = j0 + v;
-          const uint32_t key = j < dlim ? (uint32_t)j : 0u;                  // past the end the drift is zero
-#pragma unroll
-          for (int i = 0; i < LR; ++i) {
-            const bool live = i < rcnt;
-            const uint32_t h = hash_entry(prm.coef, rstart + (live ? i : 0), key, (uint32_t)prm.m);
-            const uint32_t bucket = live ? (h & 0x7fffu) : (h & (uint32_t)(kDummyCells - 1));
-            const uint32_t off = __umul24(bucket, stride_bytes) + rowbase[i];
-            const bool neg = (h & 0x8000u) != 0u;
-            if constexpr (CELL == kCellI64) {
-              unsigned long long* cell = reinterpret_cast<unsigned long long*>(lds_raw + off);
-#pragma unroll
-              for (int k = 0; k < KC; ++k) atomicAdd(cell + k, neg ? nq[k] : q[k]);
-            } else {
-              double* cell = reinterpret_cast<double*>(lds_raw + off);
-#pragma unroll
-              for (int k = 0; k < KC; ++k) atomicAdd(cell + k, neg ? -(double)u[k] : (double)u[k]);
-            }
-          }
-        }
       }
-      if constexpr (SK && CELL == kCellI32) {
+      if constexpr (SK) {
         if (have_pending) {
 #pragma unroll
           for (int k = 0; k < KC; ++k) seen_or |= pend_old[k];
@@ -723,26 +757,16 @@ state_kernel(const StateParams prm) {
     widen();
   };
   if (scalars) {
-    if (sketch) run(std::true_type{}, std::true_type{});
-    else run(std::true_type{}, std::false_type{});
-  } else {
-    run(std::false_type{}, std::true_type{});
+    if (sketch) run(std::true_type{}, std::true_type{}, std::true_type{});
+    else if (prm.do_sk) run(std::true_type{}, std::false_type{}, std::true_type{});
+    else run(std::true_type{}, std::false_type{}, std::false_type{});
+  } else if (sketch) {
+    run(std::false_type{}, std::true_type{}, std::true_type{});
   }
 
-  if constexpr (CELL == kCellI32) {
-    if (prm.do_sk) {
-      if (scalars) {
-        // drifts the integer cells cannot hold (any drift at all when the sample saw none)
-        const float b32 = prm.scale->bound32, b64 = prm.scale->bound64;
-        amax = amax * (1.0f / S32);              // back to the drift's own unit (exact: a power of two)
-        const bool bad32 = b32 > 0.0f ? !(amax < b32) : (amax > 0.0f);
-        const bool bad64 = b64 > 0.0f ? !(amax < b64) : (amax > 0.0f);
-        if (bad32 || bad64) prm.scale->flag32 = 1;
-        if (bad64) prm.scale->overflow64 = 1;
-      }
-      if ((seen_or & 0x80000000u) != 0u) prm.scale->flag32 = 1;
-    }
-  }
+  // the 32-bit cells are void: a drift beyond their terms, a cell that left its band, or any drift at all
+  // where the sample saw none
+  bool bad = prm.do_sk && (sketch ? (!(amax < kTermBound) || (seen_or & 0x80000000u) != 0u) : (!scalars || amax > 0.0f));
 
   // ---- workgroup reduction of the scalar components (fixed shape) ---------------------
   const int lane = tid & 63, wave = tid >> 6;
@@ -765,39 +789,97 @@ state_kernel(const StateParams prm) {
     const double inv = 1.0 / (double)S32;
     prm.part_np[((size_t)p * prm.K + kstart + k) * 2 + q] = s * (q == 0 ? inv * inv : inv);
   }
+  if (!prm.do_sk) return;
   // ---- flush the LDS sketch to this workgroup's slice of the partial buffer -----------
-  if (sketch) {
-    const int allcells = prm.l * prm.m;
-    unsigned long long* out = reinterpret_cast<unsigned long long*>(prm.part_sk);
-    bool left_band = false;
-    if constexpr (CELL == kCellI32) {
-      // a wave takes one (row, worker) at a time, its lanes the buckets: no divisions per cell
-      const uint32_t* words = reinterpret_cast<const uint32_t*>(lds_raw);
-      for (int combo = wave; combo < rcnt * kcnt; combo += kWaves) {
-        const int i = combo / kcnt, k = combo - i * kcnt;
-        const uint32_t* row = words + (size_t)i * row_words32 + k;
-        unsigned long long* dst = out + ((size_t)p * prm.K + kstart + k) * allcells + (size_t)(rstart + i) * prm.m;
-        for (int bkt = lane; bkt < prm.m; bkt += 64) {
-          const uint32_t word = row[cells32_bucket_word((uint32_t)bkt, KC)];
-          left_band = left_band || (word & 0x80000000u) != 0u;      // the last additions are examined here
-          long long sum = (long long)(int)(word - kCellBias);
-          if constexpr (SPLIT) {
-            const uint32_t minus = row[cells32_bucket_word((uint32_t)(bkt + prm.m), KC)];
-            left_band = left_band || (minus & 0x80000000u) != 0u;
-            sum -= (long long)(int)(minus - kCellBias);
-          }
-          dst[bkt] = (unsigned long long)sum;
+  const size_t allcells = (size_t)prm.l * prm.m;
+  // (worker kstart + k's share begins at place [(p * K + kstart + k) * allcells + rstart * m])
+  unsigned char* const share = prm.part_sk + (((size_t)p * prm.K + kstart) * allcells + (size_t)rstart * prm.m) * 8;
+  {
+    // a wave takes one (row, worker) at a time, its lanes the buckets: no divisions per cell
+    const uint32_t* words = reinterpret_cast<const uint32_t*>(lds_raw);
+    for (int combo = wave; combo < rcnt * kcnt; combo += kWaves) {
+      const int i = combo / kcnt, k = combo - i * kcnt;
+      const uint32_t* row = words + (size_t)i * row_words32 + k;
+      int* dst = reinterpret_cast<int*>(share + (size_t)k * allcells * 8) + i * prm.m;
+      for (int bkt = lane; bkt < prm.m; bkt += 64) {
+        const uint32_t word = row[cells32_bucket_word((uint32_t)bkt, KC)];
+        bad = bad || (word & 0x80000000u) != 0u;      // the last additions are examined here
+        int sum = (int)(word - kCellBias);
+        if constexpr (SPLIT) {                        // two sums inside [-2^30, 2^30): the difference fits
+          const uint32_t minus = row[cells32_bucket_word((uint32_t)(bkt + prm.m), KC)];
+          bad = bad || (minus & 0x80000000u) != 0u;
+          sum -= (int)(minus - kCellBias);
         }
-      }
-    } else {
-      for (int t = tid; t < kcnt * cells; t += kStateThreads) {
-        const int k = t / cells, c = t - k * cells;
-        out[((size_t)p * prm.K + kstart + k) * allcells + (size_t)rstart * prm.m + c] =
-            reinterpret_cast<const unsigned long long*>(lds_raw)[(size_t)c * prm.stride + k];
+        dst[bkt] = sum;
       }
     }
-    if constexpr (CELL == kCellI32) {
-      if (left_band) prm.scale->flag32 = 1;
+  }
+  CellUnit* const my_unit = prm.units + ((size_t)p * prm.G + g) * prm.R + r;
+  const bool again = block_all_max(bad ? 1.0f : 0.0f, red + kRedSums) != 0.0f;
+  if (tid == 0) *my_unit = CellUnit{1.0 / (double)S32, kCellI32, 0};
+  if (!again) return;
+
+  // ---- redo: the sketch of this workgroup once more, one worker at a time, into 8-byte cells --------
+  const T* const wbase = reinterpret_cast<const T*>(prm.w) + (long long)kstart * prm.row_stride;
+  float top = 0.0f;                                    // the largest drift of the chunk
+  for (int k = 0; k < kcnt; ++k)
+    for (long long j = cbeg + tid; j < cend; j += kStateThreads)
+      top = fmaxf(top, fabsf(Slab<T>::load_one(wbase + k * prm.row_stride + j) - w0p[j]));
+  top = block_all_max(top, red + kRedSums);
+  if (top == 0.0f) return;                             // no drift at all: the zeros above stand
+  // 64-bit integers: at most `chunk` terms of 39 bits and fewer (39 fits chunks below 2^23) stay below 2^62.
+  // A typical drift must keep 17 of them, otherwise (or if none is known) fp64.
+  int qbits = 62;
+  while (qbits > 0 && (1ll << (62 - qbits)) <= prm.chunk) --qbits;
+  if (qbits > 39) qbits = 39;
+  double S64 = 1.0, inv64 = 1.0;
+  int kind = kCellF64;
+  if (typical > 0.0 && isfinite(top)) {
+    const int e = qbits - (ilogbf(top) + 1);           // |u| <= top < 2^(ilogb + 1)  =>  |u * 2^e| < 2^qbits
+    if (typical * ldexp(1.0, e) >= 131072.0) { kind = kCellI64; S64 = ldexp(1.0, e); inv64 = ldexp(1.0, -e); }
+  }
+  if (tid == 0) {
+    *my_unit = CellUnit{inv64, kind, 0};
+    atomicMax(&prm.path->now, kind);
+  }
+  const int window = lds_quads * 2;                    // 8-byte cells the LDS holds
+  const int mrow_fields = cells32_row_buckets(mrow, KC);      // buckets per row as a placed field counts them
+  unsigned long long* const c64 = reinterpret_cast<unsigned long long*>(lds_raw);
+  for (int k = 0; k < kcnt; ++k) {
+    const T* const row = wbase + k * prm.row_stride;
+    unsigned long long* const dst = reinterpret_cast<unsigned long long*>(share + (size_t)k * allcells * 8);
+    for (int c0 = 0; c0 < cells; c0 += window) {
+      const int ccnt = cells - c0 < window ? cells - c0 : window;
+      __syncthreads();
+      for (int t = tid; t < ccnt; t += kStateThreads) c64[t] = 0ull;          // integer 0 and 0.0
+      __syncthreads();
+      for (long long j0 = cbeg + (long long)tid * V; j0 < cend; j0 += kTile) {
+        uint32_t rec[Geom::kDwords];
+        load_rec_block<Geom::kDwords, false>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, rec);
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+          const float u = j0 + v < dlim ? Slab<T>::load_one(row + j0 + v) - w0p[j0 + v] : 0.0f;
+          const double y = fma((double)u, S64, kRoundMagic);                  // round to integer
+          const long long q = __double_as_longlong(y) - __double_as_longlong(kRoundMagic);
+#pragma unroll
+          for (int i = 0; i < LR; ++i) {
+            if (i >= rcnt) continue;
+            int f = (int)rec_field_exact<LR, FB>(rec, v, i), of = i;
+            if (prm.grp > 1) {                         // placed rows: the field names the row within the group
+              const int n = f / mrow_fields;
+              f -= n * mrow_fields;
+              of = i / prm.grp * prm.grp + n;
+            }
+            const bool neg = f >= prm.m;
+            const int c = of * prm.m + (neg ? f - prm.m : f) - c0;
+            if ((unsigned)c >= (unsigned)ccnt) continue;
+            if (kind == kCellI64) atomicAdd(c64 + c, (unsigned long long)(neg ? -q : q));
+            else atomicAdd(reinterpret_cast<double*>(lds_raw) + c, neg ? -(double)u : (double)u);
+          }
+        }
+      }
+      __syncthreads();
+      for (int t = tid; t < ccnt; t += kStateThreads) dst[c0 + t] = c64[t];
     }
   }
 }

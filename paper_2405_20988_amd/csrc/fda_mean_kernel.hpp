@@ -17,13 +17,11 @@
 // (w_bar - w_t0) as rounded to fp32 -- Algorithm 1 line 9 and the xi of Section 3.2 then need
 // no second pass over the slab.
 //
-//   kCellI64  a drift enters as the integer round(u * Sm) (Sm = ScaleInfo::Sm, the mean sampled
-//             |u| maps to about 2^18, every |u| must stay below boundm = 2^30 / Sm); the K
-//             integers of a coordinate are summed in 64 bits and added to 64-bit cells.  All of
-//             it is exact, so the result does not depend on the order of additions or on the
-//             partitioning.  |sum of a cell| < K * chunk * 2^30, which the host keeps below 2^63.
-//             A drift at or above boundm raises ScaleInfo::flagm.
-//   kCellF64  fp64 sums and ds_add_f64 cells; runs only when flagm is set.
+// A drift enters as the integer round(u * Sm) (Sm: the workgroup's own unit, from a sample of its drifts,
+// see fda_kernels.hpp; every scaled drift must stay below 2^30); the K integers of a coordinate are summed in
+// 64 bits and added to 64-bit cells.  All of it is exact, so the result does not depend on the order of
+// additions.  |sum of a cell| < K * chunk * 2^30, which the host keeps below 2^63.  A workgroup that met a
+// drift too large for its terms does its sketch once more with fp64 sums and ds_add_f64 cells.
 #pragma once
 #include "fda_kernels.hpp"
 
@@ -46,8 +44,9 @@ struct MeanParams {
   int vec_ok;             // all pointers / strides allow whole-vector loads
   float* w_bar;           // [d] or NULL: receives w_t0 + mean_k u_k
   double* part_np;        // [P][3]: sum_k ||u_k||^2, sum_k <xi,u_k>, ||w_bar - w_t0||^2 of the partition
-  void* part_sk;          // [P][l*m] 8-byte words: int64 (integer cells) or double (fp64 cells)
-  ScaleInfo* scale;
+  unsigned char* part_sk; // [P][l*m] 8-byte values: int64 or double (CellUnit::kind)
+  CellUnit* units;        // [P][R]
+  PathRecord* path;
   const uint16_t* table;  // [R][dpad] records of the tabulated hash, one field per row slot
   long long dpad;
 };
@@ -64,20 +63,17 @@ struct MeanHead {
   uint32_t rec[RecGeom<LR, FB>::kDwords];      // the V records of the tabulated hash
 };
 
-template <typename T, int KB, int LR, int CELL, int FB>
+constexpr int kMeanSampleRows = 8;            // workers a thread samples (all of them, or 8 in turn)
+
+template <typename T, int KB, int LR, int FB>
 __global__ void __launch_bounds__(kStateThreads)
 mean_state_kernel(const MeanParams prm) {
-  static_assert(CELL == kCellI64 || CELL == kCellF64, "8-byte cells only");
   constexpr int V = kStateV;
   constexpr long long kTile = (long long)kStateThreads * V;
   using Batch = MeanBatch<T, KB>;
   using Geom = RecGeom<LR, FB>;
   using Head = MeanHead<LR, FB>;
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  if constexpr (CELL == kCellF64) {
-    if (prm.do_sk == 0 || prm.scale->flagm == 0) return;
-  }
-
   // consecutive workgroup ids go round-robin over the 8 XCDs: the R workgroups that read the
   // same coordinates get ids on one XCD and its L2
   const int b = blockIdx.x;
@@ -86,26 +82,17 @@ mean_state_kernel(const MeanParams prm) {
   const int p = (slot / prm.R) * 8 + xcd;
   int rstart = 0, rcnt = 0;
   if (prm.do_sk) group_range(prm.l, prm.R, r, &rstart, &rcnt);
-  const bool scalars = (CELL == kCellI64) && (r == 0);
-  bool sketch = prm.do_sk != 0;
-  if constexpr (CELL == kCellI64) {
-    // the fp64 pass will redo the sketch: only the scalar components are left to do
-    if (sketch && prm.scale->flagm != 0) {
-      if (!scalars) return;
-      sketch = false;
-    }
-  }
+  const bool scalars = r == 0;
 
   const int cells = rcnt * prm.m;
   const uint32_t dummy_base = (uint32_t)cells * 8u;
-  const int lds_cells = sketch ? cells + kDummyCells : 0;
+  const int lds_cells = prm.do_sk ? cells + kDummyCells : 0;
   double* red = reinterpret_cast<double*>(lds_raw + (size_t)lds_cells * 8);
   const int tid = threadIdx.x;
   {
     unsigned long long* c64 = reinterpret_cast<unsigned long long*>(lds_raw);
-    for (int t = tid; t < lds_cells; t += kStateThreads) c64[t] = 0ull;     // integer 0 and 0.0
+    for (int t = tid; t < lds_cells; t += kStateThreads) c64[t] = 0ull;
   }
-  __syncthreads();
 
   // spare row slots: their table fields hold buckets below kDummyCells, sent to the dummy region
   uint32_t rowbase[LR];
@@ -126,7 +113,31 @@ mean_state_kernel(const MeanParams prm) {
   const int K = prm.K;
   const int NB = (K + KB - 1) / KB;                     // batches of slab rows per tile
   const int tail = K - (NB - 1) * KB;                   // rows of the last batch, 1..KB
-  const float Sm = prm.do_sk ? prm.scale->Sm : 1.0f;
+  // the unit of this workgroup's sketch terms
+  float Sm = 1.0f;
+  bool sketch = false;
+  if (prm.do_sk) {
+    double typical = 0.0;
+    const long long len = cend - cbeg;
+    if (len > 0) {
+      auto row_of = [&](int i, int t) {
+        const int k = K <= kMeanSampleRows ? (i < K ? i : K - 1) : (int)(((unsigned)(t >> 3) * kMeanSampleRows + i) % (unsigned)K);
+        return wbase + (long long)k * rs;
+      };
+      float sum = 0.0f, top = 0.0f;
+      sample_drifts<kMeanSampleRows, T>(row_of, w0p, cbeg, len, 1, sum, top);
+      typical = sample_mean(sum, top, (len < kStateThreads ? len : kStateThreads) * kMeanSampleRows, red);
+      if (typical == 0.0) {
+        sum = top = 0.0f;
+        sample_drifts<kMeanSampleRows, T>(row_of, w0p, 0, dlim, kSampleRunsGlobal, sum, top);
+        typical = sample_mean(sum, top, (dlim < kSampleRunsGlobal * kStateThreads ? dlim : kSampleRunsGlobal * kStateThreads) * kMeanSampleRows, red);
+      }
+    }
+    const float unit = unit_for(typical, 0);
+    sketch = unit != 0.0f;                    // otherwise the pass only notes whether there is any drift at all
+    if (sketch) Sm = unit;
+  }
+  __syncthreads();                            // (the cells are clear)
   float* const wbp = scalars ? prm.w_bar : nullptr;
   const float kf = (float)K;
 
@@ -134,15 +145,16 @@ mean_state_kernel(const MeanParams prm) {
   float amax = 0.0f;
 
   // SC: this workgroup also produces the scalar components; SK: it accumulates sketch rows.
-  auto run = [&](auto sc_tag, auto sk_tag) {
+  // MX: it notes the largest drift.
+  auto run = [&](auto sc_tag, auto sk_tag, auto mx_tag) {
     constexpr bool SC = decltype(sc_tag)::value;
     constexpr bool SK = decltype(sk_tag)::value;
-    long long acc[V];         // integer cells: sum over the workers of round(u * Sm)
-    double us[V];             // fp64 cells: sum over the workers of u
+    constexpr bool MX = decltype(mx_tag)::value;
+    long long acc[V];         // sum over the workers of round(u * Sm)
     float um[V];              // scalar workgroups: sum over the workers of u, for the average model
     float sn = 0.0f, sp = 0.0f;
 #pragma unroll
-    for (int v = 0; v < V; ++v) { acc[v] = 0; us[v] = 0.0; um[v] = 0.0f; }
+    for (int v = 0; v < V; ++v) { acc[v] = 0; um[v] = 0.0f; }
 
     // slab rows k0 .. k0+KB-1 (rows past the last worker repeat it; consume() drops them)
     auto load_batch_fast = [&](Batch& bt, long long j0, int k0) {
@@ -211,11 +223,10 @@ mean_state_kernel(const MeanParams prm) {
           if constexpr (SC) {
             sn = fmaf(u, u, sn);
             sp = fmaf(h.x[v], u, sp);
-            amax = fmaxf(amax, fabsf(u));
             um[v] += u;
           }
-          if constexpr (SK && CELL == kCellI64) acc[v] += (long long)round_half_up(u * Sm);
-          if constexpr (SK && CELL == kCellF64) us[v] += (double)u;
+          if constexpr (MX) amax = fmaxf(amax, fabsf(u));
+          if constexpr (SK) acc[v] += (long long)round_half_up(u * Sm);
         }
       }
     };
@@ -260,14 +271,10 @@ mean_state_kernel(const MeanParams prm) {
             const uint32_t sb = hw & Geom::kFieldMask;                     // bucket + m * (sign is -1)
             const bool neg = sb >= (uint32_t)prm.m;
             const uint32_t off = ((neg ? sb - (uint32_t)prm.m : sb) << 3) + rowbase[i];
-            if constexpr (CELL == kCellI64) {
-              const unsigned long long q = (unsigned long long)acc[v];
-              atomicAdd(reinterpret_cast<unsigned long long*>(lds_raw + off), neg ? 0ull - q : q);
-            } else {
-              atomicAdd(reinterpret_cast<double*>(lds_raw + off), neg ? -us[v] : us[v]);
-            }
+            const unsigned long long q = (unsigned long long)acc[v];
+            atomicAdd(reinterpret_cast<unsigned long long*>(lds_raw + off), neg ? 0ull - q : q);
           }
-          acc[v] = 0; us[v] = 0.0;
+          acc[v] = 0;
         }
       }
     };
@@ -316,20 +323,18 @@ mean_state_kernel(const MeanParams prm) {
     }
   };
   if (scalars) {
-    if (sketch) run(std::true_type{}, std::true_type{});
-    else run(std::true_type{}, std::false_type{});
-  } else {
-    run(std::false_type{}, std::true_type{});
+    if (sketch) run(std::true_type{}, std::true_type{}, std::true_type{});
+    else if (prm.do_sk) run(std::true_type{}, std::false_type{}, std::true_type{});
+    else run(std::true_type{}, std::false_type{}, std::false_type{});
+  } else if (sketch) {
+    run(std::false_type{}, std::true_type{}, std::true_type{});
+  } else if (prm.do_sk) {
+    for (long long j = cbeg + tid; j < cend; j += kStateThreads)
+      for (int k = 0; k < K; ++k) amax = fmaxf(amax, fabsf(Slab<T>::load_one(wbase + (long long)k * rs + j) - w0p[j]));
   }
 
-  if constexpr (CELL == kCellI64) {
-    if (prm.do_sk && scalars) {
-      // drifts the integers cannot hold (any drift at all when the sample saw none)
-      const float bm = prm.scale->boundm;
-      const bool bad = bm > 0.0f ? !(amax < bm) : (amax > 0.0f);
-      if (bad) prm.scale->flagm = 1;
-    }
-  }
+  // the integer cells are void: a drift beyond their terms, or any drift at all where the sample saw none
+  const bool bad = prm.do_sk && (sketch ? !(amax < kTermBound / Sm) : amax > 0.0f);
 
   // ---- workgroup reduction of the scalar components (fixed shape) ---------------------
   const int lane = tid & 63, wave = tid >> 6;
@@ -347,13 +352,45 @@ mean_state_kernel(const MeanParams prm) {
     if (tid == 1 && !lin) s = 0.0;               // no LinearFDA: the projection slot stays zero
     prm.part_np[(size_t)p * 3 + tid] = s;
   }
+  if (!prm.do_sk) return;
+  const bool again = block_all_max(bad ? 1.0f : 0.0f, red + kRedSums) != 0.0f;
+  if (again) {
+    // ---- redo: the sketch of this workgroup once more, in fp64 -----------------------------------------
+    double* const cd = reinterpret_cast<double*>(lds_raw);
+    for (int t = tid; t < lds_cells; t += kStateThreads) cd[t] = 0.0;
+    __syncthreads();
+    for (long long j0 = cbeg + (long long)tid * V; j0 < cend; j0 += kTile) {
+      uint32_t rec[Geom::kDwords];
+      load_rec_block<Geom::kDwords, false>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, rec);
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+        double us = 0.0;                         // sum over the workers of u
+        if (j0 + v < dlim) {
+          const float base = w0p[j0 + v];
+          for (int k = 0; k < K; ++k) us += (double)(Slab<T>::load_one(wbase + (long long)k * rs + j0 + v) - base);
+        }
+#pragma unroll
+        for (int i = 0; i < LR; ++i) {
+          const uint32_t sb = rec_field<LR, FB>(rec, v, i) & Geom::kFieldMask;
+          const bool neg = sb >= (uint32_t)prm.m;
+          const uint32_t off = ((neg ? sb - (uint32_t)prm.m : sb) << 3) + rowbase[i];
+          atomicAdd(reinterpret_cast<double*>(lds_raw + off), neg ? -us : us);
+        }
+      }
+    }
+    __syncthreads();
+  }
   // ---- flush the LDS sketch to this workgroup's slice of the partial buffer -----------
-  if (sketch) {
+  {
     const int allcells = prm.l * prm.m;
     unsigned long long* out = reinterpret_cast<unsigned long long*>(prm.part_sk);
     const unsigned long long* c64 = reinterpret_cast<const unsigned long long*>(lds_raw);
     for (int t = tid; t < cells; t += kStateThreads)
       out[(size_t)p * allcells + (size_t)rstart * prm.m + t] = c64[t];
+  }
+  if (tid == 0) {
+    prm.units[(size_t)p * prm.R + r] = CellUnit{again ? 1.0 : 1.0 / (double)Sm, again ? kCellF64 : kCellI64, 0};
+    if (again) atomicMax(&prm.path->now, 1);
   }
 }
 

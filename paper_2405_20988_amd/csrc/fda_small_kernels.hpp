@@ -1,12 +1,10 @@
 // Device code of the FDA monitor for gfx950 (wave64): everything except the state kernel.
 // Included by fda_api.hip only.
 //
-//   hash_table_kernel, cell_count_kernel   once per context: the tabulated hash and the largest
-//                    number of coordinates a workgroup can put into one sketch cell
-//   scale_kernel     per call: the fixed-point unit of the integer sketch cells
-//   merge_kernel     fixed-order fp64 sum of the per-workgroup partials -> state[K][S]
-//   merge_mean_kernel  the same for the partials of mean_state_kernel -> mean_state[S]
-//   estimate_kernel  Algorithm 1 lines 7-8: mean state, M2, H (Thm 1, Thm 2), decision
+//   hash_table_kernel  once per context: the tabulated hash
+//   finish_kernel    fixed-order fp64 sum of the per-workgroup partials -> state[K][S], or mean_state[S];
+//                    on request with the estimate of Algorithm 1 lines 7-8 in the same launch
+//   estimate_kernel  Algorithm 1 lines 7-8 on given states: mean state, M2, H (Thm 1, Thm 2), decision
 //   sync_kernel      Algorithm 1 line 9: fused mean over workers + broadcast to all rows (+ the squared
 //                    norm of the model change, for the refresh of xi)
 //   sync_from_mean_kernel  the same from an average model that is already there, with xi
@@ -145,356 +143,358 @@ hash_table_kernel(const HashCoef hc, int l, int R, int slots, int m, int fb, int
   }
 }
 
-// ---- how many coordinates can meet in one cell of one workgroup ------------------------
-// Depends only on the hash, d and the partitioning, so it is counted once per context: the
-// exact maximum, over workgroups, rows and buckets, of the number of coordinates of the
-// workgroup's chunk that fall into the bucket.  It bounds the number of terms of any LDS cell.
-__global__ void __launch_bounds__(kStateThreads)
-cell_count_kernel(const HashCoef hc, int l, int m, int split, long long d, long long chunk,
-                  unsigned int* __restrict__ nmax) {   // nmax: the entry to raise
-  // split: the pass keeps the two signs of a bucket in cells of their own (sign-split rows)
-  extern __shared__ __align__(16) unsigned char lds_raw[];
-  unsigned int* cnt = reinterpret_cast<unsigned int*>(lds_raw);
-  __shared__ unsigned int shmax[kStateThreads / 64];
-  const int p = blockIdx.x / l, i = blockIdx.x - p * l;
-  const int ncell = split ? 2 * m : m;
-  for (int t = threadIdx.x; t < ncell; t += kStateThreads) cnt[t] = 0u;
-  __syncthreads();
-  const long long cbeg = (long long)p * chunk;
-  long long cend = cbeg + chunk;
-  if (cend > d) cend = d;
-  for (long long j = cbeg + threadIdx.x; j < cend; j += kStateThreads) {
-    const uint32_t h = hash_entry(hc, i, (uint32_t)j, (uint32_t)m);
-    atomicAdd(cnt + (h & 0x7fffu) + ((split && (h >> 15)) ? m : 0), 1u);
-  }
-  __syncthreads();
-  unsigned int mx = 0u;
-  for (int t = threadIdx.x; t < ncell; t += kStateThreads) mx = max(mx, cnt[t]);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) mx = max(mx, (unsigned int)__shfl_down((int)mx, o, 64));
-  if ((threadIdx.x & 63) == 0) shmax[threadIdx.x >> 6] = mx;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    for (int t = 1; t < kStateThreads / 64; ++t) mx = max(mx, shmax[t]);
-    atomicMax(nmax, mx);
-  }
-}
 __global__ void clear_u32_kernel(unsigned int* p, int n) {
-  if (blockIdx.x == 0 && (int)threadIdx.x < n) p[threadIdx.x] = 0u;
+  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < n; t += gridDim.x * blockDim.x) p[t] = 0u;
 }
 
-// ---- the per-call fixed-point scale ----------------------------------------------------
-// The units of the integer cells.
-// 64-bit cells: with at most nmax[1] terms per cell, |q| < 2^qbits keeps every cell below 2^62.
-// Drifts up to 2^12..2^13 times the sampled maximum are allowed for (the sample can miss the
-// tail), which leaves qbits - 13 bits below the sampled maximum.  If the mean sampled magnitude
-// would still get fewer than 17 of them, or the sample saw nothing usable, the call is sent
-// down the fp64 path right away.
-// 32-bit cells: the mean sampled magnitude maps to [2^18, 2^19) -- every term is rounded by at
-// most 2^-19 of the mean |u| -- and single drifts may reach 2^30, i.e. 2048..4096 times the mean
-// (a Student-t(3) tail over 3e9 draws reaches about 1400 times).  A cell wraps only if its sum
-// leaves (-2^31, 2^31), which for sums of up to a few thousand such terms does not happen, and
-// if it does it is noticed.  Cells that can collect more than 4096 terms get one bit less;
-// beyond 16384 terms the call goes to the 64-bit pass.
-__device__ inline ScaleInfo choose_scale(float amax, double mean, const unsigned int* nmax) {
-  ScaleInfo s;
-  s.S64 = 1.0; s.invS64 = 1.0; s.invS32 = 1.0; s.S32 = 1.0f;
-  s.bound32 = 0.0f; s.bound64 = 0.0f; s.flag32 = 0; s.overflow64 = 0;
-  s.flagm = 0; s.invSm = 1.0; s.Sm = 1.0f; s.boundm = 0.0f;
-  if (amax > 0.0f && isfinite(amax) && mean > 0.0) {
-    // ---- 64-bit cells
-    int cb = 0;
-    while (cb < 32 && (1ull << cb) <= (unsigned long long)nmax[1]) ++cb;   // terms < 2^cb
-    int qbits = 62 - cb;
-    if (qbits > 50) qbits = 50;                // the rounding trick needs |u * 2^e| < 2^51
-    const int head = 13;
-    const int ex = ilogbf(amax);               // 2^ex <= amax < 2^(ex+1)
-    const int e = qbits - (ex + head);         // |u| < 2^(ex+head)  =>  |u * 2^e| < 2^qbits
-    s.S64 = ldexp(1.0, e);
-    s.invS64 = ldexp(1.0, -e);
-    s.bound64 = (ex + head > 127) ? 3.0e38f : ldexpf(1.0f, ex + head);
-    if (!(mean * s.S64 >= 131072.0)) { s.overflow64 = 1; s.flag32 = 1; }   // < 17 bits for a typical drift
-    // ---- 32-bit cells
-    int cb32 = 0;
-    while (cb32 < 32 && (1ull << cb32) <= (unsigned long long)nmax[0]) ++cb32;
-    const int shrink = cb32 > 12 ? (cb32 - 12 + 1) / 2 : 0;
-    const int em = ilogb(mean);                // 2^em <= mean < 2^(em+1)
-    // ---- mean-state kernel: 32-bit terms, 64-bit sums, the mean magnitude at [2^18, 2^19)
-    const int emn = 18 - em;
-    if (emn > 120 || emn < -120) {
-      s.flagm = 1;
-    } else {
-      s.Sm = ldexpf(1.0f, emn);
-      s.invSm = ldexp(1.0, -emn);
-      s.boundm = (30 - emn > 127) ? 3.0e38f : ldexpf(1.0f, 30 - emn);
-      if (!(amax < s.boundm)) s.flagm = 1;
-    }
-    const int e32 = 18 - shrink - em;
-    if (e32 > 120 || e32 < -120 || shrink > 1) {
-      s.flag32 = 1;
-    } else {
-      s.S32 = ldexpf(1.0f, e32);
-      s.invS32 = ldexp(1.0, -e32);
-      s.bound32 = (30 - e32 > 127) ? 3.0e38f : ldexpf(1.0f, 30 - e32);
-      if (!(amax < s.bound32)) s.flag32 = 1;   // the sample already holds a drift too large
-    }
-  }
-  return s;
-}
-
-// Largest and mean |w_kj - w_t0_j| over `samples` coordinates of every worker: evenly spaced runs
-// of 8 consecutive coordinates (a run shares its cache lines, so the scattered reads cost an
-// eighth of what single coordinates would).  A thread takes one sampled coordinate and every
-// slices-th worker (the loads of one thread are independent HBM misses: about eight per thread,
-// several in flight); per-workgroup maximum and sum;
-// the workgroup that finishes last combines the per-workgroup results in a fixed order, chooses
-// the scales and clears the flags.  `ticket` counts finished workgroups and is left at zero.
-constexpr int kScaleMaxSlices = 8;          // a sampled coordinate's workers are split over 1..8 threads
-
-template <typename T>
-__global__ void __launch_bounds__(kSmallThreads)
-scale_kernel(const T* __restrict__ w, const float* __restrict__ w_t0, int K, long long d,
-             long long row_stride, int samples, int slices, float* __restrict__ part_max,
-             double* __restrict__ part_sum, unsigned int* __restrict__ ticket,
-             const unsigned int* __restrict__ nmax, ScaleInfo* __restrict__ out) {
-  __shared__ float sh[kSmallThreads / 64];
-  __shared__ double scratch[kSmallThreads / 64];
-  __shared__ int last;
-  float m = 0.0f;
-  double sum = 0.0;
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  const int smp = t / slices, slice = t - smp * slices;
-  if (smp < samples) {
-    // samples is a multiple of 8 and at most d, or equal to d (then every coordinate is taken)
-    const long long j = (samples & 7) ? (long long)smp
-                                      : (long long)(smp >> 3) * (d / (samples >> 3)) + (smp & 7);
-    const float base = w_t0[j];
-    float part = 0.0f;
-#pragma unroll 4
-    for (int k = slice; k < K; k += slices) {
-      const float u = fabsf(Slab<T>::load_one(w + (long long)k * row_stride + j) - base);
-      m = fmaxf(m, u);                         // fmaxf drops NaN
-      if (u == u && u < 3.0e38f) part += u;
-    }
-    sum = (double)part;
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_down(m, o, 64));
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
-  const double tot = block_sum(sum, scratch);  // has the barriers sh needs
-  if (threadIdx.x == 0) {
-    for (int q = 1; q < kSmallThreads / 64; ++q) m = fmaxf(m, sh[q]);
-    part_max[blockIdx.x] = m;
-    part_sum[blockIdx.x] = tot;
-    __threadfence();
-    last = (atomicAdd(ticket, 1u) == gridDim.x - 1) ? 1 : 0;
-  }
-  __syncthreads();
-  if (!last) return;
-  __threadfence();
-  if (threadIdx.x < 64) {                      // lane q takes partials q, q + 64, ...
-    float am = 0.0f;
-    double sm = 0.0;
-    for (int q = threadIdx.x; q < (int)gridDim.x; q += 64) {
-      am = fmaxf(am, reinterpret_cast<volatile float*>(part_max)[q]);
-      sm += reinterpret_cast<volatile double*>(part_sum)[q];
-    }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) am = fmaxf(am, __shfl_down(am, o, 64));
-    sm = wave_sum(sm);
-    if (threadIdx.x == 0) {
-      *out = choose_scale(am, sm / ((double)samples * K), nmax);
-      *ticket = 0u;
-    }
-  }
-}
-
-// state[k][s] = sum over the partitions in fp64.  A workgroup handles 32 consecutive state
-// entries; eight lanes per entry each sum every eighth partition and the eight sums are added
-// in slice order: a fixed shape (and the integer partials are exact anyway).  The scalar
-// components always come from the first pass (P32 partitions); the sketch partials from
-// whichever pass was the last to run.
-__global__ void __launch_bounds__(kSmallThreads)
-merge_kernel(const double* __restrict__ part_np, const void* __restrict__ part_sk,
-             const ScaleInfo* __restrict__ scale, float* __restrict__ state, int K, int cells,
-             int P32, int P64) {
-  __shared__ double sh[8][32];
-  const int S = 2 + cells;
-  const int o = threadIdx.x & 31, slice = threadIdx.x >> 5;
-  const long long idx = (long long)blockIdx.x * 32 + o;
-  const bool live = idx < (long long)K * S;
-  double acc = 0.0, unit = 1.0;
-  if (live) {
-    const int k = (int)(idx / S), s = (int)(idx - (long long)k * S);
-    if (s < 2) {
-#pragma unroll 8
-      for (int p = slice; p < P32; p += 8) acc += part_np[((size_t)p * K + k) * 2 + s];
-    } else {
-      const int c = s - 2;
-      if (scale->overflow64 != 0) {
-        const double* pd = reinterpret_cast<const double*>(part_sk);
-#pragma unroll 8
-        for (int p = slice; p < P64; p += 8) acc += pd[((size_t)p * K + k) * cells + c];
-      } else {
-        const bool narrow = scale->flag32 == 0;
-        const int P = narrow ? P32 : P64;
-        unit = narrow ? scale->invS32 : scale->invS64;
-        const long long* pi = reinterpret_cast<const long long*>(part_sk);
-#pragma unroll 8
-        for (int p = slice; p < P; p += 8) acc += (double)pi[((size_t)p * K + k) * cells + c];
-      }
-    }
-  }
-  sh[slice][o] = acc;
-  __syncthreads();
-  if (live && slice == 0) {
-    double t = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t += sh[q][o];
-    state[idx] = (float)(t * unit);
-  }
-}
-
-// mean_state[s] = (sum over the partitions) / K, for the partials of mean_state_kernel: the two
-// scalar sums in fp64, the sketch cells as 64-bit integers in units of 1/Sm (or fp64 when the
-// call went down the fp64 path).  Same fixed shape as merge_kernel.  One entry past the state,
-// the summed squared norm of the model change goes to *dnorm (for fda_sync_from_mean).
-__global__ void __launch_bounds__(kSmallThreads)
-merge_mean_kernel(const double* __restrict__ part_np, const void* __restrict__ part_sk,
-                  const ScaleInfo* __restrict__ scale, float* __restrict__ mean_state,
-                  double* __restrict__ dnorm, int K, int cells, int P) {
-  __shared__ double sh[8][32];
-  const int S = 2 + cells;
-  const int o = threadIdx.x & 31, slice = threadIdx.x >> 5;
-  const int s = blockIdx.x * 32 + o;
-  const bool live = s <= S;
-  double acc = 0.0, unit = 1.0;
-  if (live) {
-    if (s < 2 || s == S) {
-      const int q = s < 2 ? s : 2;
-#pragma unroll 8
-      for (int p = slice; p < P; p += 8) acc += part_np[(size_t)p * 3 + q];
-    } else {
-      const int c = s - 2;
-      if (scale->flagm != 0) {
-        const double* pd = reinterpret_cast<const double*>(part_sk);
-#pragma unroll 8
-        for (int p = slice; p < P; p += 8) acc += pd[(size_t)p * cells + c];
-      } else {
-        unit = scale->invSm;
-        const long long* pi = reinterpret_cast<const long long*>(part_sk);
-        long long isum = 0;                       // exact
-#pragma unroll 8
-        for (int p = slice; p < P; p += 8) isum += pi[(size_t)p * cells + c];
-        acc = (double)isum;
-      }
-    }
-  }
-  sh[slice][o] = acc;
-  __syncthreads();
-  if (live && slice == 0) {
-    double t = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) t += sh[q][o];
-    if (s == S) *dnorm = t;
-    else mean_state[s] = (float)(t * unit / (double)K);
-  }
+// Index of the group of group_range(K, G) that holds item k.
+__device__ inline int group_of(int K, int G, int k) {
+  const int base = K / G, rem = K % G, big = rem * (base + 1);
+  return k < big ? k / (base + 1) : rem + (k - big) / base;
 }
 
 // ----------------------------------------------------------------------------------------
 // Algorithm 1 lines 7-8, all in fp64:
 //   mean_k of the states;  row norms of the mean sketch;  M2 = their median (Section 3.1);
 //   H_sketch = n - M2/(1+eps) (Thm 1);  H_linear = n - p^2 (Thm 2);  sync = H > theta.
+// A row norm is added up in one fixed order, whichever kernel does it: the squares of 32 neighbouring
+// cells as a tree, eight such sums (256 cells) in order, those in order.
+// ----------------------------------------------------------------------------------------
+constexpr int kEstCols = kSmallThreads;      // cells per workgroup of estimate_kernel
+constexpr int kMaxEstBlocks = FDA_MAX_SKETCH_ROWS * ((FDA_STATIC_MAX_M + kEstCols - 1) / kEstCols);
+
+struct EstimateArgs {
+  int variants, l, m, K;
+  double eps, theta, tie_tol;
+  fda_estimate* out;
+};
+__device__ __forceinline__ double half_wave_sum(double v) {   // valid in lanes 0 and 32
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) v += __shfl_down(v, o, 32);
+  return v;
+}
+// One thread: the result from the sums of the two scalar components and the l row norms.
+__device__ inline void decide(const EstimateArgs& a, double nsum, double psum, const double* rows, int state_path) {
+  fda_estimate e;
+  e.mean_sqnorm = nsum / (double)a.K;
+  e.mean_proj = 0.0; e.m2 = 0.0; e.h_linear = 0.0; e.h_sketch = 0.0;
+  e.sync_linear = 0; e.sync_sketch = 0; e.near_tie_linear = 0; e.near_tie_sketch = 0;
+  e.nonfinite = 0;
+  e.state_path = state_path;
+  const double band = a.tie_tol * fmax(e.mean_sqnorm, fabs(a.theta));
+  if (a.variants & FDA_VARIANT_LINEAR) {
+    e.mean_proj = psum / (double)a.K;
+    e.h_linear = e.mean_sqnorm - e.mean_proj * e.mean_proj;
+    if (isfinite(e.h_linear)) {
+      e.sync_linear = e.h_linear > a.theta ? 1 : 0;
+      e.near_tie_linear = fabs(e.h_linear - a.theta) <= band ? 1 : 0;
+    } else {
+      e.sync_linear = 1; e.nonfinite = 1;
+    }
+  }
+  if (a.variants & FDA_VARIANT_SKETCH) {
+    // median of l values: insertion sort, then middle (even l: mean of the two middle)
+    double r[FDA_MAX_SKETCH_ROWS];
+    for (int i = 0; i < a.l; ++i) {
+      const double v = rows[i];
+      int q = i;
+      while (q > 0 && !(r[q - 1] <= v)) { r[q] = r[q - 1]; --q; }
+      r[q] = v;
+    }
+    e.m2 = (a.l & 1) ? r[a.l / 2] : 0.5 * (r[a.l / 2 - 1] + r[a.l / 2]);
+    e.h_sketch = e.mean_sqnorm - e.m2 / (1.0 + a.eps);
+    if (isfinite(e.h_sketch)) {
+      e.sync_sketch = e.h_sketch > a.theta ? 1 : 0;
+      e.near_tie_sketch = fabs(e.h_sketch - a.theta) <= band ? 1 : 0;
+    } else {
+      e.sync_sketch = 1; e.nonfinite = 1;
+    }
+  }
+  *a.out = e;
+}
+// What workgroups of one launch hand to each other goes through agent-scope accesses (which pass the L2 of the
+// XCD) and counters: the writer waits until its stores have been acknowledged before it counts itself, the
+// reader's loads cannot hit a stale line.  (__threadfence() would write back and invalidate the whole L2, once
+// per workgroup: with 640 workgroups that was 20 of the 32 us of a launch.)
+template <typename V>
+__device__ __forceinline__ void agent_store(V* p, V x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+template <typename V>
+__device__ __forceinline__ V agent_load(const V* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// Every thread of a workgroup: is it the last of `count` to get here?
+__device__ __forceinline__ bool finished_last(unsigned int* ticket, int count, int* flag) {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (threadIdx.x == 0)
+    *flag = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)count - 1u ? 1 : 0;
+  __syncthreads();
+  return *flag != 0;
+}
+
+// The workgroup that finished last: part[0], part[1] are the sums of the scalar components, then come the
+// row norms' pieces, `per` to each 256 cells (their loads are independent: taken one after the other by one
+// thread they cost a third of a microsecond each, cfg5 28 of them).
+__device__ inline void finish_estimate(const EstimateArgs& a, const double* part, int per, int state_path) {
+  __shared__ double blocks[kMaxEstBlocks];
+  __shared__ double rows[FDA_MAX_SKETCH_ROWS];
+  const int tid = threadIdx.x;
+  const int bpr = (a.m + kEstCols - 1) / kEstCols;
+  if (a.variants & FDA_VARIANT_SKETCH) {
+    const int pieces = per == 1 ? bpr : (a.m + 31) / 32;     // of one row
+    const int items = a.l * bpr * per;
+    for (int t0 = 0; t0 < items; t0 += (int)blockDim.x) {    // one piece per thread, per (1 or 8) neighbours to a block
+      const int t = t0 + tid, blk = t / per, i = blk / bpr, q = (blk - i * bpr) * per + (t - blk * per);
+      const double x = t < items && q < pieces ? agent_load(part + 2 + i * pieces + q) : 0.0;
+      double s = 0.0;
+      for (int e = 0; e < per; ++e) s += __shfl(x, e, per);
+      if (t < items && t == blk * per) blocks[blk] = s;
+    }
+    __syncthreads();
+    if (tid < a.l) {
+      double s = 0.0;
+      for (int b = 0; b < bpr; ++b) s += blocks[tid * bpr + b];
+      rows[tid] = s;
+    }
+    __syncthreads();
+  }
+  if (tid == 0) decide(a, agent_load(part), agent_load(part + 1), rows, state_path);
+}
+// sums of the two scalar components over the K states (of the first 256 threads of a workgroup)
+__device__ inline void scalar_sums(const float* state, int K, int S, double* scratch, double* part) {
+  double vn = 0.0, vp = 0.0;
+  if (threadIdx.x < kSmallThreads)
+    for (int k = threadIdx.x; k < K; k += kSmallThreads) {
+      vn += (double)state[(size_t)k * S];
+      vp += (double)state[(size_t)k * S + 1];
+    }
+  const double sn = block_sum(vn, scratch);
+  const double sp = block_sum(vp, scratch);
+  if (threadIdx.x == 0) { agent_store(part, sn); agent_store(part + 1, sp); }
+}
 // Workgroup b takes 256 consecutive cells of one sketch row (one cell per thread: mean over the
 // K workers, squared, summed over the workgroup); workgroup 0 also takes the scalar components.
-// The workgroup that finishes last adds the per-workgroup sums of every row in workgroup order,
-// takes the median and writes the result.  `ticket` counts finished workgroups and is left at 0.
-// ----------------------------------------------------------------------------------------
-constexpr int kEstCols = kSmallThreads;      // cells per workgroup
-
+// The workgroup that finishes last takes the median and writes the result.  `ticket` counts finished
+// workgroups and is left at 0.
 __global__ void __launch_bounds__(kSmallThreads)
-estimate_kernel(const float* __restrict__ state, int K, int l, int m, int variants, double eps,
-                double theta, double tie_tol, double* __restrict__ part, unsigned int* __restrict__ ticket,
-                const ScaleInfo* __restrict__ scale, int mean_mode, fda_estimate* __restrict__ out) {
-  __shared__ double scratch[kSmallThreads / 64];
+estimate_kernel(const float* __restrict__ state, EstimateArgs a, double* __restrict__ part,
+                unsigned int* __restrict__ ticket, const PathRecord* __restrict__ path) {
+  __shared__ double scratch[kSmallThreads / 32];
   __shared__ int last;
-  const int cells = (variants & FDA_VARIANT_SKETCH) ? l * m : 0;
+  const int cells = (a.variants & FDA_VARIANT_SKETCH) ? a.l * a.m : 0;
   const int S = 2 + cells;
-  const int bpr = (m + kEstCols - 1) / kEstCols;     // workgroups per sketch row
+  const int bpr = (a.m + kEstCols - 1) / kEstCols;   // workgroups per sketch row
   const int tid = threadIdx.x;
   // part[0], part[1]: sums of the two scalar components; part[2 + b]: workgroup b's row sum
   if (cells) {
     const int i = blockIdx.x / bpr, col = (blockIdx.x - i * bpr) * kEstCols + tid;
     double sq = 0.0;
-    if (col < m) {
+    if (col < a.m) {
       double c = 0.0;
-#pragma unroll 8
-      for (int k = 0; k < K; ++k) c += (double)state[(size_t)k * S + 2 + i * m + col];
-      c /= (double)K;
+      for (int k0 = 0; k0 < a.K; k0 += 16) {       // the loads of 16 workers together, added in order
+        float x[16];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) x[t] = state[(size_t)(k0 + t < a.K ? k0 + t : k0) * S + 2 + i * a.m + col];
+#pragma unroll
+        for (int t = 0; t < 16; ++t) c += k0 + t < a.K ? (double)x[t] : 0.0;
+      }
+      c /= (double)a.K;
       sq = c * c;
     }
-    const double r = block_sum(sq, scratch);
-    if (tid == 0) part[2 + blockIdx.x] = r;
+    sq = half_wave_sum(sq);
+    if ((tid & 31) == 0) scratch[tid >> 5] = sq;
+    __syncthreads();
+    if (tid == 0) {
+      double r = 0.0;
+      for (int q = 0; q < kSmallThreads / 32; ++q) r += scratch[q];
+      agent_store(part + 2 + blockIdx.x, r);
+    }
+    __syncthreads();
   }
+  if (blockIdx.x == 0) scalar_sums(state, a.K, S, scratch, part);
+  if (!finished_last(ticket, (int)gridDim.x, &last)) return;
+  // which kind of sketch cell the last state pass used
+  finish_estimate(a, part, 1, cells && path != nullptr ? path->last : -1);
+  if (tid == 0) *ticket = 0u;
+}
+
+// ----------------------------------------------------------------------------------------
+// state[k][s] = sum over the partitions in fp64, of the partials of state_kernel (rows = K) or of
+// mean_state_kernel (rows = 1; the result is divided by K, and one entry past the state, the summed squared
+// norm of the model change, goes to *dnorm for fda_sync_from_mean).
+// Workgroup 0 takes the scalar components.  The others take 32 neighbouring cells of one sketch row for `wl`
+// workers each: 512 threads = 32 cells x wl workers x slices of the partitions.  A wave's loads are whole
+// 128-byte runs, and the host splits the partitions so that a thread has about 16 of them: what bounds the
+// kernel is their latency (the partials were just written by other XCDs; with all workers of 32 cells in one
+// workgroup, up to 130 loads per thread, it took 52 us on cfg3 where it takes 9).  The slices are added in order:
+// a fixed shape.
+// With est.out != NULL the estimate follows in the same launch (7 us on cfg1, 13 on cfg3, 18 on cfg4, where
+// the two kernels took 13, 18 and 23 and the gap between them).  The workgroup that is the last to finish
+// among those of 32 cells averages them over the workers and leaves the sum of their squares; the last of
+// all takes the median.
+// ----------------------------------------------------------------------------------------
+struct FinishParams {
+  const double* part_np;           // [P][K][2], or [P][3]
+  const unsigned char* part_sk;
+  const CellUnit* units;           // [P][G][R]
+  PathRecord* path;
+  float* state;
+  double* dnorm;                   // mean-state pass only (else NULL)
+  unsigned int* ticket;            // [0]: all workgroups, then one per 32 cells; zero, left at zero
+  double* est_part;
+  int rows, K, l, m, P, G, R;      // l = m = 0: no sketch
+  int wl;                          // 1, 2, 4, 8 or 16
+  EstimateArgs est;                // est.out == NULL: no estimate
+};
+constexpr int kFinishThreads = 512;
+constexpr int kFinishCols = 32;
+constexpr int kFinishLanes = kFinishThreads / kFinishCols;
+constexpr int kFinishStates = 64;  // workers averaged at a time
+constexpr int kFinishLoads = 16;   // partials per thread the host aims at
+
+// sum over the partitions slice, slice + slices, ... of value times unit.  The loads of a batch are issued
+// together (those past the end repeat the first one).
+template <typename V>
+__device__ __forceinline__ double sum_partials(const V* q, size_t step, const CellUnit* un, int GR, int slice, int slices, int P) {
+  double acc = 0.0;
+  for (int p0 = slice; p0 < P; p0 += kFinishLoads * slices) {
+    V x[kFinishLoads];
+    double unit[kFinishLoads];
+#pragma unroll
+    for (int t = 0; t < kFinishLoads; ++t) {
+      const int p = p0 + t * slices < P ? p0 + t * slices : p0;
+      x[t] = q[p * step];
+      unit[t] = un[(size_t)p * GR].unit;
+    }
+#pragma unroll
+    for (int t = 0; t < kFinishLoads; ++t) acc += p0 + t * slices < P ? unit[t] * (double)x[t] : 0.0;
+  }
+  return acc;
+}
+
+__global__ void __launch_bounds__(kFinishThreads)
+finish_kernel(const FinishParams f) {
+  __shared__ double sh[kFinishLanes][kFinishCols];
+  __shared__ float st[kFinishStates][kFinishCols];
+  __shared__ double scratch[kFinishThreads / 64];
+  __shared__ int last;
+  const int tid = threadIdx.x;
+  const bool mean = f.dnorm != nullptr;
+  const int cells = f.l * f.m, S = 2 + cells;
+  // 0: every partial is of the kind the pass aims at (int32, mean-state pass int64)
+  const int path = f.path->now;
   if (blockIdx.x == 0) {
-    double vn = 0.0, vp = 0.0;
-    for (int k = tid; k < K; k += blockDim.x) {
-      vn += (double)state[(size_t)k * S];
-      vp += (double)state[(size_t)k * S + 1];
+    double (*s8)[64] = reinterpret_cast<double (*)[64]>(&sh[0][0]);        // [8][64]
+    const int e0 = tid & 63, slice = tid >> 6;
+    const int width = mean ? 3 : 2 * f.K;
+    for (int eb = 0; eb < width; eb += 64) {
+      const int e = eb + e0;
+      double acc = 0.0;
+      if (e < width) {
+        for (int p0 = slice; p0 < f.P; p0 += 8 * kFinishLoads) {
+          double x[kFinishLoads];
+#pragma unroll
+          for (int t = 0; t < kFinishLoads; ++t) x[t] = f.part_np[(size_t)(p0 + t * 8 < f.P ? p0 + t * 8 : p0) * width + e];
+#pragma unroll
+          for (int t = 0; t < kFinishLoads; ++t) acc += p0 + t * 8 < f.P ? x[t] : 0.0;
+        }
+      }
+      s8[slice][e0] = acc;
+      __syncthreads();
+      if (slice == 0 && e < width) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t += s8[q][e0];
+        if (!mean) f.state[(size_t)(e >> 1) * S + (e & 1)] = (float)t;
+        else if (e < 2) f.state[e] = (float)(t / (double)f.K);
+        else *f.dnorm = t;
+      }
+      __syncthreads();
     }
-    const double sn = block_sum(vn, scratch);
-    const double sp = block_sum(vp, scratch);
-    if (tid == 0) { part[0] = sn; part[1] = sp; }
+    if (f.est.out != nullptr) scalar_sums(f.state, f.rows, S, scratch, f.est_part);
+  } else {
+    const int cb = (f.m + kFinishCols - 1) / kFinishCols;                  // runs of 32 cells per sketch row
+    const int chunks = (f.rows + f.wl - 1) / f.wl;                         // workgroups per run
+    const int b = ((int)blockIdx.x - 1) / chunks, k0 = ((int)blockIdx.x - 1 - b * chunks) * f.wl;
+    const int i = b / cb;
+    const int r = group_of(f.l, f.R, i);
+    int rstart, rcnt;
+    group_range(f.l, f.R, r, &rstart, &rcnt);
+    const int col = tid & (kFinishCols - 1), y = tid / kFinishCols;
+    const int c = (b - i * cb) * kFinishCols + col;
+    const int slices = kFinishLanes / f.wl, kk = y & (f.wl - 1), slice = y / f.wl;
+    const int GR = f.G * f.R;
+    const size_t pstep = (size_t)f.rows * cells;                           // places of one partition
+    const size_t in_group = (size_t)(i - rstart) * f.m + c;
+    const int k = k0 + kk;
+    const bool live = k < f.rows && c < f.m;
+    double acc = 0.0;
+    if (live) {
+      const unsigned char* const base = f.part_sk + ((size_t)k * cells + (size_t)rstart * f.m) * 8;
+      const CellUnit* const un = f.units + (f.rows > 1 ? group_of(f.rows, f.G, k) * f.R : 0) + r;
+      if (path != 0) {
+        for (int p = slice; p < f.P; p += slices) {
+          const CellUnit u = un[(size_t)p * GR];
+          const unsigned char* q = base + p * pstep * 8;
+          acc += u.unit * (u.kind == kCellI32   ? (double)reinterpret_cast<const int*>(q)[in_group]
+                           : u.kind == kCellI64 ? (double)reinterpret_cast<const long long*>(q)[in_group]
+                                                : reinterpret_cast<const double*>(q)[in_group]);
+        }
+      } else if (mean) {
+        acc = sum_partials(reinterpret_cast<const long long*>(base) + in_group, pstep, un, GR, slice, slices, f.P);
+      } else {
+        acc = sum_partials(reinterpret_cast<const int*>(base) + in_group, pstep * 2, un, GR, slice, slices, f.P);
+      }
+    }
+    sh[y][col] = acc;
+    __syncthreads();
+    if (slice == 0) {
+      double t = 0.0;
+      for (int q = 0; q < slices; ++q) t += sh[q * f.wl + kk][col];
+      const float v = (float)(mean ? t / (double)f.K : t);
+      if (live) agent_store(f.state + (size_t)k * S + 2 + (size_t)i * f.m + c, v);
+      st[kk][col] = v;
+    }
+    __syncthreads();
+    // (only the last workgroup of a run goes on to the counter of the launch: hundreds of additions to one
+    // address take microseconds)
+    if (chunks > 1 && !finished_last(f.ticket + 1 + b, chunks, &last)) return;
+    if (f.est.out != nullptr) {
+      double avg = 0.0;
+      if (chunks == 1) {
+        if (y == 0)
+          for (int q = 0; q < f.rows; ++q) avg += (double)st[q][col];
+      } else {
+        for (int kb = 0; kb < f.rows; kb += kFinishStates) {
+          float x[kFinishStates / kFinishLanes];
+#pragma unroll
+          for (int q = 0; q < kFinishStates / kFinishLanes; ++q) {
+            const int kq = kb + q * kFinishLanes + y;
+            x[q] = kq < f.rows && c < f.m ? agent_load(f.state + (size_t)kq * S + 2 + (size_t)i * f.m + c) : 0.0f;
+          }
+#pragma unroll
+          for (int q = 0; q < kFinishStates / kFinishLanes; ++q) st[q * kFinishLanes + y][col] = x[q];
+          __syncthreads();
+          if (y == 0)
+            for (int q = 0; q < kFinishStates && kb + q < f.rows; ++q) avg += (double)st[q][col];
+          __syncthreads();
+        }
+      }
+      if (tid < 64) {
+        avg /= (double)f.rows;
+        const double s = half_wave_sum(y == 0 && c < f.m ? avg * avg : 0.0);
+        if (tid == 0) agent_store(f.est_part + 2 + b, s);
+      }
+    }
+    if (chunks > 1 && tid == 0) f.ticket[1 + b] = 0u;
   }
+  const int runs = f.l * ((f.m + kFinishCols - 1) / kFinishCols);
+  if (!finished_last(f.ticket, runs + 1, &last)) return;
+  if (f.est.out != nullptr) finish_estimate(f.est, f.est_part, kEstCols / kFinishCols, cells ? path : -1);
   if (tid == 0) {
-    __threadfence();
-    last = (atomicAdd(ticket, 1u) == gridDim.x - 1) ? 1 : 0;
+    f.path->last = path;
+    f.path->now = 0;
+    *f.ticket = 0u;
   }
-  __syncthreads();
-  if (!last || tid != 0) return;
-  __threadfence();
-  const volatile double* vpart = part;
-  fda_estimate e;
-  e.mean_sqnorm = vpart[0] / (double)K;
-  e.mean_proj = 0.0; e.m2 = 0.0; e.h_linear = 0.0; e.h_sketch = 0.0;
-  e.sync_linear = 0; e.sync_sketch = 0; e.near_tie_linear = 0; e.near_tie_sketch = 0;
-  e.nonfinite = 0;
-  // which kind of sketch cell the last state pass used (scale: its record, or NULL)
-  e.state_path = -1;
-  if (cells && scale != nullptr)
-    e.state_path = mean_mode ? (scale->flagm ? 1 : 0) : (scale->overflow64 ? 2 : (scale->flag32 ? 1 : 0));
-  const double band = tie_tol * fmax(e.mean_sqnorm, fabs(theta));
-  if (variants & FDA_VARIANT_LINEAR) {
-    e.mean_proj = vpart[1] / (double)K;
-    e.h_linear = e.mean_sqnorm - e.mean_proj * e.mean_proj;
-    if (isfinite(e.h_linear)) {
-      e.sync_linear = e.h_linear > theta ? 1 : 0;
-      e.near_tie_linear = fabs(e.h_linear - theta) <= band ? 1 : 0;
-    } else {
-      e.sync_linear = 1; e.nonfinite = 1;
-    }
-  }
-  if (cells) {
-    // median of l values: insertion sort, then middle (even l: mean of the two middle)
-    double r[FDA_MAX_SKETCH_ROWS];
-    for (int i = 0; i < l; ++i) {
-      double v = 0.0;
-      for (int b = 0; b < bpr; ++b) v += vpart[2 + i * bpr + b];
-      int q = i;
-      while (q > 0 && !(r[q - 1] <= v)) { r[q] = r[q - 1]; --q; }
-      r[q] = v;
-    }
-    e.m2 = (l & 1) ? r[l / 2] : 0.5 * (r[l / 2 - 1] + r[l / 2]);
-    e.h_sketch = e.mean_sqnorm - e.m2 / (1.0 + eps);
-    if (isfinite(e.h_sketch)) {
-      e.sync_sketch = e.h_sketch > theta ? 1 : 0;
-      e.near_tie_sketch = fabs(e.h_sketch - theta) <= band ? 1 : 0;
-    } else {
-      e.sync_sketch = 1; e.nonfinite = 1;
-    }
-  }
-  *out = e;
-  *ticket = 0u;
 }
 
 // ----------------------------------------------------------------------------------------

@@ -1,0 +1,89 @@
+"""The unit a workgroup chooses for its own sketch terms, and what it does where that unit does not hold:
+one workgroup out of range among many, drifts that no sample of the chunk sees, chunks without any drift,
+and the kernels that redo a sketch in several windows (one worker slot), skewed, placed and plain layouts
+and several row groups.  Always against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import fda_synth as S
+from fda_tolerance import check_cells
+from oracle import fda_oracle as O
+
+pytestmark = pytest.mark.gpu
+RTOL = 1e-5
+DEV = "cuda:0"
+
+
+def drifts(kind, K, d, g):
+    u = torch.randn((K, d), generator=g, device=DEV) * 1e-4
+    if kind == "outlier":                 # one worker of one chunk, off the sampled runs of 8
+        u[K - 1, d // 2 + 13] = 0.9
+    elif kind == "sparse":                # nothing but a few coordinates move
+        keep = torch.zeros(d, dtype=torch.bool, device=DEV)
+        keep[torch.randint(0, d, (9,), generator=g, device=DEV)] = True
+        u *= keep
+    elif kind == "frozen":                # most chunks do not move at all, one coordinate among them does
+        u[:, : 3 * d // 4] = 0.0
+        u[0, d // 3] = 2e-4
+    elif kind == "uneven":                # a layer whose drifts are 10^4 times the others'
+        u[:, d // 4: d // 4 + d // 50 + 1] *= 1e4
+    return u
+
+
+@pytest.mark.parametrize("kind", ["outlier", "sparse", "frozen", "uneven"])
+@pytest.mark.parametrize("K,d,l,m,dtype", [
+    (1, 90_001, 3, 500, "f32"),           # one slot, plain rows: redone in two windows
+    (2, 60_003, 2, 5000, "f32"),          # two slots, plain rows
+    (3, 70_001, 5, 251, "bf16"),          # four slots with a spare one, skewed and placed
+    (8, 120_007, 9, 250, "bf16"),         # two row groups
+    (20, 50_001, 5, 33, "f32"),           # six slots, placed; more workers than the mean-state pass samples
+])
+def test_units_and_redo(kind, K, d, l, m, dtype):
+    import paper_2405_20988_amd as F
+    g = torch.Generator(device=DEV)
+    g.manual_seed(40 + K)
+    w_t0 = (torch.randn(d, generator=g, device=DEV) * 0.05).to(torch.bfloat16).float()
+    xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    w = (w_t0 + drifts(kind, K, d, g)).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    coef = S.hash_coefficients(40 + K, l)
+    mon = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, coef, device=DEV)
+    w_host, w0_host, xi_host = S.slab_to_numpy(w), w_t0.cpu().numpy(), xi.cpu().numpy()
+    ref = O.local_state(w_host, dtype, w0_host, xi_host, coef, m)
+    mref = O.mean_state(w_host, dtype, w0_host, xi_host, coef, m)
+    for _ in range(2):                    # the second call starts from what the first one left
+        mon.local_state(w, w_t0, xi)
+        n, p, sk = mon.state_numpy()
+        assert np.allclose(n, ref["n"], rtol=RTOL, atol=0)
+        assert (np.abs(p - ref["p"]) <= RTOL * ref["p_abs"] + 1e-30).all()
+        check_cells(sk, ref["sk"], ref["sk_abs"], ref["sk_cnt"], ref["u_mean_abs"])
+        path = mon.last_state_path()
+        assert mon.estimate_variance(1e30).state_path == path
+        if kind == "outlier" and dtype == "f32":
+            assert path >= 1
+        mon.mean_state(w, w_t0, xi)
+        nb, pb, skb = mon.mean_numpy()
+        assert nb == pytest.approx(mref["n"], rel=RTOL)
+        assert abs(pb - mref["p"]) <= RTOL * mref["p_abs"] + 1e-30
+        check_cells(skb, mref["sk"], mref["sk_abs"], mref["sk_cnt"], mref["u_mean_abs"])
+    mon.close()
+
+
+@pytest.mark.parametrize("K,d,l,m", [(1, 5, 1, 1), (2, 70_001, 1, 31), (17, 30_001, 2, 33), (33, 9_001, 3, 257),
+                                     (5, 400_001, 16, 64), (40, 2_049, 8, 1000)])
+def test_step_estimate_equals_estimate_of_its_states(K, d, l, m):
+    """fda_step takes the estimate in the launch that merges the partials, fda_estimate_variance from the
+    states: the same bits, whatever the number of workers, cells and partitions."""
+    import paper_2405_20988_amd as F
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K)
+    w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+    xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    w = w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3
+    mon = F.FdaMonitor(K, d, "f32", 3, l, m, 0.06, S.hash_coefficients(K, l), device=DEV)
+    w_prev = w_t0.clone()
+    for mean in (False, True, False):
+        a = mon.step(w, w_t0, w_prev, xi, 1e30, mean=mean, want_host=True).as_dict()
+        b = (mon.estimate_variance_mean(1e30) if mean else mon.estimate_variance(1e30)).as_dict()
+        assert a == b
+    mon.close()
