@@ -1046,10 +1046,11 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
       reinterpret_cast<const unsigned char*>(out_dev) +
       (decide_by == FDA_VARIANT_LINEAR ? offsetof(fda_estimate, sync_linear)
                                        : offsetof(fda_estimate, sync_sketch)));
-  int rc = mean ? fda_mean_state(ctx, w, w_t0, xi, state, w_bar, stream) : fda_local_state(ctx, w, w_t0, xi, state, stream);
+  // the estimate is part of the launch that merges the partials of the state pass
+  fda::EstimateArgs est;
+  int rc = estimate_args(ctx, mean ? 1 : ctx->desc.K, theta, tie_tol, out_dev, &est);
   if (rc != FDA_OK) return rc;
-  rc = mean ? fda_estimate_variance_mean(ctx, state, theta, tie_tol, out_dev, nullptr, stream)
-            : fda_estimate_variance(ctx, state, theta, tie_tol, out_dev, nullptr, stream);
+  rc = mean ? mean_state_pass(ctx, w, w_t0, xi, state, w_bar, &est, stream) : local_state(ctx, w, w_t0, xi, state, &est, stream);
   if (rc != FDA_OK) return rc;
   if (w_bar != nullptr) {
     rc = fda_sync_from_mean(ctx, w, w_t0, w_prev, xi, w_bar, pred, stream);
