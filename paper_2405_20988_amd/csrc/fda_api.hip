@@ -60,8 +60,8 @@ constexpr double kPairAddCost = 13.0;      // one 64-bit LDS addition (two cells
 constexpr double kPlacedPairAddCost = 9.5; // ... when the table's row slots are placed against LDS collisions
 constexpr double kSharedByteCost = 0.25;   // per byte of w_t0 / xi / table read by one more workgroup
 constexpr int kXiBlocks = 4096;
-constexpr int kSyncNormSlices = 64;   // the synchronization kernel's partial norms are condensed to this many
-constexpr long long kSyncVectorsPerBlock = 4 * fda::kSmallThreads;   // four trips per workgroup
+constexpr int64_t kSyncSmall = 3ll << 19;  // coordinates below which the synchronization takes small blocks
+constexpr int kSyncBlocks = 49152;         // workgroups of a synchronization kernel at most
 constexpr long long kStreamBytes = 512ll << 20;   // slabs beyond this are synchronized with streaming hints
 constexpr int kPathWords = 64;        // the two path records, on lines of their own
 constexpr int64_t kAlign = 256;
@@ -91,7 +91,8 @@ struct Plan {
   int mean_words;   // ... and of the mean-state pass's table
   bool shared_table;  // both passes split the rows alike and stream one table
   int64_t cells, S, dpad;
-  int tickets;        // finished-workgroup counters: [0] estimate_kernel, then those of finish_kernel
+  int tickets;        // finished-workgroup counters: [0] estimate_kernel, then those of finish_kernel ...
+  int sync_ticket;    // ... and, from here on, those of the synchronization kernel
   int64_t off_np, off_sk, off_units, off_xi, off_syncnorm, off_path, off_ticket, off_dnorm, off_est, off_table,
       off_mean_table, ws_bytes;
 };
@@ -269,6 +270,16 @@ int make_mean_split(const fda_desc* d, int cus, int64_t lds_cu, MeanSplit* ms) {
   return FDA_OK;
 }
 
+// Workgroups of a synchronization kernel, the blocks each of them takes, and the vectors per thread of a block:
+// small ones where 4096 coordinates per workgroup would leave CUs without a workgroup or two.  (Measured: 1M coordinates 22.6 us small, 23.7 large; 2M x 8 bf16 16.6 and 15.7.)
+struct SyncGrid { long long blocks; int per, vecs; };
+SyncGrid sync_grid(int64_t d) {
+  const int vecs = d < kSyncSmall ? fda::kSyncVecsSmall : fda::kSyncVecs;
+  const long long n = (d + fda::sync_block(vecs) - 1) / fda::sync_block(vecs);
+  const int per = (int)((n + kSyncBlocks - 1) / kSyncBlocks);
+  return {(n + per - 1) / per, per, vecs};
+}
+
 int make_plan(const fda_desc* d, int cus, int64_t lds_cu, Plan* pl) {
   if (cus < 1 || lds_cu < 16384) return fail(FDA_EINVAL, "bad device description");
   const bool sk = (d->variants & FDA_VARIANT_SKETCH) != 0;
@@ -289,13 +300,14 @@ int make_plan(const fda_desc* d, int cus, int64_t lds_cu, Plan* pl) {
   pl->off_sk = round_up(pl->off_np + np_bytes, kAlign);
   pl->off_units = round_up(pl->off_sk + sk_bytes, kAlign);
   pl->off_xi = round_up(pl->off_units + unit_count * (int64_t)sizeof(fda::CellUnit), kAlign);
-  // one partial norm per workgroup of the synchronization kernel, and their sum
-  const int64_t sync_blocks = ((d->d + fda::kSyncV - 1) / fda::kSyncV + kSyncVectorsPerBlock - 1) / kSyncVectorsPerBlock;
+  // one partial norm per workgroup of the synchronization kernel and one per group of them
+  const int64_t sync_blocks = sync_grid(d->d).blocks, sync_groups = (sync_blocks + fda::kSyncGroup - 1) / fda::kSyncGroup;
   pl->off_syncnorm = round_up(pl->off_xi + kXiBlocks * 8, kAlign);
-  pl->off_path = round_up(pl->off_syncnorm + (sync_blocks + kSyncNormSlices) * 8, kAlign);
+  pl->off_path = round_up(pl->off_syncnorm + (sync_blocks + sync_groups) * 8, kAlign);
   pl->off_ticket = pl->off_path + kPathWords * 4;
   const int64_t runs = sk ? (int64_t)d->l * ((d->m + fda::kFinishCols - 1) / fda::kFinishCols) : 0;   // of 32 cells
-  pl->tickets = 2 + (int)runs;
+  pl->sync_ticket = 2 + (int)runs;
+  pl->tickets = pl->sync_ticket + (int)sync_groups;
   pl->off_dnorm = round_up(pl->off_ticket + (int64_t)pl->tickets * 4, kAlign);
   pl->off_est = round_up(pl->off_dnorm + 8, kAlign);
   pl->off_table = round_up(pl->off_est + (2 + runs) * 8, kAlign);   // one piece of a row norm per run
@@ -924,6 +936,21 @@ int fda_sync_xi(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, co
   if (reinterpret_cast<uintptr_t>(xi) % 4 != 0) return fail(FDA_EINVAL, "pointer not aligned to its element type");
   return sync_impl(ctx, w, w_t0, w_prev, xi, pred_dev, stream);
 }
+// the instantiation for the slab type, the streaming hints and the block size (small blocks: hints only help
+// slabs far beyond that size)
+#define FDA_SYNC_PICK()                                                                                \
+  do {                                                                                                 \
+    const bool small = sg.vecs == fda::kSyncVecsSmall;                                                  \
+    if (d.dtype == FDA_F32) {                                                                          \
+      if (small) FDA_SYNC_LAUNCH(float, false, fda::kSyncVecsSmall);                                    \
+      else if (hinted) FDA_SYNC_LAUNCH(float, true, fda::kSyncVecs);                                    \
+      else FDA_SYNC_LAUNCH(float, false, fda::kSyncVecs);                                               \
+    } else {                                                                                           \
+      if (small) FDA_SYNC_LAUNCH(fda::bf16_t, false, fda::kSyncVecsSmall);                              \
+      else if (hinted) FDA_SYNC_LAUNCH(fda::bf16_t, true, fda::kSyncVecs);                              \
+      else FDA_SYNC_LAUNCH(fda::bf16_t, false, fda::kSyncVecs);                                         \
+    }                                                                                                  \
+  } while (0)
 namespace {
 // xi != NULL: the synchronization kernel also leaves the squared norm of the model change, and xi is
 // written by the scaling pass of fda_update_xi alone
@@ -938,33 +965,32 @@ int sync_impl(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, cons
       (w_prev && reinterpret_cast<uintptr_t>(w_prev) % 4 != 0))
     return fail(FDA_EINVAL, "pointer not aligned to its element type");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int vec_ok = kVecOk;
-  const int V = fda::kSyncV;
-  const long long nvec = (d.d + V - 1) / V;
-  const long long blocks = (nvec + kSyncVectorsPerBlock - 1) / kSyncVectorsPerBlock;
+  const SyncGrid sg = sync_grid(d.d);
   const bool hinted = (long long)d.K * d.d * (d.dtype == FDA_F32 ? 4 : 2) > kStreamBytes;
-  const dim3 grid((unsigned)blocks), block(fda::kSmallThreads);
+  const dim3 grid((unsigned)sg.blocks), block(fda::kSmallThreads);
   double* norm_part = xi != nullptr ? reinterpret_cast<double*>(ctx->ws + ctx->plan.off_syncnorm) : nullptr;
-#define FDA_SYNC_LAUNCH(T, S)                                                                          \
-  hipLaunchKernelGGL((fda::sync_kernel<T, S>), grid, block, 0, st, static_cast<T*>(w), w_t0, w_prev,   \
-                     pred_dev, d.K, (long long)d.d, (long long)d.row_stride, vec_ok, norm_part)
-  if (d.dtype == FDA_F32) { if (hinted) FDA_SYNC_LAUNCH(float, true); else FDA_SYNC_LAUNCH(float, false); }
-  else { if (hinted) FDA_SYNC_LAUNCH(fda::bf16_t, true); else FDA_SYNC_LAUNCH(fda::bf16_t, false); }
+  double* norm_group = reinterpret_cast<double*>(ctx->ws + ctx->plan.off_syncnorm) + sg.blocks;
+  unsigned int* ticket = reinterpret_cast<unsigned int*>(ctx->ws + ctx->plan.off_ticket) + ctx->plan.sync_ticket;
+  if (xi != nullptr) {
+    rcd = clear_tickets_once(ctx, st);
+    if (rcd != FDA_OK) return rcd;
+  }
+#define FDA_SYNC_LAUNCH(T, S, N)                                                                       \
+  hipLaunchKernelGGL((fda::sync_kernel<T, S, N>), grid, block, 0, st, static_cast<T*>(w), w_t0, w_prev, \
+                     pred_dev, d.K, (long long)d.d, (long long)d.row_stride, sg.per, norm_part, norm_group, ticket)
+  FDA_SYNC_PICK();
 #undef FDA_SYNC_LAUNCH
   FDA_HIP(hipGetLastError());
   if (xi != nullptr) {
-    // the partial norms -> a few (fixed order), then the scaling pass: xi = (w_t0 - w_prev) / norm
-    double* total = norm_part + blocks;
-    hipLaunchKernelGGL(fda::sum_partials_kernel, dim3(kSyncNormSlices), dim3(fda::kSmallThreads), 0, st,
-                       norm_part, blocks, pred_dev, total);
-    FDA_HIP(hipGetLastError());
+    // the scaling pass: xi = (w_t0 - w_prev) / norm
+    const int vec_ok = kVecOk;
     const long long items = vec_ok ? (d.d + 3) / 4 : d.d;
     long long sblocks = (items + fda::kSmallThreads - 1) / fda::kSmallThreads;
     const long long cap = (long long)ctx->cus * 16;
     if (sblocks > cap) sblocks = cap;
     if (sblocks < 1) sblocks = 1;
     hipLaunchKernelGGL(fda::xi_scale_kernel, dim3((unsigned)sblocks), dim3(fda::kSmallThreads), 0, st,
-                       w_t0, w_prev, xi, pred_dev, (long long)d.d, vec_ok, total, kSyncNormSlices);
+                       w_t0, w_prev, xi, pred_dev, (long long)d.d, vec_ok, norm_group, (int)((sg.blocks + fda::kSyncGroup - 1) / fda::kSyncGroup));
     FDA_HIP(hipGetLastError());
   }
   return FDA_OK;
@@ -984,18 +1010,14 @@ int fda_sync_from_mean(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float*
       (xi && reinterpret_cast<uintptr_t>(xi) % 4 != 0))
     return fail(FDA_EINVAL, "pointer not aligned to its element type");
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int vec_ok = kVecOk;
-  const int V = fda::kSyncV;
-  const long long nvec = (d.d + V - 1) / V;
-  const long long blocks = (nvec + kSyncVectorsPerBlock - 1) / kSyncVectorsPerBlock;
+  const SyncGrid sg = sync_grid(d.d);
   const bool hinted = (long long)d.K * d.d * (d.dtype == FDA_F32 ? 4 : 2) > kStreamBytes;
-  const dim3 grid((unsigned)blocks), block(fda::kSmallThreads);
+  const dim3 grid((unsigned)sg.blocks), block(fda::kSmallThreads);
   const double* dnorm = reinterpret_cast<const double*>(ctx->ws + ctx->plan.off_dnorm);
-#define FDA_SYNC_LAUNCH(T, S)                                                                          \
-  hipLaunchKernelGGL((fda::sync_from_mean_kernel<T, S>), grid, block, 0, st, static_cast<T*>(w), w_t0, \
-                     w_prev, xi, w_bar, dnorm, pred_dev, d.K, (long long)d.d, (long long)d.row_stride, vec_ok)
-  if (d.dtype == FDA_F32) { if (hinted) FDA_SYNC_LAUNCH(float, true); else FDA_SYNC_LAUNCH(float, false); }
-  else { if (hinted) FDA_SYNC_LAUNCH(fda::bf16_t, true); else FDA_SYNC_LAUNCH(fda::bf16_t, false); }
+#define FDA_SYNC_LAUNCH(T, S, N)                                                                       \
+  hipLaunchKernelGGL((fda::sync_from_mean_kernel<T, S, N>), grid, block, 0, st, static_cast<T*>(w), w_t0, w_prev, \
+                     xi, w_bar, dnorm, pred_dev, d.K, (long long)d.d, (long long)d.row_stride, sg.per)
+  FDA_SYNC_PICK();
 #undef FDA_SYNC_LAUNCH
   FDA_HIP(hipGetLastError());
   return FDA_OK;

@@ -99,7 +99,8 @@ __device__ __forceinline__ VecT load_vec_hint(const void* p) {
   if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const VecT*>(p));
   else return *reinterpret_cast<const VecT*>(p);
 }
-typedef uint32_t u32x4_a16 __attribute__((ext_vector_type(4)));               // 16-byte aligned (LDS)
+typedef uint32_t u32x4_a16 __attribute__((ext_vector_type(4)));               // 16-byte aligned
+typedef uint32_t u32x2_a8 __attribute__((ext_vector_type(2)));                // 8-byte aligned
 constexpr bool kNtSlab = FDA_NT_SLAB != 0;
 constexpr bool kNtShared = FDA_NT_SHARED != 0;
 

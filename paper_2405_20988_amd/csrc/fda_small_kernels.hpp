@@ -499,28 +499,36 @@ finish_kernel(const FinishParams f) {
 
 // ----------------------------------------------------------------------------------------
 // Algorithm 1 line 9: read the K rows once, average in fp32 in worker order, write the
-// average to every row, to w_t0, and the old w_t0 to w_prev.
+// average to every row, to w_t0, and the old w_t0 to w_prev.  Or (sync_from_mean_kernel) the same when the
+// average model is already there, with the xi of Section 3.2.
 //
-// A lane owns 4 consecutive coordinates (16 bytes of fp32, 8 bytes of bf16), so every load and store
-// instruction of a wave covers whole cache lines, and workgroup b owns the contiguous range of such
-// vectors [b * per, (b + 1) * per), a few trips long (the host launches one workgroup per 1024
-// vectors): workgroups that run at the same time work on neighbouring addresses of every row, which
-// is what keeps the K + 2 interleaved read and write streams efficient in DRAM (ranges of hundreds
-// of KiB per workgroup cost a bf16 slab's pass a third of its rate).  STREAM: every byte is read once
+// Both are bound by HBM.  A workgroup takes one block of 4096 coordinates (two, and so on, where that would be
+// more than 49152 workgroups): workgroups launched in address order work on neighbouring addresses of every
+// row when they run together, which is what keeps the K + 2 interleaved read and write streams efficient in DRAM
+// (2048 workgroups that take every 2048th block: 5.1 instead of 5.5 TB/s on 8 x 150 000 000 bf16; ranges of
+// hundreds of KiB per workgroup: 3.5).  The limit is for launches whose predicate is zero, which cost 0.2 ns
+// per workgroup (350M coordinates: 21 us, now 12).  A lane owns 4 consecutive coordinates of a wave's 256 (16 bytes
+// of fp32, 8 bytes of bf16), so the fp32 vectors are moved in whole lines.  STREAM: every byte is read once
 // and written once, so loads and stores carry the nontemporal hint -- chosen by the host for slabs
-// too large to stay in the memory-side cache, where it gains 3-8 %; small slabs lose by it.  (With 8
-// coordinates per lane the fp32 vectors of a bf16 slab's pass become two 16-byte accesses 32 bytes
-// apart: half cache lines per instruction, which the hinted stores pay for twice.)
+// too large to stay in the memory-side cache, where it gains 3-8 %; small slabs lose by it.
+//
+// The rows of a slab whose row length is no multiple of 128 bytes start anywhere in a line.  Storing to them
+// with the lanes of the average would split one line of every four (bf16; eight for fp32) between two store
+// instructions, and partly written lines cost DRAM a read: 8 x 150 000 001 bf16 ran at 4.0 TB/s where
+// 8 x 150 000 000 ran at 5.1.  So the average goes through LDS, and every row is stored in 16-byte vectors
+// counted from its own first line boundary; one line in 64 (fp32: 128) is split.
 // ----------------------------------------------------------------------------------------
-constexpr bool kSyncContiguous = true;
-constexpr int kSyncV = 4;                    // coordinates per lane in the synchronization kernels
+constexpr int kSyncV = 4;                    // coordinates per lane and vector
+constexpr int kSyncVecs = 4;                 // vectors per thread and block: 4096 coordinates ...
+constexpr int kSyncVecsSmall = 1;            // ... or 1024, where the larger blocks would not fill the chip
+__host__ __device__ constexpr int sync_block(int vecs) { return vecs * kSyncV * kSmallThreads; }
 
 template <typename VecT, bool NT>
 __device__ __forceinline__ void store_vec_hint(void* p, VecT v) {
   if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<VecT*>(p));
   else *reinterpret_cast<VecT*>(p) = v;
 }
-// 4 slab elements at p as floats, and back
+// 4 slab elements at p as floats
 template <bool NT>
 __device__ __forceinline__ void load_slab4(const float* p, float (&x)[4]) {
   const f32x4 t = load_vec_hint<f32x4, NT>(p);
@@ -537,170 +545,191 @@ __device__ __forceinline__ void store_f32x4(float* p, const float (&x)[4]) {
   const f32x4 t = {x[0], x[1], x[2], x[3]};
   store_vec_hint<f32x4, NT>(p, t);
 }
-// what a slab row stores for 4 averaged values: the fp32 values, or their bf16 roundings (packed)
-struct RowVec4 { uint32_t w[4]; };
-__device__ __forceinline__ RowVec4 pack_row4(const float (&x)[4], const float*) {
-  RowVec4 r;
-  r.w[0] = __float_as_uint(x[0]); r.w[1] = __float_as_uint(x[1]);
-  r.w[2] = __float_as_uint(x[2]); r.w[3] = __float_as_uint(x[3]);
-  return r;
+// what a slab row stores for 4 averaged values (the fp32 values, or their bf16 roundings), into the block's
+// image in LDS
+__device__ __forceinline__ void stage4(uint32_t* img, int e, const float (&x)[4], const float*) {
+  const u32x4_a16 t = {__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+  *reinterpret_cast<u32x4_a16*>(img + e) = t;
 }
-__device__ __forceinline__ RowVec4 pack_row4(const float (&x)[4], const bf16_t*) {
-  RowVec4 r;
-  r.w[0] = f32_to_bf16_rne(x[0]) | (f32_to_bf16_rne(x[1]) << 16);
-  r.w[1] = f32_to_bf16_rne(x[2]) | (f32_to_bf16_rne(x[3]) << 16);
-  r.w[2] = 0u; r.w[3] = 0u;
-  return r;
+__device__ __forceinline__ void stage4(uint32_t* img, int e, const float (&x)[4], const bf16_t*) {
+  const u32x2_a8 t = {f32_to_bf16_rne(x[0]) | (f32_to_bf16_rne(x[1]) << 16),
+                      f32_to_bf16_rne(x[2]) | (f32_to_bf16_rne(x[3]) << 16)};
+  *reinterpret_cast<u32x2_a8*>(img + e / 2) = t;
 }
-template <bool NT>
-__device__ __forceinline__ void store_row4(float* p, const RowVec4& r) {
-  const u32x4 t = {r.w[0], r.w[1], r.w[2], r.w[3]};
-  store_vec_hint<u32x4, NT>(p, t);
-}
-template <bool NT>
-__device__ __forceinline__ void store_row4(bf16_t* p, const RowVec4& r) {
-  const u32x2_h t = {r.w[0], r.w[1]};
-  store_vec_hint<u32x2_h, NT>(p, t);
-}
-
-// the range of vectors a workgroup walks, and its stride
-struct SyncRange { long long beg, end, step; };
-__device__ __forceinline__ SyncRange sync_range(long long nvec) {
-  SyncRange r;
-  if (kSyncContiguous) {
-    const long long per = (nvec + gridDim.x - 1) / gridDim.x;
-    r.beg = (long long)blockIdx.x * per;
-    r.end = r.beg + per < nvec ? r.beg + per : nvec;
-    r.step = blockDim.x;
-  } else {
-    r.beg = (long long)blockIdx.x * blockDim.x;
-    r.end = nvec;
-    r.step = (long long)gridDim.x * blockDim.x;
+// The image's first n elements to the K rows, from element c0 of each.
+template <typename T, bool NT>
+__device__ __forceinline__ void store_rows(T* w, long long row_stride, int K, long long c0, int n, const uint32_t* img) {
+  constexpr int kPer = 16 / (int)sizeof(T);          // elements of a 16-byte vector
+  const int tid = threadIdx.x;
+  const T* const elems = reinterpret_cast<const T*>(img);
+  for (int k = 0; k < K; ++k) {
+    T* const row = w + (long long)k * row_stride + c0;
+    const int off = (int)(reinterpret_cast<uintptr_t>(row) & 127u);
+    int head = off == 0 ? 0 : (128 - off) / (int)sizeof(T);      // elements in front of the row's first line boundary
+    if (head > n) head = n;
+    const int nvec = (n - head) / kPer;
+    const int odd = sizeof(T) == 2 ? head & 1 : 0;
+    for (int v = tid; v < nvec; v += kSmallThreads) {
+      const int e = head + v * kPer;
+      const uint32_t* src = img + (sizeof(T) == 2 ? e >> 1 : e);
+      u32x4_a16 t = {src[0], src[1], src[2], src[3]};
+      if (odd) {                                     // (the same for the whole row)
+        const uint32_t next = src[4];
+        t = u32x4_a16{__builtin_amdgcn_alignbit(t.y, t.x, 16), __builtin_amdgcn_alignbit(t.z, t.y, 16),
+                      __builtin_amdgcn_alignbit(t.w, t.z, 16), __builtin_amdgcn_alignbit(next, t.w, 16)};
+      }
+      store_vec_hint<u32x4_a16, NT>(row + e, t);
+    }
+    // the elements in front (fewer than 64) and behind the vectors (fewer than 8)
+    if (tid < head) row[tid] = elems[tid];
+    const int done = head + nvec * kPer;
+    if (tid >= 64 && tid - 64 < n - done) row[done + tid - 64] = elems[done + tid - 64];
   }
-  return r;
 }
 
-template <typename T, bool STREAM>
+constexpr int kSyncGroup = 64;       // workgroups whose shares of the norm are added up in the launch
+template <typename T, bool STREAM, int VECS>
 __global__ void __launch_bounds__(kSmallThreads)
 sync_kernel(T* __restrict__ w, float* __restrict__ w_t0, float* __restrict__ w_prev,
-            const int32_t* __restrict__ pred, int K, long long d, long long row_stride, int vec_ok,
-            double* __restrict__ norm_part) {
+            const int32_t* __restrict__ pred, int K, long long d, long long row_stride, int per,
+            double* __restrict__ norm_part, double* __restrict__ norm_group, unsigned int* __restrict__ ticket) {
   // norm_part != NULL: entry [workgroup] receives the workgroup's share of ||new w_t0 - old w_t0||^2
-  // (fp32 squares of four coordinates, then fp64), which saves the refresh of xi its pass over both vectors
-  constexpr int V = kSyncV;
+  // (fp32 squares of four coordinates, then fp64), which saves the refresh of xi its pass over both vectors.
+  // The last of 64 neighbouring workgroups to finish adds their shares up, in order, into norm_group (a launch
+  // of its own for that cost every step 4.7 us, also where nothing is synchronized).
+  constexpr int V = kSyncV, kBlock = sync_block(VECS), H = VECS >= 2 ? 2 : 1;
   __shared__ double scratch[kSmallThreads / 64];
+  __shared__ int last;
+  __shared__ __align__(16) uint32_t img[kBlock * sizeof(T) / 4 + 4];
   if (pred != nullptr && *pred == 0) return;
   double nacc = 0.0;
   const float kf = (float)K;
-  const SyncRange rg = sync_range((d + V - 1) / V);
-  for (long long vi = rg.beg + threadIdx.x; vi < rg.end; vi += rg.step) {
-    const long long j0 = vi * V;
-    float acc[V];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const long long cbeg = (long long)blockIdx.x * per * kBlock;
+  for (long long c0 = cbeg; c0 < cbeg + (long long)per * kBlock && c0 < d; c0 += kBlock) {
+    const int n = d - c0 < kBlock ? (int)(d - c0) : kBlock;
+#pragma unroll 1
+    for (int q = 0; q < VECS; q += H) {
+      // two vectors next to each other (a wave's 512 coordinates): the line they share is fetched once
+      const int e0 = (wave * VECS + q) * 64 * V + lane * V;
+      if (e0 + (H - 1) * 64 * V + V <= n) {
+        float acc[H][V];
 #pragma unroll
-    for (int v = 0; v < V; ++v) acc[v] = 0.0f;
-    if (vec_ok && j0 + V <= d) {
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[h][v] = 0.0f;
+        const T* src = w + c0 + e0;
 #pragma unroll 8
-      for (int k = 0; k < K; ++k) {
-        float x[V];
-        load_slab4<STREAM>(w + (long long)k * row_stride + j0, x);
+        for (int k = 0; k < K; ++k) {
 #pragma unroll
-        for (int v = 0; v < V; ++v) acc[v] += x[v];
-      }
+          for (int h = 0; h < H; ++h) {
+            float x[V];
+            load_slab4<STREAM>(src + (long long)k * row_stride + h * 64 * V, x);
 #pragma unroll
-      for (int v = 0; v < V; ++v) acc[v] = acc[v] / kf;
-      if (w_prev != nullptr || norm_part != nullptr) {
-        float old[V];
-        load_f32_vec<V, STREAM>(w_t0 + j0, old);
-        if (w_prev != nullptr) store_f32x4<STREAM>(w_prev + j0, old);
-        if (norm_part != nullptr) {
-          const float dx = acc[0] - old[0], dy = acc[1] - old[1], dz = acc[2] - old[2], dw = acc[3] - old[3];
-          nacc += (double)fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, dw * dw)));
+            for (int v = 0; v < V; ++v) acc[h][v] += x[v];
+          }
         }
-      }
-      store_f32x4<STREAM>(w_t0 + j0, acc);
-      const RowVec4 row = pack_row4(acc, static_cast<const T*>(nullptr));
-#pragma unroll 8
-      for (int k = 0; k < K; ++k) store_row4<STREAM>(w + (long long)k * row_stride + j0, row);
-    } else {
-      for (int v = 0; v < V; ++v) {
-        const long long j = j0 + v;
-        if (j >= d) break;
-        float a = 0.0f;
-        for (int k = 0; k < K; ++k) a += Slab<T>::load_one(w + (long long)k * row_stride + j);
-        a = a / kf;
-        const float o = w_t0[j];
-        if (w_prev != nullptr) w_prev[j] = o;
-        if (norm_part != nullptr) nacc += (double)((a - o) * (a - o));
-        w_t0[j] = a;
-        for (int k = 0; k < K; ++k) Slab<T>::store_one(w + (long long)k * row_stride + j, a);
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+          const long long j0 = c0 + e0 + h * 64 * V;
+#pragma unroll
+          for (int v = 0; v < V; ++v) acc[h][v] = acc[h][v] / kf;
+          if (w_prev != nullptr || norm_part != nullptr) {
+            float old[V];
+            load_f32_vec<V, STREAM>(w_t0 + j0, old);
+            if (w_prev != nullptr) store_f32x4<STREAM>(w_prev + j0, old);
+            if (norm_part != nullptr) {
+              const float dx = acc[h][0] - old[0], dy = acc[h][1] - old[1], dz = acc[h][2] - old[2], dw = acc[h][3] - old[3];
+              nacc += (double)fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, dw * dw)));
+            }
+          }
+          store_f32x4<STREAM>(w_t0 + j0, acc[h]);
+          stage4(img, e0 + h * 64 * V, acc[h], static_cast<const T*>(nullptr));
+        }
+      } else {
+        for (int h = 0; h < H; ++h)
+          for (int v = 0; v < V; ++v) {
+            const int e = e0 + h * 64 * V + v;
+            if (e >= n) break;
+            float a = 0.0f;
+            for (int k = 0; k < K; ++k) a += Slab<T>::load_one(w + (long long)k * row_stride + c0 + e);
+            a = a / kf;
+            const float o = w_t0[c0 + e];
+            if (w_prev != nullptr) w_prev[c0 + e] = o;
+            if (norm_part != nullptr) nacc += (double)((a - o) * (a - o));
+            w_t0[c0 + e] = a;
+            Slab<T>::store_one(reinterpret_cast<T*>(img) + e, a);
+          }
       }
     }
+    __syncthreads();
+    store_rows<T, STREAM>(w, row_stride, K, c0, n, img);
+    __syncthreads();
   }
   if (norm_part != nullptr) {
     const double s = block_sum(nacc, scratch);
-    if (threadIdx.x == 0) norm_part[blockIdx.x] = s;
+    if (threadIdx.x == 0) agent_store(norm_part + blockIdx.x, s);
+    const int g = blockIdx.x / kSyncGroup, first = g * kSyncGroup;
+    const int count = (int)gridDim.x - first < kSyncGroup ? (int)gridDim.x - first : kSyncGroup;
+    if (!finished_last(ticket + g, count, &last)) return;
+    if (threadIdx.x < 64) {
+      const double t = wave_sum((int)threadIdx.x < count ? agent_load(norm_part + first + threadIdx.x) : 0.0);
+      if (threadIdx.x == 0) { norm_group[g] = t; ticket[g] = 0u; }
+    }
   }
-}
-// n partial sums -> gridDim.x sums of contiguous slices, out[workgroup], each in a fixed order
-__global__ void __launch_bounds__(kSmallThreads)
-sum_partials_kernel(const double* __restrict__ part, long long n, const int32_t* __restrict__ pred,
-                    double* __restrict__ out) {
-  __shared__ double scratch[kSmallThreads / 64];
-  if (pred != nullptr && *pred == 0) return;
-  const long long per = (n + gridDim.x - 1) / gridDim.x;
-  const long long beg = (long long)blockIdx.x * per;
-  const long long end = beg + per < n ? beg + per : n;
-  double acc = 0.0;
-  for (long long t = beg + threadIdx.x; t < end; t += kSmallThreads) acc += part[t];
-  const double s = block_sum(acc, scratch);
-  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // Algorithm 1 line 9 when the average model is already there (w_bar from mean_state_kernel):
 // every row <- w_bar, w_prev <- w_t0, w_t0 <- w_bar, and (xi != NULL) the xi of Section 3.2,
 // (w_bar - old w_t0) / ||w_bar - old w_t0||, with the squared norm taken from *dnorm.
-template <typename T, bool STREAM>
+template <typename T, bool STREAM, int VECS>
 __global__ void __launch_bounds__(kSmallThreads)
 sync_from_mean_kernel(T* __restrict__ w, float* __restrict__ w_t0, float* __restrict__ w_prev,
                       float* __restrict__ xi, const float* __restrict__ w_bar,
                       const double* __restrict__ dnorm, const int32_t* __restrict__ pred, int K,
-                      long long d, long long row_stride, int vec_ok) {
-  constexpr int V = kSyncV;
+                      long long d, long long row_stride, int per) {
+  constexpr int V = kSyncV, kBlock = sync_block(VECS);
+  __shared__ __align__(16) uint32_t img[kBlock * sizeof(T) / 4 + 4];
   if (pred != nullptr && *pred == 0) return;
   float scale = 0.0f;
   if (xi != nullptr) {
     const double nrm = sqrt(*dnorm);
     scale = (nrm > 0.0 && isfinite(nrm)) ? (float)(1.0 / nrm) : 0.0f;
   }
-  const SyncRange rg = sync_range((d + V - 1) / V);
-  for (long long vi = rg.beg + threadIdx.x; vi < rg.end; vi += rg.step) {
-    const long long j0 = vi * V;
-    if (vec_ok && j0 + V <= d) {
-      float nb[V], old[V];
-      load_f32_vec<V, STREAM>(w_bar + j0, nb);
-      load_f32_vec<V, STREAM>(w_t0 + j0, old);
-      if (w_prev != nullptr) store_f32x4<STREAM>(w_prev + j0, old);
-      store_f32x4<STREAM>(w_t0 + j0, nb);
-      if (xi != nullptr) {
-        float x[V];
+  const long long cbeg = (long long)blockIdx.x * per * kBlock;
+  for (long long c0 = cbeg; c0 < cbeg + (long long)per * kBlock && c0 < d; c0 += kBlock) {
+    const int n = d - c0 < kBlock ? (int)(d - c0) : kBlock;
 #pragma unroll
-        for (int v = 0; v < V; ++v) x[v] = (scale == 0.0f) ? 0.0f : (nb[v] - old[v]) * scale;
-        store_f32x4<STREAM>(xi + j0, x);
-      }
-      const RowVec4 row = pack_row4(nb, static_cast<const T*>(nullptr));
-#pragma unroll 8
-      for (int k = 0; k < K; ++k) store_row4<STREAM>(w + (long long)k * row_stride + j0, row);
-    } else {
-      for (int v = 0; v < V; ++v) {
-        const long long j = j0 + v;
-        if (j >= d) break;
-        const float a = w_bar[j], o = w_t0[j];
-        if (w_prev != nullptr) w_prev[j] = o;
-        w_t0[j] = a;
-        if (xi != nullptr) xi[j] = (scale == 0.0f) ? 0.0f : (a - o) * scale;
-        for (int k = 0; k < K; ++k) Slab<T>::store_one(w + (long long)k * row_stride + j, a);
+    for (int q = 0; q < VECS; ++q) {
+      const int e0 = (q * kSmallThreads + (int)threadIdx.x) * V;
+      const long long j0 = c0 + e0;
+      if (e0 + V <= n) {
+        float nb[V], old[V];
+        load_f32_vec<V, STREAM>(w_bar + j0, nb);
+        load_f32_vec<V, STREAM>(w_t0 + j0, old);
+        if (w_prev != nullptr) store_f32x4<STREAM>(w_prev + j0, old);
+        store_f32x4<STREAM>(w_t0 + j0, nb);
+        if (xi != nullptr) {
+          float x[V];
+#pragma unroll
+          for (int v = 0; v < V; ++v) x[v] = (scale == 0.0f) ? 0.0f : (nb[v] - old[v]) * scale;
+          store_f32x4<STREAM>(xi + j0, x);
+        }
+        stage4(img, e0, nb, static_cast<const T*>(nullptr));
+      } else {
+        for (int v = 0; v < V; ++v) {
+          if (e0 + v >= n) break;
+          const float a = w_bar[j0 + v], o = w_t0[j0 + v];
+          if (w_prev != nullptr) w_prev[j0 + v] = o;
+          w_t0[j0 + v] = a;
+          if (xi != nullptr) xi[j0 + v] = (scale == 0.0f) ? 0.0f : (a - o) * scale;
+          Slab<T>::store_one(reinterpret_cast<T*>(img) + e0 + v, a);
+        }
       }
     }
+    __syncthreads();
+    store_rows<T, STREAM>(w, row_stride, K, c0, n, img);
+    __syncthreads();
   }
 }
 

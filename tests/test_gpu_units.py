@@ -87,3 +87,50 @@ def test_step_estimate_equals_estimate_of_its_states(K, d, l, m):
         b = (mon.estimate_variance_mean(1e30) if mean else mon.estimate_variance(1e30)).as_dict()
         assert a == b
     mon.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("d", [1, 63, 1023, 1024, 1025, 70_003, 1_572_863, 1_572_864, 1_577_059])
+def test_sync_stores_rows_at_every_alignment(dtype, d):
+    """Rows are stored in vectors counted from their own first line boundary: row lengths and row starts off
+    every boundary, block remainders on both sides of the small blocks' limit; nothing outside the rows moves."""
+    import paper_2405_20988_amd as F
+    from paper_2405_20988_amd import binding as B
+    K, pad = 4, 37                                   # (a division by 4 is exact: torch may multiply by 1 / K)
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    for first in (0, 1, 6, 63):                      # element offset of the slab in its allocation
+        buf = torch.full((first + K * (d + pad) + 64,), 7.0, device=DEV, dtype=tdt)
+        w = buf[first:first + K * (d + pad)].view(K, d + pad)[:, :d]
+        w.copy_((torch.randn((K, d), generator=g, device=DEV) * 0.05).to(tdt))
+        rows = w.clone()
+        w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+        old = w_t0.clone()
+        w_prev, xi, w_bar = torch.zeros_like(w_t0), torch.zeros_like(w_t0), torch.zeros_like(w_t0)
+        mon = F.FdaMonitor(K, d, dtype, 3, 1, 7, 0.06, S.hash_coefficients(1, 1), row_stride=d + pad, device=DEV)
+        st = torch.cuda.current_stream().cuda_stream
+        mean = torch.zeros_like(w_t0)
+        for k in range(K):
+            mean += rows[k].float()
+        mean /= K
+        for from_mean in (False, True):
+            w.copy_(rows)
+            w_t0.copy_(old)
+            if from_mean:
+                B.fda_mean_state(mon.ctx, w.data_ptr(), w_t0.data_ptr(), xi.data_ptr(), mon.mean.data_ptr(),
+                                 w_bar.data_ptr(), st)
+                B.fda_sync_from_mean(mon.ctx, w.data_ptr(), w_t0.data_ptr(), w_prev.data_ptr(), xi.data_ptr(),
+                                     w_bar.data_ptr(), None, st)
+                want = w_bar
+                assert torch.allclose(want, mean, rtol=1e-5, atol=1e-7)
+            else:
+                B.fda_sync_xi(mon.ctx, w.data_ptr(), w_t0.data_ptr(), w_prev.data_ptr(), xi.data_ptr(), None, st)
+                want = mean
+            assert torch.equal(w_t0, want) and torch.equal(w_prev, old)
+            assert torch.equal(w, want.to(tdt).expand(K, d))
+            assert float(xi.double().norm()) == pytest.approx(1.0, rel=1e-5)
+            out = buf.clone()
+            out[first:first + K * (d + pad)].view(K, d + pad)[:, :d] = 7.0
+            assert (out == 7.0).all()
+        mon.close()
