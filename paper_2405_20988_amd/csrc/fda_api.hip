@@ -166,7 +166,9 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, Split* sp) {
           const double per_add = KC % 2 == 0 ? (placed ? kPlacedPairAddCost
                                                             : split ? kPairAddCost : kPairAddCost + 2.0 * kSelectCost)
                                                          : kAtomicCost + kSelectCost;
-          const double cost = wg * KC * (split ? kElementCost : kElementCost + kNegateCost) +
+          // (Without a sketch the pass is bound by its loads: the bytes every worker slot and every workgroup's
+          // w_t0 and xi bring through the L2.  13 x 6.9M fp32: 7 groups of 2 slots 77 us, 2 of 8 69.)
+          const double cost = !cells ? wg * (KC * (d->dtype == FDA_F32 ? 4.1 : 2.05) + 8) : wg * KC * (split ? kElementCost : kElementCost + kNegateCost) +
                               wg * LR * (split ? kDecodeCost : kDecodeCost + kSignCost) +
                               wg * LR * pairs * per_add +
                               wg * (8 + 2 * LR) * kSharedByteCost + 1e-3 * wg;

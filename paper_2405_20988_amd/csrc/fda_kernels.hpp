@@ -166,10 +166,30 @@ __device__ __forceinline__ void store_f32_vec(float* p, const float (&x)[V]) {
   }
 }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-  return v;                                   // valid in lane 0
+// v of the lane that a DPP control names (0 where there is none, or where ROWS leaves the row out)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_move(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+// Sum over the wave in a fixed shape, valid in lane 63.  (Lane moves inside the vector ALU: the twelve sums of
+// a workgroup with six workers took 4 us through the LDS permutes of __shfl_down, and take 1 here.)
+__device__ __forceinline__ double wave_sum63(double v) {
+  v += dpp_move<0x111, 0xf>(v);               // row_shr 1, 2, 4, 8: lane 15 of every row of 16 has the row's sum
+  v += dpp_move<0x112, 0xf>(v);
+  v += dpp_move<0x114, 0xf>(v);
+  v += dpp_move<0x118, 0xf>(v);
+  v += dpp_move<0x142, 0xa>(v);               // row_bcast 15: rows 1 and 3 add the row before
+  v += dpp_move<0x143, 0xc>(v);               // row_bcast 31: rows 2 and 3 add rows 0 and 1
+  return v;
+}
+__device__ __forceinline__ double wave_sum(double v) {       // ... in every lane
+  v = wave_sum63(v);
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)b, 63), hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
 // Sum over the workgroup in a fixed shape; result valid in thread 0.  `scratch` holds one
@@ -546,6 +566,39 @@ state_kernel(const StateParams prm) {
   const float* const w0p = prm.w_t0;
   const float* const xip = lin ? prm.xi : prm.w_t0;   // without LinearFDA: any readable vector
 
+  // Tiles that lie wholly inside the chunk, counted per wave: 256 coordinates.  The two waves of a SIMD do not
+  // progress alike -- the LDS serves the older one first, and with equal shares the pass ended with the younger
+  // ones alone on their SIMDs, for 490 of 3100 us on cfg5, 270 of 950 on cfg4, 40 of 185 on cfg3 -- so the older
+  // ones (waves 0 to 3) take a larger share of a chunk.  Measured: the best share lies between 0.56 and 0.6 for
+  // bf16 slabs, 0.58 and 0.65 for fp32 (3 % on cfg5, 5 % on 7 x 18M bf16, 2 % on cfg4, 4 % on cfg3).  Leaving it to
+  // the waves who takes the next tile would not keep the order of the scalar sums; s_setprio does not move it, and
+  // neither do three waves per SIMD.
+  constexpr float kOlderShare = sizeof(T) == 4 ? 0.62f : 0.57f;
+  constexpr int kWaveTile = 64 * V, kHalf = kStateThreads / 128;        // kHalf waves of either kind
+  const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int full = cend > cbeg && prm.vec_ok ? (int)((cend - cbeg) / kTile) * 2 * kHalf : 0;     // wave tiles
+  const int older = (int)((float)(full / kHalf) * (prm.do_sk ? kOlderShare : 0.5f) + 0.5f), younger = full / kHalf - older;
+  const int mine = wave_id < kHalf ? older : younger;
+  // from a wave's it-th tile to its next one: all waves side by side as long as the younger ones have any
+  auto stride_after = [&](int it) { return it + 1 <= younger ? (long long)2 * kHalf * kWaveTile : (long long)kHalf * kWaveTile; };
+
+  // whole vectors, no tests
+  auto load_fast = [&](Tile& t, long long j0, bool sc, bool sk) {
+    load_f32_vec<V, kNtShared>(w0p + j0, t.w0);
+    if (sc) load_f32_vec<V, kNtShared>(xip + j0, t.x);
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+      if constexpr (sizeof(T) == 4) {
+        const u32x4 q = load_vec_hint<u32x4, kNtSlab>(wrow[k] + j0);
+        t.w[k][0] = q.x; t.w[k][1] = q.y; t.w[k][2] = q.z; t.w[k][3] = q.w;
+      } else {
+        const u32x2_h q = load_vec_hint<u32x2_h, kNtSlab>(wrow[k] + j0);
+        t.w[k][0] = q.x; t.w[k][1] = q.y;
+      }
+    }
+    if (sk) load_rec_block<Geom::kDwords, kNtShared>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, t.rec);
+  };
+
   // the unit of this workgroup's sketch terms
   float S32 = 1.0f, amax = 0.0f;
   uint32_t seen_or = 0u;            // OR of every cell value this lane's adds returned
@@ -577,23 +630,6 @@ state_kernel(const StateParams prm) {
     constexpr bool SK = decltype(sk_tag)::value;
     constexpr bool MX = decltype(mx_tag)::value;
 
-    // whole vectors, no tests: for tiles that lie entirely inside the chunk
-    auto load_fast = [&](Tile& t, long long j0) {
-      load_f32_vec<V, kNtShared>(w0p + j0, t.w0);
-      if constexpr (SC) load_f32_vec<V, kNtShared>(xip + j0, t.x);
-#pragma unroll
-      for (int k = 0; k < KC; ++k) {
-        if constexpr (sizeof(T) == 4) {
-          const u32x4 q = load_vec_hint<u32x4, kNtSlab>(wrow[k] + j0);
-          t.w[k][0] = q.x; t.w[k][1] = q.y; t.w[k][2] = q.z; t.w[k][3] = q.w;
-        } else {
-          const u32x2_h q = load_vec_hint<u32x2_h, kNtSlab>(wrow[k] + j0);
-          t.w[k][0] = q.x; t.w[k][1] = q.y;
-        }
-      }
-      if constexpr (SK)
-        load_rec_block<Geom::kDwords, kNtShared>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, t.rec);
-    };
     // element by element, every access tested: ragged tails and slabs without dword alignment
     auto load_slow = [&](Tile& t, long long j0) {
 #pragma unroll
@@ -643,7 +679,7 @@ state_kernel(const StateParams prm) {
       held = 0;
     };
 
-    auto consume = [&](const Tile& t, long long j0) {
+    auto consume = [&](const Tile& t) {
       uint32_t pend_old[KC];                  // the last batch of returned values, not yet examined
       bool have_pending = false;
 #pragma unroll
@@ -732,28 +768,26 @@ state_kernel(const StateParams prm) {
       }
     };
 
-    // tiles that lie wholly inside the chunk (every lane has a whole vector): software
-    // pipelined, the next tile's loads in flight while the current tile is consumed
-    const long long nfast = prm.vec_ok ? (cend > cbeg ? (cend - cbeg) / kTile : 0) : 0;
-    long long j0 = cbeg + (long long)tid * V;
-    if (nfast > 0) {
+    // software pipelined: the next tile's loads are in flight while the current tile is consumed
+    if (mine > 0) {
       Tile cur;
-      load_fast(cur, j0);
-      for (long long it = 1; it < nfast; ++it) {
+      long long jt = cbeg + wave_id * kWaveTile + (tid & 63) * V;
+      load_fast(cur, jt, SC, SK);
+      for (int it = 1; it < mine; ++it) {
         Tile nxt;
-        load_fast(nxt, j0 + kTile);
-        consume(cur, j0);
+        jt += stride_after(it - 1);
+        load_fast(nxt, jt, SC, SK);
+        consume(cur);
         cur = nxt;
-        j0 += kTile;
       }
-      consume(cur, j0);
-      j0 += kTile;
+      consume(cur);
     }
+    long long j0 = cbeg + (long long)full * kWaveTile + (long long)tid * V;
     // what is left: at most one ragged tile, or everything when vectors are not possible
     for (; j0 < cend; j0 += kTile) {
       Tile t;
       load_slow(t, j0);
-      consume(t, j0);
+      consume(t);
     }
     widen();
   };
@@ -775,9 +809,9 @@ state_kernel(const StateParams prm) {
   if (scalars) {
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
-      double a = wave_sum(dn[k]);
-      double c = wave_sum(dp[k]);
-      if (lane == 0) { red[(wave * KC + k) * 2] = a; red[(wave * KC + k) * 2 + 1] = c; }
+      const double a = wave_sum63(dn[k]);
+      const double c = wave_sum63(dp[k]);
+      if (lane == 63) { red[(wave * KC + k) * 2] = a; red[(wave * KC + k) * 2 + 1] = c; }
     }
   }
   __syncthreads();
