@@ -21,7 +21,8 @@
  *     none: slab, vectors, states, result structs and the workspace belong to the caller
  *     (for example torch tensors) and must stay alive until the work enqueued on `stream`
  *     has completed.  The library keeps no caller pointer after a call returns, except
- *     the workspace given to fda_create, which it uses until fda_destroy.
+ *     the workspace given to fda_create, which it uses until fda_destroy.  (It holds one page of pinned
+ *     host memory as long as contexts exist that have read a result back.)
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).  All calls
  *     only enqueue work, except fda_estimate_variance with a non-NULL out_host, which
  *     also waits for the stream.
@@ -318,7 +319,8 @@ int fda_update_xi(fda_ctx* ctx, const float* w_t0, const float* w_prev, float* x
  *               xi == NULL (allowed without LINEAR) no xi is maintained
  *   w_prev      DEVICE [d] fp32, required when xi is given
  *   w_bar       DEVICE [d] fp32 or NULL (only used with FDA_STEP_MEAN_STATE)
- *   out_dev / out_host  as in fda_estimate_variance (out_host != NULL makes the call wait)
+ *   out_dev / out_host  as in fda_estimate_variance (out_host != NULL makes the call wait: first for the
+ *               decision, then, if that is to synchronize, for the synchronization)
  */
 #define FDA_STEP_MEAN_STATE 1
 int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float* state, float* w_bar,

@@ -404,6 +404,38 @@ int dispatch_mean(int dtype, const MeanSplit& ms, int FB, const fda::MeanParams*
   return FDA_OK;
 }
 
+// Pinned places for results that a program reads back: the estimate kernels write there themselves, which
+// spares the call a copy (a pageable copy of 64 bytes behind a kernel: 9 us).  One page for all contexts of the
+// process; a context takes a place on its first such call and gives it back when it is destroyed; the page goes
+// with the last one.  No place free: the result is copied.
+struct HostResults {
+  static constexpr int kPlaces = 64;
+  std::mutex mutex;
+  fda_estimate* page = nullptr;
+  uint64_t used = 0;
+  fda_estimate* take() {
+    std::lock_guard<std::mutex> lock(mutex);
+    if (page == nullptr) {
+      void* p = nullptr;
+      if (hipHostMalloc(&p, kPlaces * sizeof(fda_estimate), hipHostMallocPortable) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      page = static_cast<fda_estimate*>(p);
+    }
+    for (int t = 0; t < kPlaces; ++t)
+      if (!(used >> t & 1)) { used |= 1ull << t; return page + t; }
+    return nullptr;
+  }
+  void give_back(fda_estimate* place) {
+    if (place == nullptr) return;
+    std::lock_guard<std::mutex> lock(mutex);
+    used &= ~(1ull << (place - page));
+    if (used == 0) { (void)hipHostFree(page); page = nullptr; }
+  }
+};
+HostResults g_host_results;
+
 constexpr int kProfSlots = 64;
 
 // Device address of `scratch` on the current device, looked up once per device (with that device
@@ -439,6 +471,7 @@ struct fda_ctx {
   bool table_built = false;       // the hash table of the state pass has been enqueued
   bool mean_table_built = false;  // ... of the mean-state pass (the same table when the plan shares it)
   bool tickets_cleared = false;
+  fda_estimate* host_place = nullptr;   // in HostResults, once a result has been read back
   // optional timing of the state kernel (fda_profile_enable)
   bool prof_on = false;
   hipEvent_t prof_start[kProfSlots] = {};
@@ -681,6 +714,7 @@ int fda_destroy(fda_ctx* ctx) {
     if (ctx->prof_start[t]) (void)hipEventDestroy(ctx->prof_start[t]);
     if (ctx->prof_stop[t]) (void)hipEventDestroy(ctx->prof_stop[t]);
   }
+  g_host_results.give_back(ctx->host_place);
   delete ctx;
   return FDA_OK;
 }
@@ -846,13 +880,21 @@ static int estimate_args(const fda_ctx* ctx, int rows, double theta, double tie_
   if (!(tie_tol >= 0.0)) return fail(FDA_EINVAL, "tie_tol must be >= 0");
   const fda_desc& d = ctx->desc;
   const bool sk = (d.variants & FDA_VARIANT_SKETCH) != 0;
-  *args = {d.variants, sk ? d.l : 0, sk ? d.m : 1, rows, d.eps, theta, tie_tol, out_dev};
+  *args = {d.variants, sk ? d.l : 0, sk ? d.m : 1, rows, d.eps, theta, tie_tol, out_dev, nullptr};
   return FDA_OK;
 }
 
-static int copy_result(fda_estimate* out_host, const fda_estimate* out_dev, hipStream_t st) {
-  FDA_HIP(hipMemcpyAsync(out_host, out_dev, sizeof(fda_estimate), hipMemcpyDeviceToHost, st));
+// The result on its way to the host (args.host, if a place is free) and, behind the kernels, into out_host:
+// waits for the stream.
+static void want_result(fda_ctx* ctx, fda::EstimateArgs* args) {
+  if (ctx->host_place == nullptr) ctx->host_place = g_host_results.take();
+  args->host = ctx->host_place;
+}
+static int read_result(const fda::EstimateArgs& args, fda_estimate* out_host, hipStream_t st) {
+  if (args.host == nullptr)
+    FDA_HIP(hipMemcpyAsync(out_host, args.out, sizeof(fda_estimate), hipMemcpyDeviceToHost, st));
   FDA_HIP(hipStreamSynchronize(st));
+  if (args.host != nullptr) std::memcpy(out_host, args.host, sizeof(fda_estimate));
   return FDA_OK;
 }
 
@@ -869,12 +911,13 @@ static int estimate_rows(fda_ctx* ctx, const float* state, int rows, int mean_mo
   const int eblocks = args.l > 0 ? args.l * ((d.m + fda::kEstCols - 1) / fda::kEstCols) : 1;
   rc = clear_tickets_once(ctx, st);
   if (rc != FDA_OK) return rc;
+  if (out_host != nullptr) want_result(ctx, &args);
   hipLaunchKernelGGL(fda::estimate_kernel, dim3(eblocks), dim3(fda::kSmallThreads), 0, st, state, args,
                      reinterpret_cast<double*>(ctx->ws + ctx->plan.off_est),
                      reinterpret_cast<unsigned int*>(ctx->ws + ctx->plan.off_ticket),
                      path_record(ctx, mean_mode != 0));
   FDA_HIP(hipGetLastError());
-  return out_host != nullptr ? copy_result(out_host, out_dev, st) : FDA_OK;
+  return out_host != nullptr ? read_result(args, out_host, st) : FDA_OK;
 }
 
 int fda_estimate_variance(fda_ctx* ctx, const float* state, double theta, double tie_tol,
@@ -917,7 +960,7 @@ int fda_estimate_variance_static(const float* state, int32_t K, int32_t l, int32
   // the counter must start at zero whatever an earlier call left (a fill kernel, not a memset node)
   hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(1), dim3(64), 0, st, ticket, 1);
   FDA_HIP(hipGetLastError());
-  const fda::EstimateArgs args = {variants, sk ? l : 0, sk ? m : 1, K, eps, theta, tie_tol, out_dev};
+  const fda::EstimateArgs args = {variants, sk ? l : 0, sk ? m : 1, K, eps, theta, tie_tol, out_dev, nullptr};
   hipLaunchKernelGGL(fda::estimate_kernel, dim3(eblocks), dim3(fda::kSmallThreads), 0, st, state, args,
                      reinterpret_cast<double*>(base), ticket, static_cast<const fda::PathRecord*>(nullptr));
   FDA_HIP(hipGetLastError());
@@ -1074,8 +1117,17 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
   fda::EstimateArgs est;
   int rc = estimate_args(ctx, mean ? 1 : ctx->desc.K, theta, tie_tol, out_dev, &est);
   if (rc != FDA_OK) return rc;
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (out_host != nullptr) want_result(ctx, &est);
   rc = mean ? mean_state_pass(ctx, w, w_t0, xi, state, w_bar, &est, stream) : local_state(ctx, w, w_t0, xi, state, &est, stream);
   if (rc != FDA_OK) return rc;
+  if (out_host != nullptr) {
+    // The program waits for the decision: what depends on it is enqueued when it is known, and most steps end
+    // here -- two launches less in front of the wait (10 us).
+    rc = read_result(est, out_host, st);
+    if (rc != FDA_OK) return rc;
+    if ((decide_by == FDA_VARIANT_LINEAR ? out_host->sync_linear : out_host->sync_sketch) == 0) return FDA_OK;
+  }
   if (w_bar != nullptr) {
     rc = fda_sync_from_mean(ctx, w, w_t0, w_prev, xi, w_bar, pred, stream);
   } else {
@@ -1083,7 +1135,8 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
                        : fda_sync(ctx, w, w_t0, w_prev, pred, stream);
   }
   if (rc != FDA_OK) return rc;
-  return out_host != nullptr ? copy_result(out_host, out_dev, static_cast<hipStream_t>(stream)) : FDA_OK;
+  if (out_host != nullptr) FDA_HIP(hipStreamSynchronize(st));
+  return FDA_OK;
 }
 
 }  // extern "C"

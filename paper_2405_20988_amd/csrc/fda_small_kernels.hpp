@@ -167,6 +167,7 @@ struct EstimateArgs {
   int variants, l, m, K;
   double eps, theta, tie_tol;
   fda_estimate* out;
+  fda_estimate* host;              // pinned host memory that receives the result too, or NULL
 };
 __device__ __forceinline__ double half_wave_sum(double v) {   // valid in lanes 0 and 32
 #pragma unroll
@@ -211,6 +212,7 @@ __device__ inline void decide(const EstimateArgs& a, double nsum, double psum, c
     }
   }
   *a.out = e;
+  if (a.host != nullptr) *a.host = e;
 }
 // What workgroups of one launch hand to each other goes through agent-scope accesses (which pass the L2 of the
 // XCD) and counters: the writer waits until its stores have been acknowledged before it counts itself, the

@@ -134,3 +134,42 @@ def test_sync_stores_rows_at_every_alignment(dtype, d):
             out[first:first + K * (d + pad)].view(K, d + pad)[:, :d] = 7.0
             assert (out == 7.0).all()
         mon.close()
+
+
+def test_results_read_back_by_more_contexts_than_there_are_places():
+    """Results reach the host through 64 pinned places of the process; contexts beyond those get copies, and
+    places come back when contexts are destroyed.  From several threads, each on a stream of its own."""
+    import threading
+
+    import paper_2405_20988_amd as F
+    d, K, errors = 4097, 3, []
+
+    def work(t):
+        try:
+            g = torch.Generator(device=DEV)
+            g.manual_seed(t)
+            with torch.cuda.stream(torch.cuda.Stream()):
+                w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+                xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+                w = w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3
+                w_prev = w_t0.clone()
+                for _ in range(2):
+                    mons = [F.FdaMonitor(K, d, "f32", 3, 3, 50, 0.06, S.hash_coefficients(q, 3), device=DEV)
+                            for q in range(30)]
+                    for mon in mons:
+                        est = mon.step(w, w_t0, w_prev, xi, 1e30, want_host=True)
+                        dev = F.FdaEstimate.from_buffer_copy(mon.est_dev.cpu().numpy().tobytes())
+                        assert est.as_dict() == dev.as_dict() and est.mean_sqnorm > 0
+                    mons[0].step(w, w_t0, w_prev, xi, 0.0, want_host=True)      # fires: waits for the rows too
+                    assert torch.equal(w[0], w_t0) and torch.equal(w[2], w_t0)
+                    w += torch.randn((K, d), generator=g, device=DEV) * 1e-3
+                    for mon in mons:
+                        mon.close()
+        except Exception as exc:                     # noqa: BLE001 -- reported by the main thread
+            errors.append(exc)
+    threads = [threading.Thread(target=work, args=(t,)) for t in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
