@@ -58,6 +58,10 @@ constexpr double kSelectCost = 1.0;        // choosing the term or its negative 
 constexpr double kAtomicCost = 7.5;        // one 32-bit LDS addition and the OR of what it returned
 constexpr double kPairAddCost = 13.0;      // one 64-bit LDS addition (two cells) and the OR of what it returned
 constexpr double kPlacedPairAddCost = 9.5; // ... when the table's row slots are placed against LDS collisions
+// ... and its time model, for short launches
+constexpr double kTileInstrUs = 0.0133, kWorkgroupUs = 8.3, kSlotUs = 0.9, kCellUs = 0.35e-3;
+constexpr int64_t kQuickTiles = 24;
+constexpr double kQuickGain = 0.85;        // a split is given up for one that the model puts below this share of its time
 constexpr double kSharedByteCost = 0.25;   // per byte of w_t0 / xi / table read by one more workgroup
 constexpr int kXiBlocks = 4096;
 constexpr int64_t kSyncSmall = 3ll << 19;  // coordinates below which the synchronization takes small blocks
@@ -123,93 +127,20 @@ int validate(const fda_desc* d) {
   return FDA_OK;
 }
 
-int make_split(const fda_desc* d, int cus, int64_t lds_cu, Split* sp) {
-  const bool sk = (d->variants & FDA_VARIANT_SKETCH) != 0;
-  const int64_t cells = sk ? (int64_t)d->l * d->m : 0;
-  const int vec = fda::kStateV;
-  // Split the K workers into G groups and the l sketch rows into R groups so that one
-  // workgroup's sketch (rows x m cells x worker slots) fits in LDS.  The kernel has KC worker
-  // slots and LR row slots (compile-time); slots a group does not fill still execute.  Every
-  // row group repeats the loads and the fixed-point conversion of its workers' elements; every
-  // workgroup decodes its rows' table entries and re-reads w_t0 / xi / table (through L2).
-  // Pick the split with the least estimated vector-ALU work per coordinate.
-  const int l = sk ? d->l : 1;
-  double best = -1.0;
-  int bestG = 0, bestR = 0, bestKC = 0, bestLR = 0, bestSplit = 0;
-  for (int G = 1; G <= d->K; ++G) {
-    const int kc = (d->K + G - 1) / G;
-    {
-      int KC = 0;                                            // the smallest kernel that holds kc workers
-      for (int c : fda::kKCSet)
-        if (c >= kc) { KC = c; break; }
-      if (KC == 0) continue;
-      // sign-split rows (even slot counts): no negated terms, no select per addition, twice the LDS
-      // (without a sketch either kind of kernel does the same)
-      for (int split = KC % 2 == 0 ? 1 : 0; split >= 0; --split) {
-        if (!fda::narrow_kernel_exists(KC, split != 0)) continue;
-        for (int R = 1; R <= l; ++R) {
-          const int rc = (l + R - 1) / R;
-          int LR = 0;                                        // row slots of the kernel that would run
-          if (rc <= fda::kMaxLR && KC * rc <= fda::kMaxSlots) LR = rc;
-          if (LR == 0) continue;
-          const int64_t need = cells ? (int64_t)fda::cells32_words(rc, split ? 2 * d->m : d->m, KC) * 4 : 0;
-          if (need + kLdsReserve > lds_cu) continue;
-          // Estimated cost per coordinate, in vector-ALU instructions (an LDS addition counted as what it
-          // keeps the compute unit from issuing): per element slot the load / drift / fixed-point work
-          // (with the negated terms unless the rows are sign-split), per row slot the table field, per
-          // addition the select (unless split), the overflow OR and the LDS instruction itself.
-          const double wg = (double)G * R;
-          const double pairs = KC % 2 == 0 ? KC / 2 : KC;                       // LDS instructions per row slot
-          // (a table with placed rows avoids about a third of the LDS collisions)
-          const bool placed = split && cells && fda::placed_kernel_exists(KC) &&
-                              !(d->flags & FDA_DESC_PLAIN_TABLE) && fda::placed_group_rows(rc, d->m, KC) >= 2;
-          const double per_add = KC % 2 == 0 ? (placed ? kPlacedPairAddCost
-                                                            : split ? kPairAddCost : kPairAddCost + 2.0 * kSelectCost)
-                                                         : kAtomicCost + kSelectCost;
-          // (Without a sketch the pass is bound by its loads: the bytes every worker slot and every workgroup's
-          // w_t0 and xi bring through the L2.  13 x 6.9M fp32: 7 groups of 2 slots 77 us, 2 of 8 69.)
-          const double cost = !cells ? wg * (KC * (d->dtype == FDA_F32 ? 4.1 : 2.05) + 8) : wg * KC * (split ? kElementCost : kElementCost + kNegateCost) +
-                              wg * LR * (split ? kDecodeCost : kDecodeCost + kSignCost) +
-                              wg * LR * pairs * per_add +
-                              wg * (8 + 2 * LR) * kSharedByteCost + 1e-3 * wg;
-          if (best < 0.0 || cost < best) {
-            best = cost; bestG = G; bestR = R; bestKC = KC; bestLR = LR; bestSplit = split;
-          }
-          break;   // a larger R only costs more for this G
-        }
-      }
-    }
-  }
-  if (bestG == 0)
-    return fail(FDA_ERANGE, "one row of an m = %d sketch does not fit in %lld bytes of LDS", d->m,
-                (long long)lds_cu);
-  sp->G = bestG;
-  sp->R = bestR;
-  sp->split = bestSplit;
-  sp->kcnt_max = (d->K + bestG - 1) / bestG;
-  sp->rcnt_max = (l + bestR - 1) / bestR;
-  sp->KC = bestKC;
-  sp->LR = bestLR;
-  const int64_t sk_bytes = cells ? (int64_t)fda::cells32_words(sp->rcnt_max, sp->split ? 2 * d->m : d->m, sp->KC) * 4 : 0;
-  sp->lds_bytes = round_up(sk_bytes, 16) + kLdsReserve;
-  // one workgroup per CU: the kernels hold more registers than two resident workgroups would allow
-  const int occ = 1;
-  const int64_t tile = (int64_t)fda::kStateThreads * vec;
-  // Partitions: all workgroups do the same amount of work, so the launch should fill the resident
-  // slots a whole number of times; and a workgroup costs its set-up, reductions and flush on top of
-  // its tiles (measured: about six tiles' worth).  Among the first few feasible numbers of rounds of
-  // resident workgroups keep the cheapest: rounds x (tiles per workgroup + overhead).
-  // Feasible: a 32-bit cell should take about 12000 terms at most (16384 of typical size, one way, fill its
-  // band).  The cells of sign-split rows take the terms of one
-  // hash sign each, which do not cancel when the drifts themselves lean one way: they are kept at about
-  // 3500 expected terms (a term of mean magnitude is 2^18..2^19 units: the band of 2^30 then holds unless
-  // more than about half of a cell's mass leans one way -- such a call finishes on the 64-bit cells).
-  const int64_t slots = (int64_t)cus * occ, gr = (int64_t)bestG * bestR;
-  const int64_t tiles = (d->d + tile - 1) / tile;
+// Partitions: all workgroups do the same amount of work, so the launch should fill the resident
+// slots a whole number of times; and a workgroup costs its set-up, reductions and flush on top of
+// its tiles (measured: about six tiles' worth).  Among the first few feasible numbers of rounds of
+// resident workgroups keep the cheapest: rounds x (tiles per workgroup + overhead).
+// Feasible: a 32-bit cell should take about 12000 terms at most (16384 of typical size, one way, fill its
+// band).  The cells of sign-split rows take the terms of one
+// hash sign each, which do not cancel when the drifts themselves lean one way: they are kept at about
+// 3500 expected terms (a term of mean magnitude is 2^18..2^19 units: the band of 2^30 then holds unless
+// more than about half of a cell's mass leans one way -- such a call finishes on the 64-bit cells).
+int64_t choose_partitions(const fda_desc* d, int64_t cells, int64_t tiles, int64_t slots, int64_t gr, int split) {
   int64_t pmin = 1;
   if (cells) {
-    const int64_t per_row = (int64_t)d->m * (bestSplit ? 2 : 1);
-    const int64_t terms = bestSplit ? kMaxTermsPlannedSplit : kMaxTermsPlanned;
+    const int64_t per_row = (int64_t)d->m * (split ? 2 : 1);
+    const int64_t terms = split ? kMaxTermsPlannedSplit : kMaxTermsPlanned;
     pmin = (d->d + per_row * terms - 1) / (per_row * terms);
     if (pmin > tiles) pmin = tiles;
   }
@@ -227,8 +158,96 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, Split* sp) {
     if (best_time < 0.0 || est < best_time * 0.98) { best_time = est; P = cand; }
     if (cand == tiles) break;                           // one tile per workgroup: nothing finer
   }
-  sp->P = (int)P;
-  sp->chunk = round_up((d->d + P - 1) / P, tile);
+  return P;
+}
+
+int make_split(const fda_desc* d, int cus, int64_t lds_cu, Split* sp) {
+  const bool sk = (d->variants & FDA_VARIANT_SKETCH) != 0;
+  const int64_t cells = sk ? (int64_t)d->l * d->m : 0;
+  const int64_t tile = (int64_t)fda::kStateThreads * fda::kStateV;
+  const int64_t tiles = (d->d + tile - 1) / tile;
+  // one workgroup per CU: the kernels hold more registers than two resident workgroups would allow
+  const int64_t slots = cus;
+  // Split the K workers into G groups and the l sketch rows into R groups so that one
+  // workgroup's sketch (rows x m cells x worker slots) fits in LDS.  The kernel has KC worker
+  // slots and LR row slots (compile-time); slots a group does not fill still execute.  Every
+  // row group repeats the loads and the fixed-point conversion of its workers' elements; every
+  // workgroup decodes its rows' table entries and re-reads w_t0 / xi / table (through L2).
+  // Pick the split with the least estimated vector-ALU work per coordinate -- unless the launch is so short
+  // that what a workgroup costs besides its tiles decides.
+  const int l = sk ? d->l : 1;
+  struct Cand { int G, R, KC, LR, split; double cost, us; int64_t P; };
+  Cand best = {}, quick = {};
+  for (int pass = 0; pass < 2; ++pass)        // first the cheapest, then the quickest that splits the rows like it
+  for (int G = 1; G <= d->K; ++G) {
+    const int kc = (d->K + G - 1) / G;
+    int KC = 0;                                              // the smallest kernel that holds kc workers
+    for (int c : fda::kKCSet)
+      if (c >= kc) { KC = c; break; }
+    if (KC == 0) continue;
+    // sign-split rows (even slot counts): no negated terms, no select per addition, twice the LDS
+    // (without a sketch either kind of kernel does the same)
+    for (int split = KC % 2 == 0 ? 1 : 0; split >= 0; --split) {
+      if (!fda::narrow_kernel_exists(KC, split != 0)) continue;
+      for (int R = 1; R <= l; ++R) {
+        const int rc = (l + R - 1) / R;
+        int LR = 0;                                          // row slots of the kernel that would run
+        if (rc <= fda::kMaxLR && KC * rc <= fda::kMaxSlots) LR = rc;
+        if (LR == 0) continue;
+        const int64_t need = cells ? (int64_t)fda::cells32_words(rc, split ? 2 * d->m : d->m, KC) * 4 : 0;
+        if (need + kLdsReserve > lds_cu) continue;
+        // Estimated cost per coordinate, in vector-ALU instructions (an LDS addition counted as what it
+        // keeps the compute unit from issuing): per element slot the load / drift / fixed-point work
+        // (with the negated terms unless the rows are sign-split), per row slot the table field, per
+        // addition the select (unless split), the overflow OR and the LDS instruction itself.
+        const double wg = (double)G * R;
+        const double pairs = KC % 2 == 0 ? KC / 2 : KC;                         // LDS instructions per row slot
+        // (a table with placed rows avoids about a third of the LDS collisions)
+        const bool can_place = split && cells && fda::placed_kernel_exists(KC) && fda::placed_group_rows(rc, d->m, KC) >= 2;
+        auto cost_of = [&](bool placed) {
+          const double per_add = KC % 2 != 0 ? kAtomicCost + kSelectCost
+                                 : placed    ? kPlacedPairAddCost
+                                 : split     ? kPairAddCost : kPairAddCost + 2.0 * kSelectCost;
+          return wg * KC * (split ? kElementCost : kElementCost + kNegateCost) +
+                 wg * LR * (split ? kDecodeCost : kDecodeCost + kSignCost) +
+                 wg * LR * pairs * per_add +
+                 wg * (8 + 2 * LR) * kSharedByteCost + 1e-3 * wg;
+        };
+        Cand c = {G, R, KC, LR, split, cost_of(can_place && !(d->flags & FDA_DESC_PLAIN_TABLE)), 0.0, 0};
+        // (Without a sketch the pass is bound by its loads: the bytes every worker slot and every workgroup's
+        // w_t0 and xi bring through the L2.  13 x 6.9M fp32: 7 groups of 2 slots 77 us, 2 of 8 69.)
+        if (!cells) c.cost = wg * (KC * (d->dtype == FDA_F32 ? 4.1 : 2.05) + 8);
+        c.P = choose_partitions(d, cells, tiles, slots, wg, split);
+        // The time of the launch.  Measured on 5 x 250 and 7 x 1000 sketches, 61706 to 2.6M coordinates, 3 to 50
+        // workers (within 10 %): a tile takes 32 clocks per instruction of the cost, a workgroup besides its
+        // tiles 8.3 us, 0.9 us per worker slot (sample, sums) and 0.35 us per 1000 cells (flush).  (The same
+        // for a plain table, which must not change the workgroups.)
+        c.us = (double)((c.P * G * R + slots - 1) / slots) *
+               ((double)((tiles + c.P - 1) / c.P) * (cost_of(can_place) / wg) * kTileInstrUs +
+                kWorkgroupUs + kSlotUs * KC + kCellUs * rc * d->m * KC);
+        if (pass == 0 && (best.G == 0 || c.cost < best.cost)) best = c;
+        if (pass == 1 && KC % 2 == 0 && R == best.R && split == best.split && (quick.G == 0 || c.us < quick.us)) quick = c;
+        break;   // a larger R only costs more for this G
+      }
+    }
+  }
+  if (best.G == 0)
+    return fail(FDA_ERANGE, "one row of an m = %d sketch does not fit in %lld bytes of LDS", d->m,
+                (long long)lds_cu);
+  // Short launches: more groups of fewer workers where that is clearly faster (5 x 61706: 3 groups of 2 slots 9.9
+  // us, 1 of 6 14.3; 30 x 100001: 15 of 2 14.0 us, 5 of 6 18.9).  Vectors below 24 tiles keep the cheapest split.
+  if (cells && tiles >= kQuickTiles && quick.G != 0 && quick.us < kQuickGain * best.us) best = quick;
+  sp->G = best.G;
+  sp->R = best.R;
+  sp->split = best.split;
+  sp->kcnt_max = (d->K + best.G - 1) / best.G;
+  sp->rcnt_max = (l + best.R - 1) / best.R;
+  sp->KC = best.KC;
+  sp->LR = best.LR;
+  const int64_t sk_bytes = cells ? (int64_t)fda::cells32_words(sp->rcnt_max, sp->split ? 2 * d->m : d->m, sp->KC) * 4 : 0;
+  sp->lds_bytes = round_up(sk_bytes, 16) + kLdsReserve;
+  sp->P = (int)best.P;
+  sp->chunk = round_up((d->d + best.P - 1) / best.P, tile);
   // cells that may collect more than 4096 terms get a unit one bit coarser: the expected number of terms of a
   // cell and six standard deviations
   sp->shrink = 0;

@@ -173,3 +173,27 @@ def test_results_read_back_by_more_contexts_than_there_are_places():
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+@pytest.mark.parametrize("K,d,l,m,dtype,slots", [(3, 2_100_001, 2, 60, "f32", 4), (4, 2_600_003, 2, 60, "bf16", 4),
+                                                 (6, 4_200_001, 2, 60, "f32", 6), (6, 4_200_001, 3, 31, "bf16", 6),
+                                                 (8, 6_000_001, 1, 33, "f32", 8), (8, 6_000_001, 2, 31, "bf16", 8)])
+def test_kernels_with_many_worker_slots(K, d, l, m, dtype, slots):
+    """Short launches take more groups of two workers; these are long enough for four, six and eight."""
+    import paper_2405_20988_amd as F
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K + d)
+    w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+    w = (w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    coef = S.hash_coefficients(K, l)
+    mon = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, coef, device=DEV)
+    assert (mon.plan["worker_groups"], mon.plan["worker_slots"]) == (1, slots), mon.plan
+    mon.local_state(w, w_t0, xi)
+    n, p, sk = mon.state_numpy()
+    ref = O.local_state(S.slab_to_numpy(w), dtype, w_t0.cpu().numpy(), xi.cpu().numpy(), coef, m)
+    assert np.allclose(n, ref["n"], rtol=RTOL, atol=0)
+    assert (np.abs(p - ref["p"]) <= RTOL * ref["p_abs"] + 1e-30).all()
+    check_cells(sk, ref["sk"], ref["sk_abs"], ref["sk_cnt"], ref["u_mean_abs"])
+    assert mon.last_state_path() == 0
+    mon.close()
