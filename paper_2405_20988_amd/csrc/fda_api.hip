@@ -192,7 +192,7 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, Split* sp) {
       for (int R = 1; R <= l; ++R) {
         const int rc = (l + R - 1) / R;
         int LR = 0;                                          // row slots of the kernel that would run
-        if (rc <= fda::kMaxLR && KC * rc <= fda::kMaxSlots) LR = rc;
+        if (rc <= fda::kMaxLR && KC * rc <= fda::max_slots(KC)) LR = rc;
         if (LR == 0) continue;
         const int64_t need = cells ? (int64_t)fda::cells32_words(rc, split ? 2 * d->m : d->m, KC) * 4 : 0;
         if (need + kLdsReserve > lds_cu) continue;
@@ -549,8 +549,10 @@ int build_table(fda_ctx* ctx, int R, int slots, int fb, int words, int grp, int 
   const fda_desc& d = ctx->desc;
   const Plan& pl = ctx->plan;
   const long long groups = pl.dpad / 4;
-  // what the kernel's arrays assume: at most 8 row slots, records of at most 8 words, placement groups of 2..8 rows
-  if (slots < 1 || slots > 8 || words < 1 || words > 8 || grp < 1 || grp > 8 || slots * fb > words * 16)
+  // what the kernel's arrays assume: at most kMaxLR row slots, as many words of a record, placement groups of 2 rows
+  // or more
+  if (slots < 1 || slots > fda::kMaxLR || words < 1 || words > fda::kMaxLR || grp < 1 || grp > fda::kMaxLR ||
+      slots * fb > words * 16)
     return fail(FDA_EINVAL, "table shape out of range: %d slots of %d bits in %d words, groups of %d", slots, fb, words, grp);
   hipLaunchKernelGGL(fda::hash_table_kernel,
                      dim3((unsigned)((groups + fda::kSmallThreads - 1) / fda::kSmallThreads), (unsigned)R),

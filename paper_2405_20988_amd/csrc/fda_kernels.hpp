@@ -243,6 +243,8 @@ __device__ __forceinline__ uint32_t hash_entry(const HashCoef& hc, int row, uint
 }
 
 // ---- the tabulated hash: geometry of a record and of a lane's share of a tile -----------
+constexpr int kMaxLR = 9;                    // sketch-row slots of one workgroup, and of a record
+constexpr int kMaxPlaceGroups = (kMaxLR + 1) / 2;      // placement groups (of two rows or more) of a record
 constexpr int kDummyCells = 64;              // cells of the dummy region (power of two)
 // field width for a sketch of m columns (a field is below 2 m): 11 bits while m <= 1024, else 16
 __host__ __device__ constexpr int field_bits_for(int m) { return m <= 1024 ? 11 : 16; }

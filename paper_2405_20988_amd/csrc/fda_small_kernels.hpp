@@ -38,9 +38,9 @@ constexpr int kPlaceSweeps = 3;
 __global__ void __launch_bounds__(kSmallThreads)
 hash_table_kernel(const HashCoef hc, int l, int R, int slots, int m, int fb, int words, int grp, int KC,
                   long long d, long long dpad, uint16_t* __restrict__ table) {
-  __shared__ uint16_t fld[kSmallThreads][4][8];                // plain fields, by thread, coordinate, row
-  __shared__ uint8_t rotsel[kSmallThreads][4][4];              // chosen rotation, by thread, coordinate, placement group
-  __shared__ uint8_t hist[kSmallThreads / 64][16][8][16];      // by wave, (16 lanes, v), slot, class
+  __shared__ uint16_t fld[kSmallThreads][4][kMaxLR];           // plain fields, by thread, coordinate, row
+  __shared__ uint8_t rotsel[kSmallThreads][4][kMaxPlaceGroups];  // chosen rotation, by thread, coordinate, placement group
+  __shared__ uint8_t hist[kSmallThreads / 64][16][kMaxLR][16];     // by wave, (16 lanes, v), slot, class
   const int r = blockIdx.y;
   const int tid = threadIdx.x;
   const long long j4 = ((long long)blockIdx.x * blockDim.x + tid) * 4;
@@ -60,9 +60,9 @@ hash_table_kernel(const HashCoef hc, int l, int R, int slots, int m, int fb, int
     }
   }
   if (placed) {                                                // (uniform over the workgroup)
-    const int ngroups = (rcnt + grp - 1) / grp;                // at most 4: grp >= 2, at most 8 rows
+    const int ngroups = (rcnt + grp - 1) / grp;                // at most kMaxPlaceGroups: grp >= 2, at most kMaxLR rows
     for (int q = 0; q < 4; ++q)
-      for (int g = 0; g < 4; ++g) rotsel[tid][q][g] = 0;
+      for (int g = 0; g < kMaxPlaceGroups; ++g) rotsel[tid][q][g] = 0;
     __syncthreads();
     const int wave = tid >> 6, lane = tid & 63;
     // problem (16 lanes gi, coordinate v) = lane & 15; placement groups lane >> 4, lane >> 4 + 4, ...
@@ -85,7 +85,7 @@ hash_table_kernel(const HashCoef hc, int l, int R, int slots, int m, int fb, int
             const int cur = rotsel[member0 + t][v][g];
             for (int a = 0; a < n; ++a) { int row = a + cur; if (row >= n) row -= n; h[a][cls(t, row)] -= 1; }
           }
-          int mx[8];
+          int mx[kMaxLR];
           for (int a = 0; a < n; ++a) {
             int top = 0;
             for (int c = 0; c < 16; ++c) top = h[a][c] > top ? h[a][c] : top;
@@ -109,10 +109,10 @@ hash_table_kernel(const HashCoef hc, int l, int R, int slots, int m, int fb, int
     __syncthreads();
   }
   if (j4 >= dpad) return;
-  uint32_t dw[16];                                             // 4 records of at most 8 words
-  for (int t = 0; t < 16; ++t) dw[t] = 0u;
+  uint32_t dw[2 * kMaxLR];                             // 4 records of at most kMaxLR words
+  for (int t = 0; t < 2 * kMaxLR; ++t) dw[t] = 0u;
   for (int q = 0; q < 4; ++q) {
-    unsigned long long bits[3] = {0ull, 0ull, 0ull};          // slots * fb <= 8 * 16 bits
+    unsigned long long bits[3] = {0ull, 0ull, 0ull};          // slots * fb <= 9 * 16 bits
     for (int i = 0; i < slots; ++i) {
       unsigned long long f = fld[tid][q][i];
       if (placed && i < rcnt) {

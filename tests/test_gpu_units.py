@@ -36,7 +36,7 @@ def drifts(kind, K, d, g):
     (1, 90_001, 3, 500, "f32"),           # one slot, plain rows: redone in two windows
     (2, 60_003, 2, 5000, "f32"),          # two slots, plain rows
     (3, 70_001, 5, 251, "bf16"),          # four slots with a spare one, skewed and placed
-    (8, 120_007, 9, 250, "bf16"),         # two row groups
+    (8, 120_007, 9, 250, "bf16"),         # nine rows (the widest workgroup), four slots
     (20, 50_001, 5, 33, "f32"),           # six slots, placed; more workers than the mean-state pass samples
 ])
 def test_units_and_redo(kind, K, d, l, m, dtype):
@@ -66,6 +66,36 @@ def test_units_and_redo(kind, K, d, l, m, dtype):
         assert nb == pytest.approx(mref["n"], rel=RTOL)
         assert abs(pb - mref["p"]) <= RTOL * mref["p_abs"] + 1e-30
         check_cells(skb, mref["sk"], mref["sk_abs"], mref["sk_cnt"], mref["u_mean_abs"])
+    mon.close()
+
+
+@pytest.mark.parametrize("K,d,l,m,dtype,groups,mean_groups", [
+    (1, 5_003, 9, 33, "f32", 1, 1),         # one slot, plain rows of 16-bit or 11-bit fields
+    (1, 5_003, 9, 1025, "bf16", 1, 1),
+    (2, 2_047, 9, 1100, "bf16", 1, 1),      # two slots, nine fields of 13 bits, placement groups of three rows
+    (4, 2_049, 9, 250, "f32", 1, 1),        # four slots: all registers of a wave
+    (3, 70_001, 9, 1, "bf16", 1, 1),
+    (5, 20_001, 9, 2200, "f32", 3, 1),      # the state pass splits the rows, the mean-state pass does not
+    (3, 9_001, 10, 64, "f32", 2, 2),         # the first sketch of two row groups
+])
+def test_nine_rows_in_one_workgroup(K, d, l, m, dtype, groups, mean_groups):
+    """Integer-valued drifts: states and average state bit for bit, so every field of every record is checked."""
+    import paper_2405_20988_amd as F
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K + l)
+    w_t0 = torch.zeros(d, device=DEV)
+    xi = torch.zeros(d, device=DEV)
+    w = torch.randint(-4, 5, (K, d), generator=g, device=DEV).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    coef = S.hash_coefficients(7, l)
+    mon = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, coef, device=DEV)
+    assert mon.plan["row_groups"] == groups and mon.plan["mean_row_groups"] == mean_groups
+    ref = O.local_state(S.slab_to_numpy(w), dtype, w_t0.cpu().numpy(), xi.cpu().numpy(), coef, m)
+    mon.local_state(w, w_t0, xi)
+    n, _, sk = mon.state_numpy()
+    assert np.array_equal(n, ref["n"].astype(np.float32)) and np.array_equal(sk, ref["sk"].astype(np.float32))
+    mon.mean_state(w, w_t0, xi)
+    _, _, skb = mon.mean_numpy()
+    assert np.array_equal(skb, (ref["sk"].sum(axis=0) / K).astype(np.float32))
     mon.close()
 
 
