@@ -1130,6 +1130,8 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
   if (xi != nullptr && w_prev == nullptr) return fail(FDA_EINVAL, "w_prev is required when xi is given");
   const bool mean = (flags & FDA_STEP_MEAN_STATE) != 0;
   if (!mean && w_bar != nullptr) return fail(FDA_EINVAL, "w_bar needs FDA_STEP_MEAN_STATE");
+  // (the synchronization checks this too, but a step that reads its decision back may end before it)
+  if (reinterpret_cast<uintptr_t>(w_prev) % 4 != 0) return fail(FDA_EINVAL, "pointer not aligned to its element type");
   const int32_t* pred = reinterpret_cast<const int32_t*>(
       reinterpret_cast<const unsigned char*>(out_dev) +
       (decide_by == FDA_VARIANT_LINEAR ? offsetof(fda_estimate, sync_linear)

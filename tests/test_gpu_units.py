@@ -227,3 +227,20 @@ def test_kernels_with_many_worker_slots(K, d, l, m, dtype, slots):
     check_cells(sk, ref["sk"], ref["sk_abs"], ref["sk_cnt"], ref["u_mean_abs"])
     assert mon.last_state_path() == 0
     mon.close()
+
+
+def test_step_refuses_a_misaligned_w_prev_whatever_it_decides():
+    import paper_2405_20988_amd as F
+    from paper_2405_20988_amd import binding as B
+    K, d = 3, 5000
+    w_t0 = torch.zeros(d, device=DEV)
+    xi = torch.zeros(d, device=DEV)
+    w = torch.ones((K, d), device=DEV)
+    w_prev = torch.zeros(d + 1, device=DEV)
+    mon = F.FdaMonitor(K, d, "f32", 3, 3, 50, 0.06, S.hash_coefficients(1, 3), device=DEV)
+    for want_host in (False, True):
+        with pytest.raises(F.FdaError):
+            B.fda_step(mon.ctx, w.data_ptr(), w_t0.data_ptr(), w_prev.data_ptr() + 2, xi.data_ptr(),
+                       mon.state.data_ptr(), None, 1e30, 1e-5, B.FDA_VARIANT_LINEAR, 0, mon.est_dev.data_ptr(),
+                       want_host=want_host)
+    mon.close()
