@@ -509,7 +509,11 @@ int clear_tickets_once(fda_ctx* c, hipStream_t st) {
   hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(64), dim3(fda::kSmallThreads), 0, st,
                      reinterpret_cast<unsigned int*>(c->ws + c->plan.off_path), kPathWords + c->plan.tickets);
   FDA_HIP(hipGetLastError());
-  c->tickets_cleared = true;
+  // (a launch that is only being captured has cleared nothing yet: eager calls before its first replay clear the
+  // counters themselves)
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  FDA_HIP(hipStreamIsCapturing(st, &status));
+  c->tickets_cleared = status == hipStreamCaptureStatusNone;
   return FDA_OK;
 }
 

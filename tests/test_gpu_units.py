@@ -244,3 +244,48 @@ def test_step_refuses_a_misaligned_w_prev_whatever_it_decides():
                        mon.state.data_ptr(), None, 1e30, 1e-5, B.FDA_VARIANT_LINEAR, 0, mon.est_dev.data_ptr(),
                        want_host=want_host)
     mon.close()
+
+
+@pytest.mark.parametrize("call", ["sync_xi", "linear_state"])
+def test_eager_calls_between_the_capture_of_a_first_call_and_its_replay(call):
+    """A context whose first call is only captured has no counters cleared yet; eager calls and, after them,
+    several replays give what a context of its own gives."""
+    import paper_2405_20988_amd as F
+    K, d = 5, 200_003
+    g = torch.Generator(device=DEV)
+    g.manual_seed(9)
+    w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+    w = w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3
+    xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    new = lambda: F.FdaMonitor(K, d, "f32", 1, 1, 1, 0.06, S.hash_coefficients(1, 1), device=DEV)
+    mon, ref = new(), new()
+    mon.workspace.fill_(0x5A)
+    bufs = [[t.clone() for t in (w, w_t0, w_t0, xi)] for _ in range(2)]      # slab, w_t0, w_prev, xi
+
+    def one(m, b):
+        for dst, src in zip(b, (w, w_t0, w_t0, xi)):
+            dst.copy_(src)
+        if call == "sync_xi":
+            m.sync_xi(*b)
+        else:
+            m.local_state(b[0], b[1], b[3])
+
+    def check(m):
+        torch.cuda.synchronize()
+        assert torch.equal(m.state, ref.state) or call == "sync_xi"
+        for x, y in zip(*bufs):
+            assert torch.equal(x, y)
+    one(ref, bufs[1])
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        one(mon, bufs[0])
+    one(mon, bufs[0])
+    check(mon)
+    for _ in range(3):
+        bufs[0][3].zero_()
+        mon.state.zero_()
+        graph.replay()
+        check(mon)
+    mon.close()
+    ref.close()
