@@ -427,6 +427,13 @@ int dispatch_mean(int dtype, const MeanSplit& ms, int FB, const fda::MeanParams*
 // spares the call a copy (a pageable copy of 64 bytes behind a kernel: 9 us).  One page for all contexts of the
 // process; a context takes a place on its first such call and gives it back when it is destroyed; the page goes
 // with the last one.  No place free: the result is copied.
+// Another stream of the program may be capturing a graph meanwhile, which allocations and frees are only
+// allowed beside in the relaxed mode.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError(); }
+  ~RelaxedCapture() { if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError(); }
+};
 struct HostResults {
   static constexpr int kPlaces = 64;
   std::mutex mutex;
@@ -435,6 +442,7 @@ struct HostResults {
   fda_estimate* take() {
     std::lock_guard<std::mutex> lock(mutex);
     if (page == nullptr) {
+      const RelaxedCapture relaxed;
       void* p = nullptr;
       if (hipHostMalloc(&p, kPlaces * sizeof(fda_estimate), hipHostMallocPortable) != hipSuccess) {
         (void)hipGetLastError();
@@ -450,7 +458,10 @@ struct HostResults {
     if (place == nullptr) return;
     std::lock_guard<std::mutex> lock(mutex);
     used &= ~(1ull << (place - page));
-    if (used == 0) { (void)hipHostFree(page); page = nullptr; }
+    if (used != 0) return;
+    const RelaxedCapture relaxed;
+    if (hipHostFree(page) == hipSuccess) page = nullptr;
+    else (void)hipGetLastError();                      // the page stays for the next context
   }
 };
 HostResults g_host_results;

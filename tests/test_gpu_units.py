@@ -289,3 +289,52 @@ def test_eager_calls_between_the_capture_of_a_first_call_and_its_replay(call):
         check(mon)
     mon.close()
     ref.close()
+
+
+def test_contexts_are_destroyed_and_results_read_back_while_a_graph_is_captured():
+    """The pinned page of the process is taken with the first result that is read back and goes with the last
+    context: neither disturbs a capture on another stream."""
+    import gc
+    import threading
+
+    import paper_2405_20988_amd as F
+    gc.collect()
+    K, d = 3, 5001
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+    w = w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3
+    xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    other = torch.cuda.Stream()
+    new = lambda: F.FdaMonitor(K, d, "f32", 3, 3, 50, 0.06, S.hash_coefficients(1, 3), device=DEV)
+    mon, beside = new(), new()
+    for m in (mon, beside):
+        m.local_state(w, w_t0, xi)
+    want = mon.state.clone()
+    est, errors = [], []
+
+    def read_back():
+        try:
+            with torch.cuda.stream(other):
+                est.append(beside.estimate_variance(1e30))
+            beside.close()                             # gives the page back
+        except Exception as exc:                       # noqa: BLE001 -- reported below
+            errors.append(exc)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mon.local_state(w, w_t0, xi)
+        t = threading.Thread(target=read_back)
+        t.start()
+        t.join()
+        mon.estimate_variance(1e30, want_host=False)
+    assert not errors, errors
+    for _ in range(3):
+        mon.state.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(mon.state, want)
+        dev = F.FdaEstimate.from_buffer_copy(mon.est_dev.cpu().numpy().tobytes())
+        assert dev.as_dict() == est[0].as_dict()
+    mon.close()
