@@ -427,8 +427,9 @@ int dispatch_mean(int dtype, const MeanSplit& ms, int FB, const fda::MeanParams*
 // spares the call a copy (a pageable copy of 64 bytes behind a kernel: 9 us).  One page for all contexts of the
 // process; a context takes a place on its first such call and gives it back when it is destroyed; the page goes
 // with the last one.  No place free: the result is copied.
-// Another stream of the program may be capturing a graph meanwhile, which allocations and frees are only
-// allowed beside in the relaxed mode.
+// Another stream of the program may be capturing a graph meanwhile: beside a capture in the global mode
+// allocations, frees and waits are only allowed to threads in the relaxed mode (a wait in another mode is refused
+// and voids the capture).
 struct RelaxedCapture {
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   RelaxedCapture() { if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError(); }
@@ -929,7 +930,10 @@ static void want_result(fda_ctx* ctx, fda::EstimateArgs* args) {
 static int read_result(const fda::EstimateArgs& args, fda_estimate* out_host, hipStream_t st) {
   if (args.host == nullptr)
     FDA_HIP(hipMemcpyAsync(out_host, args.out, sizeof(fda_estimate), hipMemcpyDeviceToHost, st));
-  FDA_HIP(hipStreamSynchronize(st));
+  {
+    const RelaxedCapture relaxed;
+    FDA_HIP(hipStreamSynchronize(st));
+  }
   if (args.host != nullptr) std::memcpy(out_host, args.host, sizeof(fda_estimate));
   return FDA_OK;
 }
