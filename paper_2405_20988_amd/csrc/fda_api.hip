@@ -63,7 +63,8 @@ constexpr double kTileInstrUs = 0.0133, kWorkgroupUs = 8.3, kSlotUs = 0.9, kCell
 constexpr int64_t kQuickTiles = 24;
 constexpr double kQuickGain = 0.85;        // a split is given up for one that the model puts below this share of its time
 constexpr double kSharedByteCost = 0.25;   // per byte of w_t0 / xi / table read by one more workgroup
-constexpr int kXiBlocks = 4096;
+constexpr int kXiBlocks = 1024;           // workgroups of the norm pass of fda_update_xi at most: every workgroup of the scaling pass reads their sums
+constexpr int kXiScaleBlocks = 24576;     // ... of the scaling pass (launches whose predicate is zero pay 0.2 ns for each)
 constexpr int64_t kSyncSmall = 3ll << 19;  // coordinates below which the synchronization takes small blocks
 constexpr int kSyncBlocks = 49152;         // workgroups of a synchronization kernel at most
 constexpr long long kStreamBytes = 512ll << 20;   // slabs beyond this are synchronized with streaming hints
@@ -1037,6 +1038,24 @@ int fda_sync_xi(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, co
     }                                                                                                  \
   } while (0)
 namespace {
+// the two models and xi are too large to stay in the memory-side cache: streaming hints
+bool xi_streams(int64_t d) { return 12 * d > kStreamBytes; }
+// xi = (w_t0 - w_prev) / the norm whose square is spread over npartial sums
+int launch_xi_scale(int64_t d, const float* w_t0, const float* w_prev, float* xi, const int32_t* pred_dev,
+                    const double* partial, int npartial, hipStream_t st) {
+  const SyncGrid sg = sync_grid(d);
+  const int per = (int)((sg.blocks * sg.per + kXiScaleBlocks - 1) / kXiScaleBlocks);
+  const dim3 grid((unsigned)((sg.blocks * sg.per + per - 1) / per)), block(fda::kSmallThreads);
+#define FDA_XI_LAUNCH(S, N)                                                                                  \
+  hipLaunchKernelGGL((fda::xi_scale_kernel<S, N>), grid, block, 0, st, w_t0, w_prev, xi, pred_dev, (long long)d, \
+                     per, partial, npartial)
+  if (sg.vecs == fda::kSyncVecsSmall) FDA_XI_LAUNCH(false, fda::kSyncVecsSmall);
+  else if (xi_streams(d)) FDA_XI_LAUNCH(true, fda::kSyncVecs);
+  else FDA_XI_LAUNCH(false, fda::kSyncVecs);
+#undef FDA_XI_LAUNCH
+  FDA_HIP(hipGetLastError());
+  return FDA_OK;
+}
 // xi != NULL: the synchronization kernel also leaves the squared norm of the model change, and xi is
 // written by the scaling pass of fda_update_xi alone
 int sync_impl(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, const int32_t* pred_dev,
@@ -1067,16 +1086,8 @@ int sync_impl(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, cons
 #undef FDA_SYNC_LAUNCH
   FDA_HIP(hipGetLastError());
   if (xi != nullptr) {
-    // the scaling pass: xi = (w_t0 - w_prev) / norm
-    const int vec_ok = kVecOk;
-    const long long items = vec_ok ? (d.d + 3) / 4 : d.d;
-    long long sblocks = (items + fda::kSmallThreads - 1) / fda::kSmallThreads;
-    const long long cap = (long long)ctx->cus * 16;
-    if (sblocks > cap) sblocks = cap;
-    if (sblocks < 1) sblocks = 1;
-    hipLaunchKernelGGL(fda::xi_scale_kernel, dim3((unsigned)sblocks), dim3(fda::kSmallThreads), 0, st,
-                       w_t0, w_prev, xi, pred_dev, (long long)d.d, vec_ok, norm_group, (int)((sg.blocks + fda::kSyncGroup - 1) / fda::kSyncGroup));
-    FDA_HIP(hipGetLastError());
+    return launch_xi_scale(d.d, w_t0, w_prev, xi, pred_dev, norm_group,
+                           (int)((sg.blocks + fda::kSyncGroup - 1) / fda::kSyncGroup), st);
   }
   return FDA_OK;
 }
@@ -1120,22 +1131,16 @@ int fda_update_xi(fda_ctx* ctx, const float* w_t0, const float* w_prev, float* x
     return fail(FDA_EINVAL, "pointer not aligned to its element type");
   hipStream_t st = static_cast<hipStream_t>(stream);
   double* partial = reinterpret_cast<double*>(ctx->ws + ctx->plan.off_xi);
-  const int vec_ok = kVecOk;
-  const long long items = vec_ok ? (d.d + 3) / 4 : d.d;       // what one thread takes per loop trip
-  long long blocks = (items + fda::kSmallThreads * 4 - 1) / (fda::kSmallThreads * 4);
+  long long blocks = (d.d + fda::sync_block(fda::kSyncVecs) - 1) / fda::sync_block(fda::kSyncVecs);
   if (blocks > kXiBlocks) blocks = kXiBlocks;
-  if (blocks < 1) blocks = 1;
-  hipLaunchKernelGGL(fda::xi_norm_kernel, dim3((unsigned)blocks), dim3(fda::kSmallThreads), 0, st,
-                     w_t0, w_prev, pred_dev, (long long)d.d, vec_ok, partial);
+  if (xi_streams(d.d))
+    hipLaunchKernelGGL(fda::xi_norm_kernel<true>, dim3((unsigned)blocks), dim3(fda::kSmallThreads), 0, st,
+                       w_t0, w_prev, pred_dev, (long long)d.d, partial);
+  else
+    hipLaunchKernelGGL(fda::xi_norm_kernel<false>, dim3((unsigned)blocks), dim3(fda::kSmallThreads), 0, st,
+                       w_t0, w_prev, pred_dev, (long long)d.d, partial);
   FDA_HIP(hipGetLastError());
-  long long sblocks = (items + fda::kSmallThreads - 1) / fda::kSmallThreads;
-  const long long cap = (long long)ctx->cus * 16;
-  if (sblocks > cap) sblocks = cap;
-  if (sblocks < 1) sblocks = 1;
-  hipLaunchKernelGGL(fda::xi_scale_kernel, dim3((unsigned)sblocks), dim3(fda::kSmallThreads), 0, st,
-                     w_t0, w_prev, xi, pred_dev, (long long)d.d, vec_ok, partial, (int)blocks);
-  FDA_HIP(hipGetLastError());
-  return FDA_OK;
+  return launch_xi_scale(d.d, w_t0, w_prev, xi, pred_dev, partial, (int)blocks, st);
 }
 
 int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float* state, float* w_bar,

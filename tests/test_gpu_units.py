@@ -338,3 +338,27 @@ def test_contexts_are_destroyed_and_results_read_back_while_a_graph_is_captured(
         dev = F.FdaEstimate.from_buffer_copy(mon.est_dev.cpu().numpy().tobytes())
         assert dev.as_dict() == est[0].as_dict()
     mon.close()
+
+
+@pytest.mark.parametrize("shift", [0, 1])
+@pytest.mark.parametrize("d", [1, 3, 1023, 1025, 4097, 1_572_863, 1_572_865, 44_739_242, 44_739_243, 100_663_297])
+def test_update_xi_at_the_edges_of_its_blocks(d, shift):
+    """Remainders of vectors and blocks, the sizes where the block size, the hints and the blocks per workgroup
+    change, and vectors off 16 bytes.  Bound: the fp32 runs of four squares leave the norm within 2 * 2^-24, the
+    rounded factor and the product add 2^-24 each."""
+    import paper_2405_20988_amd as F
+    g = torch.Generator(device=DEV)
+    g.manual_seed(d)
+    prev = torch.randn(d + shift, generator=g, device=DEV)[shift:]
+    now = (torch.randn(d + shift, generator=g, device=DEV) * 1e-3)[shift:].add_(prev)
+    buf = torch.full((d + shift + 8,), 7.0, device=DEV)
+    mon = F.FdaMonitor(1, d, "bf16", 1, 1, 8, 0.06, S.hash_coefficients(1, 1), device=DEV)
+    xi = buf[shift:shift + d]
+    mon.update_xi(now, prev, xi)
+    diff = (now - prev).double()
+    want = diff / torch.linalg.vector_norm(diff)
+    assert ((xi.double() - want).abs() <= 2.0 ** -22 * want.abs() + 1e-44).all()
+    assert (buf[:shift] == 7.0).all() and (buf[shift + d:] == 7.0).all()
+    mon.update_xi(now, now, xi)                          # no change: zeros
+    assert not xi.any()
+    mon.close()
