@@ -436,6 +436,10 @@ struct RelaxedCapture {
   RelaxedCapture() { if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError(); }
   ~RelaxedCapture() { if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) (void)hipGetLastError(); }
 };
+hipError_t wait_for(hipStream_t st) {
+  const RelaxedCapture relaxed;
+  return hipStreamSynchronize(st);
+}
 struct HostResults {
   static constexpr int kPlaces = 64;
   std::mutex mutex;
@@ -763,7 +767,7 @@ int fda_last_state_path(fda_ctx* ctx, int32_t* path, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   fda::PathRecord rec;
   FDA_HIP(hipMemcpyAsync(&rec, path_record(ctx, false), sizeof(rec), hipMemcpyDeviceToHost, st));
-  FDA_HIP(hipStreamSynchronize(st));
+  FDA_HIP(wait_for(st));
   *path = rec.last;
   return FDA_OK;
 }
@@ -774,7 +778,7 @@ int fda_last_mean_state_path(fda_ctx* ctx, int32_t* path, void* stream) {
   hipStream_t st = static_cast<hipStream_t>(stream);
   fda::PathRecord rec;
   FDA_HIP(hipMemcpyAsync(&rec, path_record(ctx, true), sizeof(rec), hipMemcpyDeviceToHost, st));
-  FDA_HIP(hipStreamSynchronize(st));
+  FDA_HIP(wait_for(st));
   *path = rec.last;
   return FDA_OK;
 }
@@ -931,10 +935,7 @@ static void want_result(fda_ctx* ctx, fda::EstimateArgs* args) {
 static int read_result(const fda::EstimateArgs& args, fda_estimate* out_host, hipStream_t st) {
   if (args.host == nullptr)
     FDA_HIP(hipMemcpyAsync(out_host, args.out, sizeof(fda_estimate), hipMemcpyDeviceToHost, st));
-  {
-    const RelaxedCapture relaxed;
-    FDA_HIP(hipStreamSynchronize(st));
-  }
+  FDA_HIP(wait_for(st));
   if (args.host != nullptr) std::memcpy(out_host, args.host, sizeof(fda_estimate));
   return FDA_OK;
 }
@@ -1182,7 +1183,7 @@ int fda_step(fda_ctx* ctx, void* w, float* w_t0, float* w_prev, float* xi, float
                        : fda_sync(ctx, w, w_t0, w_prev, pred, stream);
   }
   if (rc != FDA_OK) return rc;
-  if (out_host != nullptr) FDA_HIP(hipStreamSynchronize(st));
+  if (out_host != nullptr) FDA_HIP(wait_for(st));
   return FDA_OK;
 }
 
