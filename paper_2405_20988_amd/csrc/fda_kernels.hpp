@@ -601,6 +601,35 @@ state_kernel(const StateParams prm) {
     if (sk) load_rec_block<Geom::kDwords, kNtShared>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, t.rec);
   };
 
+  // element by element, every access tested: ragged tails
+  auto load_slow = [&](Tile& t, long long j0, bool sc, bool sk) {
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const bool in = (j0 + v < dlim);
+      t.w0[v] = in ? w0p[j0 + v] : 0.0f;
+      if (sc) t.x[v] = in ? xip[j0 + v] : 0.0f;
+    }
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+      const T* row = wrow[k] + j0;
+      if constexpr (sizeof(T) == 4) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          t.w[k][v] = (j0 + v < dlim) ? __float_as_uint(Slab<T>::load_one(row + v)) : 0u;
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; v += 2) {
+          const uint16_t* h = reinterpret_cast<const uint16_t*>(row);
+          const uint32_t lo = (j0 + v < dlim) ? (uint32_t)h[v] : 0u;
+          const uint32_t hi = (j0 + v + 1 < dlim) ? (uint32_t)h[v + 1] : 0u;
+          t.w[k][v >> 1] = lo | (hi << 16);
+        }
+      }
+    }
+    // the table is padded to dpad (whole blocks of 256 coordinates): always whole records
+    if (sk) load_rec_block<Geom::kDwords, false>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, t.rec);
+  };
+
   // the unit of this workgroup's sketch terms
   float S32 = 1.0f, amax = 0.0f;
   uint32_t seen_or = 0u;            // OR of every cell value this lane's adds returned
@@ -631,36 +660,6 @@ state_kernel(const StateParams prm) {
     constexpr bool SC = decltype(sc_tag)::value;
     constexpr bool SK = decltype(sk_tag)::value;
     constexpr bool MX = decltype(mx_tag)::value;
-
-    // element by element, every access tested: ragged tails and slabs without dword alignment
-    auto load_slow = [&](Tile& t, long long j0) {
-#pragma unroll
-      for (int v = 0; v < V; ++v) {
-        const bool in = (j0 + v < dlim);
-        t.w0[v] = in ? w0p[j0 + v] : 0.0f;
-        if constexpr (SC) t.x[v] = in ? xip[j0 + v] : 0.0f;
-      }
-#pragma unroll
-      for (int k = 0; k < KC; ++k) {
-        const T* row = wrow[k] + j0;
-        if constexpr (sizeof(T) == 4) {
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            t.w[k][v] = (j0 + v < dlim) ? __float_as_uint(Slab<T>::load_one(row + v)) : 0u;
-        } else {
-#pragma unroll
-          for (int v = 0; v < 4; v += 2) {
-            const uint16_t* h = reinterpret_cast<const uint16_t*>(row);
-            const uint32_t lo = (j0 + v < dlim) ? (uint32_t)h[v] : 0u;
-            const uint32_t hi = (j0 + v + 1 < dlim) ? (uint32_t)h[v + 1] : 0u;
-            t.w[k][v >> 1] = lo | (hi << 16);
-          }
-        }
-      }
-      // the table is padded to dpad (whole blocks of 256 coordinates): always whole records
-      if constexpr (SK)
-        load_rec_block<Geom::kDwords, false>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, t.rec);
-    };
 
     // fp32 partial sums of the scalar components: kept over kScalarTiles tiles (that many times V
     // terms each), then added to the fp64 sums -- the fp64 conversions and additions are the most
@@ -788,7 +787,7 @@ state_kernel(const StateParams prm) {
     // what is left: at most one ragged tile, or everything when vectors are not possible
     for (; j0 < cend; j0 += kTile) {
       Tile t;
-      load_slow(t, j0);
+      load_slow(t, j0, SC, SK);
       consume(t);
     }
     widen();
@@ -808,24 +807,26 @@ state_kernel(const StateParams prm) {
   // ---- workgroup reduction of the scalar components (fixed shape) ---------------------
   const int lane = tid & 63, wave = tid >> 6;
   constexpr int kWaves = kStateThreads / 64;
-  if (scalars) {
+  // the sums of drifts that were scaled by 1 / inv (a power of two: exact to undo)
+  auto put_scalars = [&](const double (&n)[KC], const double (&q)[KC], double inv) {
+    if (scalars) {
 #pragma unroll
-    for (int k = 0; k < KC; ++k) {
-      const double a = wave_sum63(dn[k]);
-      const double c = wave_sum63(dp[k]);
-      if (lane == 63) { red[(wave * KC + k) * 2] = a; red[(wave * KC + k) * 2 + 1] = c; }
+      for (int k = 0; k < KC; ++k) {
+        const double a = wave_sum63(n[k]);
+        const double c = wave_sum63(q[k]);
+        if (lane == 63) { red[(wave * KC + k) * 2] = a; red[(wave * KC + k) * 2 + 1] = c; }
+      }
     }
-  }
-  __syncthreads();
-  if (scalars && tid < 2 * kcnt) {
-    const int k = tid >> 1, q = tid & 1;
-    double s = 0.0;
-    for (int wv = 0; wv < kWaves; ++wv) s += red[(wv * KC + k) * 2 + q];
-    if (q == 1 && !lin) s = 0.0;               // no LinearFDA: the projection slot stays zero
-    // the sums were formed on drifts scaled by S32 (a power of two: exact to undo)
-    const double inv = 1.0 / (double)S32;
-    prm.part_np[((size_t)p * prm.K + kstart + k) * 2 + q] = s * (q == 0 ? inv * inv : inv);
-  }
+    __syncthreads();
+    if (scalars && tid < 2 * kcnt) {
+      const int k = tid >> 1, c = tid & 1;
+      double s = 0.0;
+      for (int wv = 0; wv < kWaves; ++wv) s += red[(wv * KC + k) * 2 + c];
+      if (c == 1 && !lin) s = 0.0;             // no LinearFDA: the projection slot stays zero
+      prm.part_np[((size_t)p * prm.K + kstart + k) * 2 + c] = s * (c == 0 ? inv * inv : inv);
+    }
+  };
+  put_scalars(dn, dp, 1.0 / (double)S32);
   if (!prm.do_sk) return;
   // ---- flush the LDS sketch to this workgroup's slice of the partial buffer -----------
   const size_t allcells = (size_t)prm.l * prm.m;
@@ -857,11 +858,43 @@ state_kernel(const StateParams prm) {
   if (!again) return;
 
   // ---- redo: the sketch of this workgroup once more, one worker at a time, into 8-byte cells --------
-  const T* const wbase = reinterpret_cast<const T*>(prm.w) + (long long)kstart * prm.row_stride;
+  // The scalar sums too, from the drifts as they are: scaled by a unit that follows the workgroup's own sample,
+  // one drift 2^45 times the sampled ones squares to infinity.  (Below 2^30 a scaled drift cannot.)
   float top = 0.0f;                                    // the largest drift of the chunk
-  for (int k = 0; k < kcnt; ++k)
-    for (long long j = cbeg + tid; j < cend; j += kStateThreads)
-      top = fmaxf(top, fabsf(Slab<T>::load_one(wbase + k * prm.row_stride + j) - w0p[j]));
+  {
+    double n[KC], q[KC];
+#pragma unroll
+    for (int k = 0; k < KC; ++k) { n[k] = 0.0; q[k] = 0.0; }
+    auto fetch = [&](Tile& t, long long j0) {
+      if (j0 + V <= dlim) load_fast(t, j0, true, false);
+      else load_slow(t, j0, true, false);
+    };
+    auto add = [&](const Tile& t) {
+#pragma unroll
+      for (int v = 0; v < V; ++v) {
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+          const float u = raw_elem(t.w[k], v) - t.w0[v];
+          n[k] = fma((double)u, (double)u, n[k]);
+          q[k] = fma((double)t.x[v], (double)u, q[k]);
+          top = fmaxf(top, fabsf(u));
+        }
+      }
+    };
+    long long j0 = cbeg + (long long)tid * V;
+    if (j0 < cend) {
+      Tile cur;
+      fetch(cur, j0);
+      for (j0 += kTile; j0 < cend; j0 += kTile) {
+        Tile nxt;
+        fetch(nxt, j0);
+        add(cur);
+        cur = nxt;
+      }
+      add(cur);
+    }
+    put_scalars(n, q, 1.0);
+  }
   top = block_all_max(top, red + kRedSums);
   if (top == 0.0f) return;                             // no drift at all: the zeros above stand
   // 64-bit integers: at most `chunk` terms of 39 bits and fewer (39 fits chunks below 2^23) stay below 2^62.
@@ -879,6 +912,7 @@ state_kernel(const StateParams prm) {
     *my_unit = CellUnit{inv64, kind, 0};
     atomicMax(&prm.path->now, kind);
   }
+  const T* const wbase = reinterpret_cast<const T*>(prm.w) + (long long)kstart * prm.row_stride;
   const int window = lds_quads * 2;                    // 8-byte cells the LDS holds
   const int mrow_fields = cells32_row_buckets(mrow, KC);      // buckets per row as a placed field counts them
   unsigned long long* const c64 = reinterpret_cast<unsigned long long*>(lds_raw);

@@ -1,0 +1,64 @@
+"""What a workgroup of a state pass does where its own fixed-point unit does not hold: the sums and the sketch that
+it forms once more.  Always against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import fda_synth as S
+from fda_tolerance import check_cells
+from oracle import fda_oracle as O
+
+pytestmark = pytest.mark.gpu
+RTOL = 1e-5
+DEV = "cuda:0"
+
+
+def gen(seed):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(seed)
+    return g
+
+
+def check_both(w, w_t0, xi, dtype, l, m, seed, path=None):
+    """State and average state of the slab within the suite's tolerances; the state pass's kind of cell."""
+    import paper_2405_20988_amd as F
+    K, d = w.shape
+    coef = S.hash_coefficients(seed, l)
+    mon = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, coef, device=DEV)
+    args = S.slab_to_numpy(w), dtype, w_t0.cpu().numpy(), xi.cpu().numpy(), coef, m
+    ref, mref = O.local_state(*args), O.mean_state(*args)
+    mon.local_state(w, w_t0, xi)
+    n, p, sk = mon.state_numpy()
+    assert np.isfinite(n).all() and np.allclose(n, ref["n"], rtol=RTOL, atol=0)
+    assert (np.abs(p - ref["p"]) <= RTOL * ref["p_abs"] + 1e-30).all()
+    check_cells(sk, ref["sk"], ref["sk_abs"], ref["sk_cnt"], ref["u_mean_abs"])
+    got = mon.last_state_path()
+    assert path is None or got in path, got
+    assert mon.estimate_variance(1e30).nonfinite == 0
+    mon.mean_state(w, w_t0, xi)
+    nb, pb, skb = mon.mean_numpy()
+    assert nb == pytest.approx(mref["n"], rel=RTOL)
+    assert abs(pb - mref["p"]) <= RTOL * mref["p_abs"] + 1e-30
+    check_cells(skb, mref["sk"], mref["sk_abs"], mref["sk_cnt"], mref["u_mean_abs"])
+    mon.close()
+
+
+@pytest.mark.parametrize("K,d,l,m,dtype", [(5, 100_001, 5, 250, "f32"), (2, 60_003, 9, 250, "f32"), (1, 70_001, 3, 500, "f32"),
+                                           (8, 90_001, 7, 1000, "bf16"), (6, 50_001, 10, 64, "f32")])
+def test_sums_where_most_of_a_chunk_hardly_moves(K, d, l, m, dtype):
+    """Half of the model moves by 1e-3, the other half by 1e-20, except one coordinate of it that no workgroup
+    samples (20 behind a multiple of 32; runs of 8 start at those): its square in units of the sampled drifts is
+    2^150.  And a coordinate that rests at 1e14, which in those units is beyond fp32 itself."""
+    g = gen(K)
+    u = torch.randn((K, d), generator=g, device=DEV) * 1e-3
+    half = d // 2
+    u[:, half:] *= 1e-17
+    w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+    w_t0[half:] = 0.0
+    w_t0 = w_t0.to(torch.bfloat16).float()
+    j = (half + 9_000) // 2048 * 2048 + 20 + 32 * 5
+    u[:, j] = torch.randn(K, generator=g, device=DEV) * 1e-3
+    w_t0[j + 2048] = 1e14
+    w = (w_t0 + u).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    w_t0[j + 2048] = float(w[0, j + 2048])
+    check_both(w, w_t0, torch.randn(d, generator=g, device=DEV) / d ** 0.5, dtype, l, m, K, path=(1, 2))
