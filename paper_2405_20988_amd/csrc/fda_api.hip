@@ -497,6 +497,11 @@ int static_scratch(unsigned char** out) {
 
 }  // namespace
 
+// A launch that a context needs once in front of others.
+struct Once {
+  bool done = false, captured = false;   // enqueued to run; recorded into a graph
+  unsigned long long capture = 0;        // ... by this capture
+};
 struct fda_ctx {
   fda_desc desc;
   fda::HashCoef coef;
@@ -504,9 +509,9 @@ struct fda_ctx {
   unsigned char* ws;
   int device;
   int cus;
-  bool table_built = false;       // the hash table of the state pass has been enqueued
-  bool mean_table_built = false;  // ... of the mean-state pass (the same table when the plan shares it)
-  bool tickets_cleared = false;
+  Once table;                     // the hash table of the state pass
+  Once mean_table;                // ... of the mean-state pass (`table` when the plan shares it)
+  Once tickets;                   // the counters' first clearing
   fda_estimate* host_place = nullptr;   // in HostResults, once a result has been read back
   // optional timing of the state kernel (fda_profile_enable)
   bool prof_on = false;
@@ -518,19 +523,34 @@ struct fda_ctx {
 };
 
 namespace {
+// Whether the launch behind `once` is still to be enqueued on st.  One that is only being captured has done nothing
+// yet: calls outside that capture, before its first replay, enqueue it for themselves.
+int still_to_do(Once* once, hipStream_t st, bool* todo) {
+  *todo = !once->done;
+  if (once->done) return FDA_OK;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  unsigned long long id = 0;
+  FDA_HIP(hipStreamGetCaptureInfo(st, &status, &id));
+  if (status == hipStreamCaptureStatusNone) {
+    once->done = true;
+  } else {
+    *todo = !once->captured || once->capture != id;
+    once->captured = true;
+    once->capture = id;
+  }
+  return FDA_OK;
+}
+
 // The finished-workgroup counters of finish_kernel and estimate_kernel start at zero and are left
 // at zero by every launch; the workspace arrives uninitialised, so they are cleared once.
 int clear_tickets_once(fda_ctx* c, hipStream_t st) {
-  if (c->tickets_cleared) return FDA_OK;
+  bool todo;
+  const int rc = still_to_do(&c->tickets, st, &todo);
+  if (rc != FDA_OK || !todo) return rc;
   // (the path records, two pairs of ints, lie in front of the counters)
   hipLaunchKernelGGL(fda::clear_u32_kernel, dim3(64), dim3(fda::kSmallThreads), 0, st,
                      reinterpret_cast<unsigned int*>(c->ws + c->plan.off_path), kPathWords + c->plan.tickets);
   FDA_HIP(hipGetLastError());
-  // (a launch that is only being captured has cleared nothing yet: eager calls before its first replay clear the
-  // counters themselves)
-  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-  FDA_HIP(hipStreamIsCapturing(st, &status));
-  c->tickets_cleared = status == hipStreamCaptureStatusNone;
   return FDA_OK;
 }
 
@@ -587,19 +607,15 @@ int build_table(fda_ctx* ctx, int R, int slots, int fb, int words, int grp, int 
 // about to run (for_mean: fda_mean_state, else fda_local_state).
 int prepare_sketch(fda_ctx* ctx, bool for_mean, hipStream_t st) {
   const Plan& pl = ctx->plan;
-  if (!for_mean && !ctx->table_built) {
-    int rc = build_table(ctx, pl.narrow.R, pl.narrow.LR, pl.narrow_fb, pl.words, pl.grp, pl.narrow.KC, pl.off_table, st);
-    if (rc != FDA_OK) return rc;
-    ctx->table_built = true;
-    if (pl.shared_table) ctx->mean_table_built = true;
-  }
-  if (for_mean && !ctx->mean_table_built) {
-    int rc = build_table(ctx, pl.mean.R, pl.mean.rcnt_max, pl.fb, pl.mean_words, 1, 1, pl.off_mean_table, st);
-    if (rc != FDA_OK) return rc;
-    ctx->mean_table_built = true;
-    if (pl.shared_table) ctx->table_built = true;
-  }
-  return FDA_OK;
+  Once* const once = for_mean && !pl.shared_table ? &ctx->mean_table : &ctx->table;
+  bool todo;
+  int rc = still_to_do(once, st, &todo);
+  if (rc != FDA_OK || !todo) return rc;
+  rc = for_mean
+           ? build_table(ctx, pl.mean.R, pl.mean.rcnt_max, pl.fb, pl.mean_words, 1, 1, pl.off_mean_table, st)
+           : build_table(ctx, pl.narrow.R, pl.narrow.LR, pl.narrow_fb, pl.words, pl.grp, pl.narrow.KC, pl.off_table, st);
+  if (rc != FDA_OK) *once = Once{};
+  return rc;
 }
 
 fda::PathRecord* path_record(const fda_ctx* ctx, bool for_mean) {

@@ -291,6 +291,43 @@ def test_eager_calls_between_the_capture_of_a_first_call_and_its_replay(call):
     ref.close()
 
 
+@pytest.mark.parametrize("first", ["local_state", "mean_state"])
+@pytest.mark.parametrize("K,l,m", [(4, 5, 250), (1, 3, 64)])      # a table for each pass; one that both stream
+def test_eager_sketches_between_the_capture_of_a_first_call_and_its_replay(first, K, l, m):
+    """The hash tables that a captured first call records are not there yet when an eager call follows: it makes
+    them itself.  States and average states are those of a context of its own, before and after the replays."""
+    import paper_2405_20988_amd as F
+    d = 30_011
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K)
+    w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+    w = w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3
+    xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    new = lambda: F.FdaMonitor(K, d, "f32", 3, l, m, 0.06, S.hash_coefficients(1, l), device=DEV)
+    mon, ref = new(), new()
+    ref.local_state(w, w_t0, xi)
+    ref.mean_state(w, w_t0, xi)
+    mon.workspace.fill_(0)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        getattr(mon, first)(w, w_t0, xi)
+    for replays in range(4):
+        mon.state.zero_()
+        mon.mean.zero_()
+        mon.local_state(w, w_t0, xi)
+        mon.mean_state(w, w_t0, xi)
+        torch.cuda.synchronize()
+        assert torch.equal(mon.state, ref.state) and torch.equal(mon.mean, ref.mean)
+        out = mon.state if first == "local_state" else mon.mean
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(mon.state, ref.state) and torch.equal(mon.mean, ref.mean)
+    mon.close()
+    ref.close()
+
+
 def test_contexts_are_destroyed_and_results_read_back_while_a_graph_is_captured():
     """The pinned page of the process is taken with the first result that is read back and goes with the last
     context: neither disturbs a capture on another stream."""
