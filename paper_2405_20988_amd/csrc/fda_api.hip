@@ -556,6 +556,7 @@ int clear_tickets_once(fda_ctx* c, hipStream_t st) {
 
 // Fold the recorded event pairs into the running totals (waits for them).
 int prof_drain(fda_ctx* c) {
+  const RelaxedCapture relaxed;
   for (int t = 0; t < c->prof_pending; ++t) {
     FDA_HIP(hipEventSynchronize(c->prof_stop[t]));
     float ms = 0.0f;

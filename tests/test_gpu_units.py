@@ -377,6 +377,49 @@ def test_contexts_are_destroyed_and_results_read_back_while_a_graph_is_captured(
     mon.close()
 
 
+def test_kernel_times_are_read_while_a_graph_is_captured():
+    """fda_profile_read waits for events of its own context: beside a capture on another stream that is allowed and
+    leaves the capture whole."""
+    import threading
+
+    import paper_2405_20988_amd as F
+    from paper_2405_20988_amd import binding as B
+    K, d = 3, 5001
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    w_t0 = torch.randn(d, generator=g, device=DEV) * 0.05
+    w = w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3
+    xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    mon, timed = (F.FdaMonitor(K, d, "f32", 3, 3, 50, 0.06, S.hash_coefficients(1, 3), device=DEV) for _ in range(2))
+    mon.local_state(w, w_t0, xi)
+    want = mon.state.clone()
+    B.fda_profile_enable(timed.ctx, True)
+    with torch.cuda.stream(torch.cuda.Stream()):
+        timed.local_state(w, w_t0, xi)
+    torch.cuda.synchronize()
+    out = []
+
+    def read():
+        try:
+            out.append(B.fda_profile_read(timed.ctx))
+        except Exception as exc:                       # noqa: BLE001 -- compared below
+            out.append(exc)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        mon.local_state(w, w_t0, xi)
+        t = threading.Thread(target=read)
+        t.start()
+        t.join()
+    assert isinstance(out[0], tuple) and out[0][1] == 1, out
+    for _ in range(3):
+        mon.state.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(mon.state, want)
+    mon.close()
+    timed.close()
+
+
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("d", [1, 3, 1023, 1025, 4097, 1_572_863, 1_572_865, 44_739_242, 44_739_243, 100_663_297])
 def test_update_xi_at_the_edges_of_its_blocks(d, shift):
