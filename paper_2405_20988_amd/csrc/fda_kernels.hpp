@@ -174,6 +174,10 @@ __device__ __forceinline__ double dpp_move(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xf, false);
   return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, ROWS, 0xf, false));
+}
 // Sum over the wave in a fixed shape, valid in lane 63.  (Lane moves inside the vector ALU: the twelve sums of
 // a workgroup with six workers took 4 us through the LDS permutes of __shfl_down, and take 1 here.)
 __device__ __forceinline__ double wave_sum63(double v) {
@@ -330,52 +334,67 @@ __device__ __forceinline__ float raw_elem(const uint32_t (&r)[2], int v) {      
 // A workgroup adds drifts to its sketch cells as integers round(u * 2^e).  It chooses 2^e itself, from a
 // sample of the drifts it is about to stream: 512 of its coordinates (runs of 8, which share their cache
 // lines, evenly spaced over the chunk) of up to 8 of its workers, one coordinate per thread.  The typical
-// magnitude is the mean of the sample without its largest value, so that one outlier does not coarsen the
-// unit of everything else.  (One unit per call, from a kernel of its own in front of the pass, took 8 to
+// magnitude is the mean of the sample without the run that holds most of it, so that an outlier, or a few
+// next to each other, do not coarsen the unit of everything else: their terms then leave the cells' range and
+// the workgroup redoes its sketch.  (One unit per call, from a kernel of its own in front of the pass, took 8 to
 // 24 us per call -- cfg1 8, cfg4 24 -- where the workgroups' own samples take 1 to 2.)
 // A sample of nothing but zeros (frozen layers, sparse updates) is repeated over all coordinates.
 constexpr int kSampleRunsGlobal = 4;
+constexpr int kSampleRun = 8;                // coordinates of a run, one per lane
 
-// sum and largest |u| of `rounds` * kStateThreads sampled coordinates of [beg, beg + len), NL rows each;
-// row_of(i, t): row i for sample t
+// What a workgroup saw of its sample: the sum of |u|, and of the run where it is largest.
+struct Sampled { float sum, run; };
+
+// this thread's part, of `rounds` * kStateThreads sampled coordinates of [beg, beg + len), `live` (at most NL) rows
+// each; row_of(i, t): row i for sample t (a readable row also where i >= live)
 template <int NL, typename T, typename RowOf>
-__device__ __forceinline__ void sample_drifts(RowOf row_of, const float* w0, long long beg, long long len, int rounds,
-                                              float& sum, float& top) {
+__device__ __forceinline__ Sampled sample_drifts(RowOf row_of, int live, const float* w0, long long beg, long long len,
+                                                 int rounds) {
   const long long n = (long long)rounds * kStateThreads;
+  Sampled s = {0.0f, 0.0f};
   for (int q = 0; q < rounds; ++q) {
     const int t = q * kStateThreads + (int)threadIdx.x;
-    if (len <= n && t >= len) return;
-    const long long j = beg + (len <= n ? (long long)t : (long long)(t >> 3) * (len / (n >> 3)) + (t & 7));
-    const float base = w0[j];
-    float x[NL];
+    float part = 0.0f;
+    if (len > n || t < len) {
+      const long long j = beg + (len <= n ? (long long)t : (long long)(t / kSampleRun) * (len / (n / kSampleRun)) + t % kSampleRun);
+      const float base = w0[j];
+      float x[NL];
 #pragma unroll
-    for (int i = 0; i < NL; ++i) x[i] = Slab<T>::load_one(row_of(i, t) + j);
+      for (int i = 0; i < NL; ++i) x[i] = Slab<T>::load_one(row_of(i, t) + j);
 #pragma unroll
-    for (int i = 0; i < NL; ++i) {
-      const float u = fabsf(x[i] - base);
-      const bool usable = u < 3.0e38f;                     // not NaN, not infinite
-      top = usable ? fmaxf(top, u) : top;
-      sum += usable ? u : 0.0f;
+      for (int i = 0; i < NL; ++i) {
+        const float u = fabsf(x[i] - base);
+        part += i < live && u < 3.0e38f ? u : 0.0f;        // neither NaN nor infinite
+      }
     }
+    s.sum += part;
+    part += dpp_move<0x111, 0xf>(part);                    // lanes 7 and 15 of every row of 16: the sum of a run
+    part += dpp_move<0x112, 0xf>(part);
+    part += dpp_move<0x114, 0xf>(part);
+    s.run = fmaxf(s.run, threadIdx.x % kSampleRun == kSampleRun - 1 ? part : 0.0f);
   }
+  return s;
 }
-// every thread: the typical magnitude of the workgroup's sample (0: the sample saw no drift)
-__device__ __forceinline__ double sample_mean(float sum, float top, long long count, double* scratch) {
-  double s = (double)sum;
+// every thread: the typical magnitude of a sample of `coords` coordinates, `rows` rows each (0: it saw no drift)
+__device__ __forceinline__ double sample_mean(Sampled s, long long coords, int rows, float* scratch) {
+  constexpr int kWaves = kStateThreads / 64;
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
-    s += __shfl_xor(s, o, 64);
-    top = fmaxf(top, __shfl_xor(top, o, 64));
+    s.sum += __shfl_xor(s.sum, o, 64);
+    s.run = fmaxf(s.run, __shfl_xor(s.run, o, 64));
   }
-  constexpr int kWaves = kStateThreads / 64;
-  float* tops = reinterpret_cast<float*>(scratch + kWaves);
-  if ((threadIdx.x & 63) == 0) { scratch[threadIdx.x >> 6] = s; tops[threadIdx.x >> 6] = top; }
+  if ((threadIdx.x & 63) == 0) { scratch[threadIdx.x >> 6] = s.sum; scratch[kWaves + (threadIdx.x >> 6)] = s.run; }
   __syncthreads();
-  s = 0.0;
-  for (int q = 0; q < kWaves; ++q) { s += scratch[q]; top = fmaxf(top, tops[q]); }
+  double sum = 0.0;
+  float run = 0.0f;
+  for (int q = 0; q < kWaves; ++q) { sum += (double)scratch[q]; run = fmaxf(run, scratch[kWaves + q]); }
   __syncthreads();
-  if (count >= 256) { s = fmax(s - (double)top, 0.0); count -= 1; }
-  return s / (double)count;
+  if (coords >= 32 * kSampleRun) {
+    // (what is left after a run that holds everything but 2^-18 is not known: fp32 sums)
+    sum = sum - (double)run > 0x1p-18 * sum ? sum - (double)run : 0.0;
+    coords -= kSampleRun;
+  }
+  return sum / (double)(coords * rows);
 }
 // 2^e that maps a typical magnitude to [2^(18-shrink), 2^(19-shrink)): a term is then rounded by at most
 // 2^-(19-shrink) of it and single drifts may reach 2048 to 4096 times it before a term leaves 30 bits (a
@@ -639,14 +658,12 @@ state_kernel(const StateParams prm) {
     const long long len = cend - cbeg;
     if (len > 0) {
       auto row_of = [&](int i, int) { return wrow[i]; };
-      float sum = 0.0f, top = 0.0f;
-      sample_drifts<KC, T>(row_of, w0p, cbeg, len, 1, sum, top);
-      typical = sample_mean(sum, top, (len < kStateThreads ? len : kStateThreads) * KC, red);
-      if (typical == 0.0) {
-        sum = top = 0.0f;
-        sample_drifts<KC, T>(row_of, w0p, 0, dlim, kSampleRunsGlobal, sum, top);
-        typical = sample_mean(sum, top, (dlim < kSampleRunsGlobal * kStateThreads ? dlim : kSampleRunsGlobal * kStateThreads) * KC, red);
-      }
+      float* const scratch = reinterpret_cast<float*>(red);
+      typical = sample_mean(sample_drifts<KC, T>(row_of, kcnt, w0p, cbeg, len, 1),
+                            len < kStateThreads ? len : kStateThreads, kcnt, scratch);
+      if (typical == 0.0)
+        typical = sample_mean(sample_drifts<KC, T>(row_of, kcnt, w0p, 0, dlim, kSampleRunsGlobal),
+                              dlim < kSampleRunsGlobal * kStateThreads ? dlim : kSampleRunsGlobal * kStateThreads, kcnt, scratch);
     }
     const float unit = unit_for(typical, prm.shrink);
     sketch = unit != 0.0f;          // otherwise the pass only notes whether there is any drift at all

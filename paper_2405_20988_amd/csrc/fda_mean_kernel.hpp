@@ -124,14 +124,13 @@ mean_state_kernel(const MeanParams prm) {
         const int k = K <= kMeanSampleRows ? (i < K ? i : K - 1) : (int)(((unsigned)(t >> 3) * kMeanSampleRows + i) % (unsigned)K);
         return wbase + (long long)k * rs;
       };
-      float sum = 0.0f, top = 0.0f;
-      sample_drifts<kMeanSampleRows, T>(row_of, w0p, cbeg, len, 1, sum, top);
-      typical = sample_mean(sum, top, (len < kStateThreads ? len : kStateThreads) * kMeanSampleRows, red);
-      if (typical == 0.0) {
-        sum = top = 0.0f;
-        sample_drifts<kMeanSampleRows, T>(row_of, w0p, 0, dlim, kSampleRunsGlobal, sum, top);
-        typical = sample_mean(sum, top, (dlim < kSampleRunsGlobal * kStateThreads ? dlim : kSampleRunsGlobal * kStateThreads) * kMeanSampleRows, red);
-      }
+      const int rows = K < kMeanSampleRows ? K : kMeanSampleRows;
+      float* const scratch = reinterpret_cast<float*>(red);
+      typical = sample_mean(sample_drifts<kMeanSampleRows, T>(row_of, rows, w0p, cbeg, len, 1),
+                            len < kStateThreads ? len : kStateThreads, rows, scratch);
+      if (typical == 0.0)
+        typical = sample_mean(sample_drifts<kMeanSampleRows, T>(row_of, rows, w0p, 0, dlim, kSampleRunsGlobal),
+                              dlim < kSampleRunsGlobal * kStateThreads ? dlim : kSampleRunsGlobal * kStateThreads, rows, scratch);
     }
     const float unit = unit_for(typical, 0);
     sketch = unit != 0.0f;                    // otherwise the pass only notes whether there is any drift at all

@@ -19,8 +19,8 @@ def gen(seed):
     return g
 
 
-def check_both(w, w_t0, xi, dtype, l, m, seed, path=None):
-    """State and average state of the slab within the suite's tolerances; the state pass's kind of cell."""
+def check_both(w, w_t0, xi, dtype, l, m, seed, path=None, mean_path=None):
+    """State and average state of the slab within the suite's tolerances; the passes' kinds of cell."""
     import paper_2405_20988_amd as F
     K, d = w.shape
     coef = S.hash_coefficients(seed, l)
@@ -40,6 +40,7 @@ def check_both(w, w_t0, xi, dtype, l, m, seed, path=None):
     assert nb == pytest.approx(mref["n"], rel=RTOL)
     assert abs(pb - mref["p"]) <= RTOL * mref["p_abs"] + 1e-30
     check_cells(skb, mref["sk"], mref["sk_abs"], mref["sk_cnt"], mref["u_mean_abs"])
+    assert mean_path is None or mon.last_mean_state_path() == mean_path
     mon.close()
 
 
@@ -62,3 +63,19 @@ def test_sums_where_most_of_a_chunk_hardly_moves(K, d, l, m, dtype):
     w = (w_t0 + u).to(torch.float32 if dtype == "f32" else torch.bfloat16)
     w_t0[j + 2048] = float(w[0, j + 2048])
     check_both(w, w_t0, torch.randn(d, generator=g, device=DEV) / d ** 0.5, dtype, l, m, K, path=(1, 2))
+
+
+@pytest.mark.parametrize("size", [1e5, 1e6])
+@pytest.mark.parametrize("together", [1, 2, 8])
+@pytest.mark.parametrize("K,l,m", [(1, 1, 5000), (2, 1, 5000), (3, 1, 5000), (5, 2, 2000)])
+def test_outliers_that_the_sample_sees(K, l, m, together, size):
+    """The first coordinates of a chunk are a sampled run.  Drifts there, `size` times the others, do not coarsen the
+    unit of the others: of the last worker, whose row spare worker slots repeat; one, two or a whole run of them."""
+    import paper_2405_20988_amd as F
+    d, g = 60_003, gen(K)
+    plan = F.FdaMonitor(K, d, "f32", 3, l, m, 0.06, S.hash_coefficients(K, l), device=DEV).plan
+    u = torch.randn((K, d), generator=g, device=DEV) * 1e-4
+    for j in (plan["chunk"], 3 * plan["mean_chunk"]):
+        u[K - 1, j:j + together] = 1e-4 * size
+    w_t0 = torch.zeros(d, device=DEV)
+    check_both(u, w_t0, torch.randn(d, generator=g, device=DEV) / d ** 0.5, "f32", l, m, K, path=(1, 2), mean_path=1)
