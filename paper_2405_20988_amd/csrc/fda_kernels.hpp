@@ -422,6 +422,17 @@ __device__ __forceinline__ float block_all_max(float v, double* scratch) {
   return v;
 }
 
+// sum of a double over the workgroup in a fixed shape, in every thread
+__device__ __forceinline__ double block_all_sum(double v, double* scratch) {
+  v = wave_sum63(v);
+  if ((threadIdx.x & 63) == 63) scratch[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = 0.0;
+  for (int q = 0; q < kStateThreads / 64; ++q) v += scratch[q];
+  __syncthreads();
+  return v;
+}
+
 // ----------------------------------------------------------------------------------------
 // Algorithm 1 line 6.  Workgroup (p, g, r) streams coordinates [p*chunk, (p+1)*chunk) of the
 // workers of group g exactly once and owns the sketch rows of row group r.  Per tile every
@@ -456,7 +467,7 @@ __device__ __forceinline__ float block_all_max(float v, double* scratch) {
 //   seen (by the next addition to the word or by the flush) and the pass is void anyway.
 // A workgroup that saw a value outside the band, or a drift its terms cannot hold, does its own sketch
 // once more, one worker at a time, into 8-byte cells (redo, below): 64-bit integers whose unit follows from
-// the largest drift of the chunk, or fp64 (ds_add_f64) where the drifts' range is too wide for those.  The
+// the magnitudes of the chunk, or fp64 (ds_add_f64) where the drifts' range is too wide for those.  The
 // other workgroups are not concerned.
 // ----------------------------------------------------------------------------------------
 constexpr uint32_t kCellBias = 0x40000000u;   // a 32-bit cell holds its sum plus 2^30
@@ -877,7 +888,8 @@ state_kernel(const StateParams prm) {
   // ---- redo: the sketch of this workgroup once more, one worker at a time, into 8-byte cells --------
   // The scalar sums too, from the drifts as they are: scaled by a unit that follows the workgroup's own sample,
   // one drift 2^45 times the sampled ones squares to infinity.  (Below 2^30 a scaled drift cannot.)
-  float top = 0.0f;                                    // the largest drift of the chunk
+  float top = 0.0f;                                    // the largest drift of the chunk ...
+  double mass = 0.0;                                   // ... and the sum of |u| over the chunk and the worker slots
   {
     double n[KC], q[KC];
 #pragma unroll
@@ -894,6 +906,7 @@ state_kernel(const StateParams prm) {
           const float u = raw_elem(t.w[k], v) - t.w0[v];
           n[k] = fma((double)u, (double)u, n[k]);
           q[k] = fma((double)t.x[v], (double)u, q[k]);
+          mass += (double)fabsf(u);
           top = fmaxf(top, fabsf(u));
         }
       }
@@ -914,16 +927,16 @@ state_kernel(const StateParams prm) {
   }
   top = block_all_max(top, red + kRedSums);
   if (top == 0.0f) return;                             // no drift at all: the zeros above stand
-  // 64-bit integers: at most `chunk` terms of 39 bits and fewer (39 fits chunks below 2^23) stay below 2^62.
-  // A typical drift must keep 17 of them, otherwise (or if none is known) fp64.
-  int qbits = 62;
-  while (qbits > 0 && (1ll << (62 - qbits)) <= prm.chunk) --qbits;
-  if (qbits > 39) qbits = 39;
+  // 64-bit integers: no sum of terms exceeds the sum of their magnitudes, which maps below 2^61, and no term 2^51
+  // (the rounding by kRoundMagic).  A typical drift keeps 30 bits or more, otherwise the cells are fp64: a drift 2^17
+  // times the others leaves them 33 bits (a unit below 2^39 of the largest drift would leave them 21).
+  mass = block_all_sum(mass, red + kRedSums);
   double S64 = 1.0, inv64 = 1.0;
   int kind = kCellF64;
-  if (typical > 0.0 && isfinite(top)) {
-    const int e = qbits - (ilogbf(top) + 1);           // |u| <= top < 2^(ilogb + 1)  =>  |u * 2^e| < 2^qbits
-    if (typical * ldexp(1.0, e) >= 131072.0) { kind = kCellI64; S64 = ldexp(1.0, e); inv64 = ldexp(1.0, -e); }
+  if (isfinite(mass)) {                                // no drift is infinite or NaN
+    const int e1 = 60 - ilogb(mass), e2 = 50 - ilogbf(top), e = e1 < e2 ? e1 : e2;
+    const double ref = typical > 0.0 ? typical : mass / ((double)(cend - cbeg) * KC);
+    if (ref * ldexp(1.0, e) >= 0x1p30) { kind = kCellI64; S64 = ldexp(1.0, e); inv64 = ldexp(1.0, -e); }
   }
   if (tid == 0) {
     *my_unit = CellUnit{inv64, kind, 0};

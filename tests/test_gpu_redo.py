@@ -79,3 +79,26 @@ def test_outliers_that_the_sample_sees(K, l, m, together, size):
         u[K - 1, j:j + together] = 1e-4 * size
     w_t0 = torch.zeros(d, device=DEV)
     check_both(u, w_t0, torch.randn(d, generator=g, device=DEV) / d ** 0.5, "f32", l, m, K, path=(1, 2), mean_path=1)
+
+
+@pytest.mark.parametrize("ratio", [2.0 ** 12, 2.0 ** 17, 2.0 ** 20, 2.0 ** 24])
+@pytest.mark.parametrize("K,l,m,dtype", [(1, 3, 500, "f32"), (2, 1, 500, "bf16"), (3, 5, 250, "f32"), (8, 2, 500, "bf16")])
+def test_a_redone_sketch_keeps_thirty_bits_of_the_other_drifts(K, l, m, dtype, ratio):
+    """One workgroup's worth of coordinates, one drift `ratio` times the others'.  A cell is off by its own fp32
+    rounding and by half a unit for each of its terms, with 2^30 units or more to a typical drift (twice that is
+    allowed: what is typical is sampled); the fp64 cells of the largest ratio are inside that too."""
+    import paper_2405_20988_amd as F
+    d, g = 2_000, gen(K)
+    w = (torch.randn((K, d), generator=g, device=DEV) * 1e-3).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    w[K - 1, 700] = 1e-3 * ratio
+    coef = S.hash_coefficients(K, l)
+    mon = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, coef, device=DEV)
+    zero = torch.zeros(d, device=DEV)
+    ref = O.local_state(S.slab_to_numpy(w), dtype, zero.cpu().numpy(), zero.cpu().numpy(), coef, m)
+    mon.local_state(w, zero, zero)
+    n, _, sk = mon.state_numpy()
+    assert mon.last_state_path() >= 1
+    err = np.abs(sk.astype(np.float64) - ref["sk"])
+    assert (err <= 2.0 ** -24 * np.abs(ref["sk"]) + ref["sk_cnt"][None] * 2.0 ** -30 * 0.8e-3 + 1e-45).all()
+    assert np.allclose(n, ref["n"], rtol=2.0 ** -23, atol=0)
+    mon.close()
