@@ -928,15 +928,16 @@ state_kernel(const StateParams prm) {
   top = block_all_max(top, red + kRedSums);
   if (top == 0.0f) return;                             // no drift at all: the zeros above stand
   // 64-bit integers: no sum of terms exceeds the sum of their magnitudes, which maps below 2^61, and no term 2^51
-  // (the rounding by kRoundMagic).  A typical drift keeps 30 bits or more, otherwise the cells are fp64: a drift 2^17
-  // times the others leaves them 33 bits (a unit below 2^39 of the largest drift would leave them 21).
+  // (the rounding by kRoundMagic).  A typical drift keeps 29 bits or more, otherwise the cells are fp64: its rounding
+  // then stays 2^4 below that of the state's fp32 cells.  (A drift 2^17 times the others leaves them 33 bits; a unit
+  // below 2^39 of the largest drift would leave them 21.)
   mass = block_all_sum(mass, red + kRedSums);
   double S64 = 1.0, inv64 = 1.0;
   int kind = kCellF64;
   if (isfinite(mass)) {                                // no drift is infinite or NaN
     const int e1 = 60 - ilogb(mass), e2 = 50 - ilogbf(top), e = e1 < e2 ? e1 : e2;
     const double ref = typical > 0.0 ? typical : mass / ((double)(cend - cbeg) * KC);
-    if (ref * ldexp(1.0, e) >= 0x1p30) { kind = kCellI64; S64 = ldexp(1.0, e); inv64 = ldexp(1.0, -e); }
+    if (ref * ldexp(1.0, e) >= 0x1p29) { kind = kCellI64; S64 = ldexp(1.0, e); inv64 = ldexp(1.0, -e); }
   }
   if (tid == 0) {
     *my_unit = CellUnit{inv64, kind, 0};
