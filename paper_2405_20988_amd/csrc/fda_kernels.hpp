@@ -338,9 +338,14 @@ __device__ __forceinline__ float raw_elem(const uint32_t (&r)[2], int v) {      
 // next to each other, do not coarsen the unit of everything else: their terms then leave the cells' range and
 // the workgroup redoes its sketch.  (One unit per call, from a kernel of its own in front of the pass, took 8 to
 // 24 us per call -- cfg1 8, cfg4 24 -- where the workgroups' own samples take 1 to 2.)
-// A sample of nothing but zeros (frozen layers, sparse updates) is repeated over all coordinates.
+// A sample of nothing but zeros (frozen layers, sparse updates) is repeated over all coordinates.  A chunk of
+// fewer than 256 coordinates (the ragged end) has too few to leave a run out: the sample takes the ones in front too.
 constexpr int kSampleRunsGlobal = 4;
 constexpr int kSampleRun = 8;                // coordinates of a run, one per lane
+constexpr int kSampleTrimmed = 32 * kSampleRun;        // coordinates a sample needs to leave a run out
+__device__ __forceinline__ long long sample_begin(long long beg, long long end) {
+  return end - beg >= kSampleTrimmed ? beg : end > kStateThreads ? end - kStateThreads : 0;
+}
 
 // What a workgroup saw of its sample: the sum of |u|, and of the run where it is largest.
 struct Sampled { float sum, run; };
@@ -389,7 +394,7 @@ __device__ __forceinline__ double sample_mean(Sampled s, long long coords, int r
   float run = 0.0f;
   for (int q = 0; q < kWaves; ++q) { sum += (double)scratch[q]; run = fmaxf(run, scratch[kWaves + q]); }
   __syncthreads();
-  if (coords >= 32 * kSampleRun) {
+  if (coords >= kSampleTrimmed) {
     // (what is left after a run that holds everything but 2^-18 is not known: fp32 sums)
     sum = sum - (double)run > 0x1p-18 * sum ? sum - (double)run : 0.0;
     coords -= kSampleRun;
@@ -666,11 +671,11 @@ state_kernel(const StateParams prm) {
   double typical = 0.0;             // mean sampled |u|
   bool sketch = false;
   if (prm.do_sk) {
-    const long long len = cend - cbeg;
-    if (len > 0) {
+    if (cend > cbeg) {
+      const long long sbeg = sample_begin(cbeg, cend), len = cend - sbeg;
       auto row_of = [&](int i, int) { return wrow[i]; };
       float* const scratch = reinterpret_cast<float*>(red);
-      typical = sample_mean(sample_drifts<KC, T>(row_of, kcnt, w0p, cbeg, len, 1),
+      typical = sample_mean(sample_drifts<KC, T>(row_of, kcnt, w0p, sbeg, len, 1),
                             len < kStateThreads ? len : kStateThreads, kcnt, scratch);
       if (typical == 0.0)
         typical = sample_mean(sample_drifts<KC, T>(row_of, kcnt, w0p, 0, dlim, kSampleRunsGlobal),

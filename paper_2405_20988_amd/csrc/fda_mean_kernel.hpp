@@ -118,15 +118,15 @@ mean_state_kernel(const MeanParams prm) {
   bool sketch = false;
   if (prm.do_sk) {
     double typical = 0.0;
-    const long long len = cend - cbeg;
-    if (len > 0) {
+    if (cend > cbeg) {
+      const long long sbeg = sample_begin(cbeg, cend), len = cend - sbeg;
       auto row_of = [&](int i, int t) {
         const int k = K <= kMeanSampleRows ? (i < K ? i : K - 1) : (int)(((unsigned)(t >> 3) * kMeanSampleRows + i) % (unsigned)K);
         return wbase + (long long)k * rs;
       };
       const int rows = K < kMeanSampleRows ? K : kMeanSampleRows;
       float* const scratch = reinterpret_cast<float*>(red);
-      typical = sample_mean(sample_drifts<kMeanSampleRows, T>(row_of, rows, w0p, cbeg, len, 1),
+      typical = sample_mean(sample_drifts<kMeanSampleRows, T>(row_of, rows, w0p, sbeg, len, 1),
                             len < kStateThreads ? len : kStateThreads, rows, scratch);
       if (typical == 0.0)
         typical = sample_mean(sample_drifts<kMeanSampleRows, T>(row_of, rows, w0p, 0, dlim, kSampleRunsGlobal),

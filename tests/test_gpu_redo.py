@@ -101,3 +101,16 @@ def test_a_redone_sketch_keeps_29_bits_of_the_other_drifts(K, l, m, dtype, ratio
     assert (err <= 2.0 ** -24 * np.abs(ref["sk"]) + ref["sk_cnt"][None] * 2.0 ** -30 * 0.8e-3 + 1e-45).all()
     assert np.allclose(n, ref["n"], rtol=2.0 ** -23, atol=0)
     mon.close()
+
+
+@pytest.mark.parametrize("size", [2.0 ** 12, 2.0 ** 14, 2.0 ** 17])
+@pytest.mark.parametrize("K,d,l,m,dtype", [(3, 2_049, 1, 16, "f32"), (2, 2_049, 3, 16, "bf16"), (6, 4_100, 2, 16, "f32"),
+                                           (5, 10_245, 2, 32, "f32"), (8, 100_107, 1, 16, "f32"), (4, 300, 1, 16, "f32")])
+def test_an_outlier_in_a_short_last_chunk(K, d, l, m, dtype, size):
+    """The last workgroup has a few coordinates of its own, the last one of them `size` times the others: it leaves
+    the other workers' drifts there their unit."""
+    g = gen(d)
+    w_t0 = torch.zeros(d, device=DEV)
+    w = (torch.randn((K, d), generator=g, device=DEV) * 1e-3).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    w[K - 1, d - 1] = 1e-3 * size
+    check_both(w, w_t0, torch.randn(d, generator=g, device=DEV) / d ** 0.5, dtype, l, m, K, path=(0, 1))
