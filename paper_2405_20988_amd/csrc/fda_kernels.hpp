@@ -894,6 +894,7 @@ state_kernel(const StateParams prm) {
   // The scalar sums too, from the drifts as they are: scaled by a unit that follows the workgroup's own sample,
   // one drift 2^45 times the sampled ones squares to infinity.  (Below 2^30 a scaled drift cannot.)
   float top = 0.0f;                                    // the largest drift of the chunk ...
+  const long long j0_first = cbeg + (long long)tid * V;
   double mass = 0.0;                                   // ... and the sum of |u| over the chunk and the worker slots
   {
     double n[KC], q[KC];
@@ -936,12 +937,24 @@ state_kernel(const StateParams prm) {
   // (the rounding by kRoundMagic).  A typical drift keeps 29 bits or more, otherwise the cells are fp64: its rounding
   // then stays 2^4 below that of the state's fp32 cells.  (A drift 2^17 times the others leaves them 33 bits; a unit
   // below 2^39 of the largest drift would leave them 21.)
+  // (What is typical follows from all coordinates here, where the sample met more than one such drift: the magnitude
+  // that the means of half of the threads reach.)
+  const long long tiles = j0_first < cend ? (cend - j0_first + kTile - 1) / kTile : 0;
+  const int scale = mass > 0.0 ? ilogb(mass / (double)(tiles * (V * KC))) : INT32_MIN;
   mass = block_all_sum(mass, red + kRedSums);
   double S64 = 1.0, inv64 = 1.0;
   int kind = kCellF64;
   if (isfinite(mass)) {                                // no drift is infinite or NaN
     const int e1 = 60 - ilogb(mass), e2 = 50 - ilogbf(top), e = e1 < e2 ? e1 : e2;
-    const double ref = typical > 0.0 ? typical : mass / ((double)(cend - cbeg) * KC);
+    double ref = typical > 0.0 ? typical : mass / ((double)(cend - cbeg) * KC);
+    constexpr int kNone = -200;                        // below every float's exponent
+    const int lanes = (int)(cend - cbeg < kTile ? (cend - cbeg + V - 1) / V : kStateThreads);
+    int lo = kNone, hi = 128;                          // the largest exponent that half of them reach
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (2.0 * block_all_sum(scale >= mid ? 1.0 : 0.0, red + kRedSums) >= lanes) lo = mid; else hi = mid - 1;
+    }
+    if (lo != kNone && ref > ldexp(16.0, lo)) ref = ldexp(1.0, lo);
     if (ref * ldexp(1.0, e) >= 0x1p29) { kind = kCellI64; S64 = ldexp(1.0, e); inv64 = ldexp(1.0, -e); }
   }
   if (tid == 0) {
