@@ -471,7 +471,7 @@ __device__ __forceinline__ double block_all_sum(double v, double* scratch) {
 //   what two 32-bit additions would have left; once it leaves the band its top bit is
 //   seen (by the next addition to the word or by the flush) and the pass is void anyway.
 // A workgroup that saw a value outside the band, or a drift its terms cannot hold, does its own sketch
-// once more, one worker at a time, into 8-byte cells (redo, below): 64-bit integers whose unit follows from
+// once more into 8-byte cells (redo, below): 64-bit integers whose unit follows from
 // the magnitudes of the chunk, or fp64 (ds_add_f64) where the drifts' range is too wide for those.  The
 // other workgroups are not concerned.
 // ----------------------------------------------------------------------------------------
@@ -890,7 +890,29 @@ state_kernel(const StateParams prm) {
   if (tid == 0) *my_unit = CellUnit{1.0 / (double)S32, kCellI32, 0};
   if (!again) return;
 
-  // ---- redo: the sketch of this workgroup once more, one worker at a time, into 8-byte cells --------
+  // ---- redo: the sketch of this workgroup once more, into 8-byte cells ------------------------------
+  // The other workgroups have ended by then, so what it takes is the latency of one CU's loads and its LDS
+  // additions: the tiles are loaded as in the pass, the next one in flight, and sign-split rows leave room for the
+  // 8-byte cells of all workers at once.  (A call where one drift is 2^14 times the others: 30 x 7M fp32 0.89 ms,
+  // 8 x 350M bf16 20.8 -- 0.18 and 3.3 without it; one worker at a time, element by element, 1.93 and 34.5.)
+  auto sweep = [&](auto sc_tag, auto sk_tag, auto&& add) {
+    constexpr bool SC = decltype(sc_tag)::value, SK = decltype(sk_tag)::value;
+    auto fetch = [&](Tile& t, long long j0) {
+      if (j0 + V <= dlim) load_fast(t, j0, SC, SK);
+      else load_slow(t, j0, SC, SK);
+    };
+    long long j0 = cbeg + (long long)tid * V;
+    if (j0 >= cend) return;
+    Tile cur;
+    fetch(cur, j0);
+    for (j0 += kTile; j0 < cend; j0 += kTile) {
+      Tile nxt;
+      fetch(nxt, j0);
+      add(cur);
+      cur = nxt;
+    }
+    add(cur);
+  };
   // The scalar sums too, from the drifts as they are: scaled by a unit that follows the workgroup's own sample,
   // one drift 2^45 times the sampled ones squares to infinity.  (Below 2^30 a scaled drift cannot.)
   float top = 0.0f;                                    // the largest drift of the chunk ...
@@ -900,11 +922,7 @@ state_kernel(const StateParams prm) {
     double n[KC], q[KC];
 #pragma unroll
     for (int k = 0; k < KC; ++k) { n[k] = 0.0; q[k] = 0.0; }
-    auto fetch = [&](Tile& t, long long j0) {
-      if (j0 + V <= dlim) load_fast(t, j0, true, false);
-      else load_slow(t, j0, true, false);
-    };
-    auto add = [&](const Tile& t) {
+    sweep(std::true_type{}, std::false_type{}, [&](const Tile& t) {
 #pragma unroll
       for (int v = 0; v < V; ++v) {
 #pragma unroll
@@ -916,19 +934,7 @@ state_kernel(const StateParams prm) {
           top = fmaxf(top, fabsf(u));
         }
       }
-    };
-    long long j0 = cbeg + (long long)tid * V;
-    if (j0 < cend) {
-      Tile cur;
-      fetch(cur, j0);
-      for (j0 += kTile; j0 < cend; j0 += kTile) {
-        Tile nxt;
-        fetch(nxt, j0);
-        add(cur);
-        cur = nxt;
-      }
-      add(cur);
-    }
+    });
     put_scalars(n, q, 1.0);
   }
   top = block_all_max(top, red + kRedSums);
@@ -961,45 +967,57 @@ state_kernel(const StateParams prm) {
     *my_unit = CellUnit{inv64, kind, 0};
     atomicMax(&prm.path->now, kind);
   }
-  const T* const wbase = reinterpret_cast<const T*>(prm.w) + (long long)kstart * prm.row_stride;
-  const int window = lds_quads * 2;                    // 8-byte cells the LDS holds
+  const bool ints = __builtin_amdgcn_readfirstlane(kind) == kCellI64;
+  const int window = lds_quads * 2;                    // 8-byte cells the LDS holds: of `per` workers, or some of one
+  const int per = window >= cells ? window / cells : 1;
   const int mrow_fields = cells32_row_buckets(mrow, KC);      // buckets per row as a placed field counts them
+  const float rows_per_field = 1.0f / (float)mrow_fields;
   unsigned long long* const c64 = reinterpret_cast<unsigned long long*>(lds_raw);
-  for (int k = 0; k < kcnt; ++k) {
-    const T* const row = wbase + k * prm.row_stride;
-    unsigned long long* const dst = reinterpret_cast<unsigned long long*>(share + (size_t)k * allcells * 8);
+  for (int kb = 0; kb < kcnt; kb += per) {
+    const int ke = kb + per < kcnt ? kb + per : kcnt;
     for (int c0 = 0; c0 < cells; c0 += window) {
       const int ccnt = cells - c0 < window ? cells - c0 : window;
       __syncthreads();
-      for (int t = tid; t < ccnt; t += kStateThreads) c64[t] = 0ull;          // integer 0 and 0.0
+      for (int t = tid; t < (ke - kb) * ccnt; t += kStateThreads) c64[t] = 0ull;          // integer 0 and 0.0
       __syncthreads();
-      for (long long j0 = cbeg + (long long)tid * V; j0 < cend; j0 += kTile) {
-        uint32_t rec[Geom::kDwords];
-        load_rec_block<Geom::kDwords, false>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, rec);
+      sweep(std::false_type{}, std::true_type{}, [&](const Tile& t) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-          const float u = j0 + v < dlim ? Slab<T>::load_one(row + j0 + v) - w0p[j0 + v] : 0.0f;
-          const double y = fma((double)u, S64, kRoundMagic);                  // round to integer
-          const long long q = __double_as_longlong(y) - __double_as_longlong(kRoundMagic);
+          unsigned long long x[KC];                    // the terms: round(u * S64), or u
+#pragma unroll
+          for (int k = 0; k < KC; ++k) {
+            const double u = (double)(raw_elem(t.w[k], v) - t.w0[v]);
+            x[k] = ints ? (unsigned long long)(__double_as_longlong(fma(u, S64, kRoundMagic)) - __double_as_longlong(kRoundMagic))
+                        : (unsigned long long)__double_as_longlong(u);
+          }
 #pragma unroll
           for (int i = 0; i < LR; ++i) {
             if (i >= rcnt) continue;
-            int f = (int)rec_field_exact<LR, FB>(rec, v, i), of = i;
+            int f = (int)rec_field_exact<LR, FB>(t.rec, v, i), of = i;
             if (prm.grp > 1) {                         // placed rows: the field names the row within the group
-              const int n = f / mrow_fields;
+              const int n = (int)(((float)f + 0.5f) * rows_per_field);       // f / mrow_fields, exact: f < 2^13, n < 9
               f -= n * mrow_fields;
               of = i / prm.grp * prm.grp + n;
             }
             const bool neg = f >= prm.m;
             const int c = of * prm.m + (neg ? f - prm.m : f) - c0;
             if ((unsigned)c >= (unsigned)ccnt) continue;
-            if (kind == kCellI64) atomicAdd(c64 + c, (unsigned long long)(neg ? -q : q));
-            else atomicAdd(reinterpret_cast<double*>(lds_raw) + c, neg ? -(double)u : (double)u);
+            unsigned long long* cell = c64 + c;
+#pragma unroll
+            for (int k = 0; k < KC; ++k) {
+              if (k < kb || k >= ke) continue;
+              if (ints) atomicAdd(cell, neg ? 0ull - x[k] : x[k]);
+              else atomicAdd(reinterpret_cast<double*>(cell), __longlong_as_double((long long)(neg ? x[k] ^ (1ull << 63) : x[k])));
+              cell += ccnt;
+            }
           }
         }
-      }
+      });
       __syncthreads();
-      for (int t = tid; t < ccnt; t += kStateThreads) dst[c0 + t] = c64[t];
+      for (int k = kb; k < ke; ++k) {
+        unsigned long long* const dst = reinterpret_cast<unsigned long long*>(share + (size_t)k * allcells * 8) + c0;
+        for (int t = tid; t < ccnt; t += kStateThreads) dst[t] = c64[(k - kb) * ccnt + t];
+      }
     }
   }
 }

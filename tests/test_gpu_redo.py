@@ -134,3 +134,52 @@ def test_what_is_typical_of_a_redone_chunk(K, l, m, dtype):
     err = np.abs(sk.astype(np.float64) - ref["sk"])
     assert (err <= 2.0 ** -24 * np.abs(ref["sk"]) + ref["sk_cnt"][None] * 2.0 ** -30 * 0.8e-3 + 1e-45).all()
     mon.close()
+
+
+@pytest.mark.parametrize("size,path", [(2.0 ** 14, 1), (1e12, 2)])       # 64-bit integers, fp64
+@pytest.mark.parametrize("K,d,l,m,dtype", [
+    (1, 50_001, 9, 250, "f32"), (1, 50_001, 1, 20_000, "bf16"),          # half of a worker's cells at a time
+    (2, 50_001, 1, 15_000, "f32"),                                       # one worker at a time
+    (5, 100_001, 5, 250, "f32"), (8, 50_001, 7, 1000, "bf16"), (4, 30_001, 5, 500, "f32"), (8, 30_001, 4, 300, "bf16"),  # all
+    (3, 2_049, 1, 16, "f32"), (30, 60_001, 9, 250, "bf16"),
+    (2, 1_500_003, 2, 64, "f32")])                                       # several tiles to a chunk
+def test_redone_sketches_of_every_layout(K, d, l, m, dtype, size, path):
+    """One workgroup in the middle and the one of the ragged end meet a drift that their terms cannot hold."""
+    g = gen(K)
+    w_t0 = torch.randn(d, generator=g, device=DEV).mul_(0.05).to(torch.bfloat16).float()
+    w = (w_t0 + torch.randn((K, d), generator=g, device=DEV) * 1e-3).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    w[K - 1, d - 1] = -1e-3 * size
+    w[0, d // 2 + 37] = 1e-3 * size
+    check_both(w, w_t0, torch.randn(d, generator=g, device=DEV) / d ** 0.5, dtype, l, m, K, path=(path,), mean_path=1)
+
+
+def microseconds(call):
+    """A pass among others: the best of five groups."""
+    start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    best = float("inf")
+    for _ in range(6):
+        start.record()
+        for _ in range(4):
+            call()
+        stop.record()
+        stop.synchronize()
+        best = min(best, start.elapsed_time(stop) * 250.0)
+    return best
+
+
+def test_a_redone_state_does_not_take_ten_times_the_pass():
+    """One workgroup of 255 redoes its sketch: 5 times the pass without it (11 times with one worker and one element
+    at a time)."""
+    import paper_2405_20988_amd as F
+    K, d = 30, 7_000_000
+    mon = F.FdaMonitor(K, d, "f32", 3, 5, 250, 0.06, S.hash_coefficients(1, 5), device=DEV)
+    w_t0 = torch.zeros(d, device=DEV)
+    w = torch.randn((K, d), generator=gen(1), device=DEV) * 1e-3
+    plain = microseconds(lambda: mon.local_state(w, w_t0, w_t0))
+    assert mon.last_state_path() == 0
+    w[1, d // 3 + 5] = 1e-3 * 2 ** 14
+    redone = microseconds(lambda: mon.local_state(w, w_t0, w_t0))
+    assert mon.last_state_path() == 1
+    print("plain %.0f us, redone %.0f us" % (plain, redone))
+    assert redone < 8.0 * plain
+    mon.close()
