@@ -144,16 +144,18 @@ mean_state_kernel(const MeanParams prm) {
   float amax = 0.0f;
 
   // SC: this workgroup also produces the scalar components; SK: it accumulates sketch rows.
-  // MX: it notes the largest drift.
-  auto run = [&](auto sc_tag, auto sk_tag, auto mx_tag) {
+  // MX: it notes the largest drift.  WIDE: the sketch in fp64, unscaled.
+  auto run = [&](auto sc_tag, auto sk_tag, auto mx_tag, auto wide_tag) {
     constexpr bool SC = decltype(sc_tag)::value;
     constexpr bool SK = decltype(sk_tag)::value;
     constexpr bool MX = decltype(mx_tag)::value;
-    long long acc[V];         // sum over the workers of round(u * Sm)
+    constexpr bool WIDE = decltype(wide_tag)::value;
+    using Acc = std::conditional_t<WIDE, double, long long>;
+    Acc acc[V];               // sum over the workers of round(u * Sm), or of u
     float um[V];              // scalar workgroups: sum over the workers of u, for the average model
     float sn = 0.0f, sp = 0.0f;
 #pragma unroll
-    for (int v = 0; v < V; ++v) { acc[v] = 0; um[v] = 0.0f; }
+    for (int v = 0; v < V; ++v) { acc[v] = Acc(0); um[v] = 0.0f; }
 
     // slab rows k0 .. k0+KB-1 (rows past the last worker repeat it; consume() drops them)
     auto load_batch_fast = [&](Batch& bt, long long j0, int k0) {
@@ -225,7 +227,8 @@ mean_state_kernel(const MeanParams prm) {
             um[v] += u;
           }
           if constexpr (MX) amax = fmaxf(amax, fabsf(u));
-          if constexpr (SK) acc[v] += (long long)round_half_up(u * Sm);
+          if constexpr (SK && WIDE) acc[v] += (double)u;
+          else if constexpr (SK) acc[v] += (long long)round_half_up(u * Sm);
         }
       }
     };
@@ -270,10 +273,14 @@ mean_state_kernel(const MeanParams prm) {
             const uint32_t sb = hw & Geom::kFieldMask;                     // bucket + m * (sign is -1)
             const bool neg = sb >= (uint32_t)prm.m;
             const uint32_t off = ((neg ? sb - (uint32_t)prm.m : sb) << 3) + rowbase[i];
-            const unsigned long long q = (unsigned long long)acc[v];
-            atomicAdd(reinterpret_cast<unsigned long long*>(lds_raw + off), neg ? 0ull - q : q);
+            if constexpr (WIDE) {
+              atomicAdd(reinterpret_cast<double*>(lds_raw + off), neg ? -acc[v] : acc[v]);
+            } else {
+              const unsigned long long q = (unsigned long long)acc[v];
+              atomicAdd(reinterpret_cast<unsigned long long*>(lds_raw + off), neg ? 0ull - q : q);
+            }
           }
-          acc[v] = 0;
+          acc[v] = Acc(0);
         }
       }
     };
@@ -321,12 +328,14 @@ mean_state_kernel(const MeanParams prm) {
       finish(h, j0, false);
     }
   };
+  constexpr std::true_type yes{};
+  constexpr std::false_type no{};
   if (scalars) {
-    if (sketch) run(std::true_type{}, std::true_type{}, std::true_type{});
-    else if (prm.do_sk) run(std::true_type{}, std::false_type{}, std::true_type{});
-    else run(std::true_type{}, std::false_type{}, std::false_type{});
+    if (sketch) run(yes, yes, yes, no);
+    else if (prm.do_sk) run(yes, no, yes, no);
+    else run(yes, no, no, no);
   } else if (sketch) {
-    run(std::false_type{}, std::true_type{}, std::true_type{});
+    run(no, yes, yes, no);
   } else if (prm.do_sk) {
     for (long long j = cbeg + tid; j < cend; j += kStateThreads)
       for (int k = 0; k < K; ++k) amax = fmaxf(amax, fabsf(Slab<T>::load_one(wbase + (long long)k * rs + j) - w0p[j]));
@@ -354,29 +363,17 @@ mean_state_kernel(const MeanParams prm) {
   if (!prm.do_sk) return;
   const bool again = block_all_max(bad ? 1.0f : 0.0f, red + kRedSums) != 0.0f;
   if (again) {
-    // ---- redo: the sketch of this workgroup once more, in fp64 -----------------------------------------
+    // ---- redo: the sketch of this workgroup once more, in fp64, as in the pass --------------------------
+    // (30 x 7M fp32: 284 us a call where every workgroup does this, 228 where one does, 149 where none does; element
+    // by element 782 and 471.)
     double* const cd = reinterpret_cast<double*>(lds_raw);
     for (int t = tid; t < lds_cells; t += kStateThreads) cd[t] = 0.0;
     __syncthreads();
-    for (long long j0 = cbeg + (long long)tid * V; j0 < cend; j0 += kTile) {
-      uint32_t rec[Geom::kDwords];
-      load_rec_block<Geom::kDwords, false>(recs + (j0 >> 8) * (64 * Geom::kDwords), (int)(j0 >> 2) & 63, rec);
+    // (the row bases are reloaded here: kept live from the pass they push eight and nine rows to 139..153 registers,
+    // beyond what two workgroups per CU leave)
 #pragma unroll
-      for (int v = 0; v < V; ++v) {
-        double us = 0.0;                         // sum over the workers of u
-        if (j0 + v < dlim) {
-          const float base = w0p[j0 + v];
-          for (int k = 0; k < K; ++k) us += (double)(Slab<T>::load_one(wbase + (long long)k * rs + j0 + v) - base);
-        }
-#pragma unroll
-        for (int i = 0; i < LR; ++i) {
-          const uint32_t sb = rec_field<LR, FB>(rec, v, i) & Geom::kFieldMask;
-          const bool neg = sb >= (uint32_t)prm.m;
-          const uint32_t off = ((neg ? sb - (uint32_t)prm.m : sb) << 3) + rowbase[i];
-          atomicAdd(reinterpret_cast<double*>(lds_raw + off), neg ? -us : us);
-        }
-      }
-    }
+    for (int i = 0; i < LR; ++i) asm volatile("" : "+s"(rowbase[i]));
+    run(no, yes, no, yes);
     __syncthreads();
   }
   // ---- flush the LDS sketch to this workgroup's slice of the partial buffer -----------

@@ -183,3 +183,20 @@ def test_a_redone_state_does_not_take_ten_times_the_pass():
     print("plain %.0f us, redone %.0f us" % (plain, redone))
     assert redone < 8.0 * plain
     mon.close()
+
+
+def test_a_redone_average_state_does_not_take_four_times_the_pass():
+    """Every workgroup redoes its sketch: twice the pass without it (5 times element by element)."""
+    import paper_2405_20988_amd as F
+    K, d = 30, 7_000_000
+    mon = F.FdaMonitor(K, d, "f32", 3, 5, 250, 0.06, S.hash_coefficients(1, 5), device=DEV)
+    w_t0 = torch.zeros(d, device=DEV)
+    w = torch.randn((K, d), generator=gen(1), device=DEV) * 1e-3
+    plain = microseconds(lambda: mon.mean_state(w, w_t0, w_t0))
+    assert mon.last_mean_state_path() == 0
+    w[:, 11::mon.plan["mean_chunk"] // 4] = 1e-3 * 2 ** 20
+    redone = microseconds(lambda: mon.mean_state(w, w_t0, w_t0))
+    assert mon.last_mean_state_path() == 1
+    print("plain %.0f us, redone %.0f us" % (plain, redone))
+    assert redone < 3.5 * plain
+    mon.close()
