@@ -180,7 +180,8 @@ __device__ __forceinline__ float dpp_move(float v) {
 }
 // Sum over the wave in a fixed shape, valid in lane 63.  (Lane moves inside the vector ALU: the twelve sums of
 // a workgroup with six workers took 4 us through the LDS permutes of __shfl_down, and take 1 here.)
-__device__ __forceinline__ double wave_sum63(double v) {
+template <typename F>
+__device__ __forceinline__ F wave_sum63(F v) {
   v += dpp_move<0x111, 0xf>(v);               // row_shr 1, 2, 4, 8: lane 15 of every row of 16 has the row's sum
   v += dpp_move<0x112, 0xf>(v);
   v += dpp_move<0x114, 0xf>(v);
@@ -188,6 +189,14 @@ __device__ __forceinline__ double wave_sum63(double v) {
   v += dpp_move<0x142, 0xa>(v);               // row_bcast 15: rows 1 and 3 add the row before
   v += dpp_move<0x143, 0xc>(v);               // row_bcast 31: rows 2 and 3 add rows 0 and 1
   return v;
+}
+__device__ __forceinline__ float wave_max63(float v) {       // the largest of values >= 0
+  v = fmaxf(v, dpp_move<0x111, 0xf>(v));
+  v = fmaxf(v, dpp_move<0x112, 0xf>(v));
+  v = fmaxf(v, dpp_move<0x114, 0xf>(v));
+  v = fmaxf(v, dpp_move<0x118, 0xf>(v));
+  v = fmaxf(v, dpp_move<0x142, 0xa>(v));
+  return fmaxf(v, dpp_move<0x143, 0xc>(v));
 }
 __device__ __forceinline__ double wave_sum(double v) {       // ... in every lane
   v = wave_sum63(v);
@@ -383,12 +392,9 @@ __device__ __forceinline__ Sampled sample_drifts(RowOf row_of, int live, const f
 // every thread: the typical magnitude of a sample of `coords` coordinates, `rows` rows each (0: it saw no drift)
 __device__ __forceinline__ double sample_mean(Sampled s, long long coords, int rows, float* scratch) {
   constexpr int kWaves = kStateThreads / 64;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    s.sum += __shfl_xor(s.sum, o, 64);
-    s.run = fmaxf(s.run, __shfl_xor(s.run, o, 64));
-  }
-  if ((threadIdx.x & 63) == 0) { scratch[threadIdx.x >> 6] = s.sum; scratch[kWaves + (threadIdx.x >> 6)] = s.run; }
+  s.sum = wave_sum63(s.sum);
+  s.run = wave_max63(s.run);
+  if ((threadIdx.x & 63) == 63) { scratch[threadIdx.x >> 6] = s.sum; scratch[kWaves + (threadIdx.x >> 6)] = s.run; }
   __syncthreads();
   double sum = 0.0;
   float run = 0.0f;
@@ -415,14 +421,14 @@ constexpr float kTermBound = 1073741824.0f;              // 2^30: scaled drifts 
 // block_all_max needs beside them.
 constexpr int kRedSums = kStateThreads / 64 * kMaxKC * 2;
 
-// largest value of a float over the workgroup, in every thread
+// largest of floats >= 0 over the workgroup, in every thread
 __device__ __forceinline__ float block_all_max(float v, double* scratch) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  v = wave_max63(v);
   float* tops = reinterpret_cast<float*>(scratch);
-  if ((threadIdx.x & 63) == 0) tops[threadIdx.x >> 6] = v;
+  if ((threadIdx.x & 63) == 63) tops[threadIdx.x >> 6] = v;
   __syncthreads();
-  for (int q = 0; q < kStateThreads / 64; ++q) v = fmaxf(v, tops[q]);
+  v = tops[0];
+  for (int q = 1; q < kStateThreads / 64; ++q) v = fmaxf(v, tops[q]);
   __syncthreads();
   return v;
 }
