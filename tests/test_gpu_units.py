@@ -442,3 +442,34 @@ def test_update_xi_at_the_edges_of_its_blocks(d, shift):
     mon.update_xi(now, now, xi)                          # no change: zeros
     assert not xi.any()
     mon.close()
+
+
+@pytest.mark.parametrize("K,dtype", [(128, "f32"), (256, "bf16")])
+def test_many_workers_of_a_small_model_are_synchronized(K, dtype):
+    """Small blocks with streaming hints: a slab just beyond 512 MiB, rows off every line.  Whole numbers, whose mean
+    over 2^k workers is exact."""
+    import paper_2405_20988_amd as F
+    d = 1_049_003
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K)
+    old = torch.randint(-8, 9, (d,), generator=g, device=DEV).float()
+    storage = torch.float32 if dtype == "f32" else torch.bfloat16
+    w = torch.empty((K, d), device=DEV, dtype=storage)
+    mean = torch.zeros(d, device=DEV)
+    for k in range(K):
+        row = torch.randint(-8, 9, (d,), generator=g, device=DEV).float()
+        mean += row
+        w[k] = row
+    mean /= K
+    mon = F.FdaMonitor(K, d, dtype, 1, device=DEV)
+    w_t0, w_prev, xi = old.clone(), torch.empty_like(old), torch.empty_like(old)
+    want = (mean.double() - old.double()) / torch.linalg.vector_norm(mean.double() - old.double())
+    mon.sync_xi(w, w_t0, w_prev, xi)
+    assert torch.equal(w_t0, mean) and torch.equal(w_prev, old)
+    assert bool((w == mean.to(storage)).all())
+    assert torch.allclose(xi.double(), want, rtol=1e-6, atol=0)
+    w_bar = torch.flip(mean, (0,)).contiguous()
+    mon.sync_from_mean(w, w_t0, w_bar, w_prev)
+    assert torch.equal(w_t0, w_bar) and torch.equal(w_prev, mean)
+    assert bool((w == w_bar.to(storage)).all())
+    mon.close()
