@@ -473,3 +473,20 @@ def test_many_workers_of_a_small_model_are_synchronized(K, dtype):
     assert torch.equal(w_t0, w_bar) and torch.equal(w_prev, mean)
     assert bool((w == w_bar.to(storage)).all())
     mon.close()
+
+
+@pytest.mark.parametrize("K,d", [(15, 5_001), (16, 5_001), (17, 1_023), (60, 30_001), (300, 5_003), (131, 70_001), (24, 262_147)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_rows_split_over_workgroups(K, d, dtype):
+    """fda_sync_from_mean stores the rows of a block from several workgroups: every row once, the models once."""
+    import paper_2405_20988_amd as F
+    g = torch.Generator(device=DEV)
+    g.manual_seed(K)
+    old, new = (torch.randn(d, generator=g, device=DEV) for _ in range(2))
+    w = torch.randn((K, d), generator=g, device=DEV).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    mon = F.FdaMonitor(K, d, dtype, 1, device=DEV)
+    w_t0, w_prev = old.clone(), torch.empty_like(old)
+    mon.sync_from_mean(w, w_t0, new, w_prev)
+    assert torch.equal(w_t0, new) and torch.equal(w_prev, old)
+    assert bool((w == new.to(w.dtype)).all())
+    mon.close()
