@@ -154,7 +154,9 @@ int fda_workspace_bytes(const fda_desc* desc, size_t* bytes);
  * All calls of one context use that workspace for their partial results: enqueue them on one
  * stream (or order them yourself); calls of one context that overlap on the device race.  A
  * context is used by one host thread at a time, with the device it was created on current
- * (anything else is FDA_EINVAL). */
+ * (anything else is FDA_EINVAL).
+ * fda_destroy enqueues nothing and does not wait for the context's work, with one exception: the last context that
+ * has read a result back also frees the library's pinned page, and that waits for the device. */
 int fda_create(fda_ctx** ctx, const fda_desc* desc, void* workspace, size_t workspace_bytes);
 int fda_destroy(fda_ctx* ctx);
 

@@ -238,7 +238,9 @@ int make_split(const fda_desc* d, int cus, int64_t lds_cu, Split* sp) {
     return fail(FDA_ERANGE, "one row of an m = %d sketch does not fit in %lld bytes of LDS", d->m,
                 (long long)lds_cu);
   // Short launches: more groups of fewer workers where that is clearly faster (5 x 61706: 3 groups of 2 slots 9.9
-  // us, 1 of 6 14.3; 30 x 100001: 15 of 2 14.0 us, 5 of 6 18.9).  Vectors below 24 tiles keep the cheapest split.
+  // us, 1 of 6 14.3; 30 x 100001: 15 of 2 14.0 us, 5 of 6 18.9).  Vectors below 24 tiles keep the cheapest split, which
+  // measures slower there too (5 x 30000 fp32 24.3 us a step against 19.9, 60 x 30000 31.2 against 25.7): what speaks for
+  // the line is only that small vectors exercise the kernels of six and eight slots.
   if (cells && tiles >= kQuickTiles && quick.G != 0 && quick.us < kQuickGain * best.us) best = quick;
   sp->G = best.G;
   sp->R = best.R;

@@ -6,9 +6,12 @@ A sketch cell is a cancelling sum of n_cell terms.  Its bound is
 
 on every cell that is not nearly empty of drift, i.e. whose sum of |u_kj| is at least half of
 what n_cell average terms would give, sum_{j in cell} |u_kj| >= 0.5 * n_cell * mean_j |u_kj|.
-The kernels add a term as the integer round(u * 2^e) with 2^e * mean|u| >= 2^17: every term is
-off by at most 2^-18 of the mean |u|, a cell by at most n_cell * 2^-18 * mean|u| = 3.8e-6 *
-n_cell * mean|u|, which is inside (1) on those cells.  A cell whose terms are all far below the
+The kernels add a term as the integer round(u * 2^e) with 2^e * t >= 2^17, t the typical |u| in a
+sample of the workgroup that adds it: every term is off by at most 2^-18 t.  Where the t of the
+workgroups average to no more than the mean |u|, a cell is off by at most n_cell * 2^-18 * mean|u| =
+3.8e-6 * n_cell * mean|u|, which is inside (1) on those cells.  (That does not follow where a cell
+draws most of its terms from the workgroups with the largest drifts, where workers of very different
+drifts share a workgroup, or where a sample meets several outliers of which its chunk has few.)  A cell whose terms are all far below the
 mean (a sparse or clustered drift) keeps the same absolute rounding while (1) shrinks with its
 terms; only there the bound is
 
