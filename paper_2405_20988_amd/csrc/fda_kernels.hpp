@@ -59,7 +59,7 @@ struct StateParams {
   int P;                  // coordinate partitions
   int shrink;             // the unit of the 32-bit cells is this many bits coarser (cells that take many terms)
   int do_lin;
-  int do_sk;
+  int do_sk;              // (chooses the kernel)
   int vec_ok;             // whole-vector loads and stores may be used (pointers are element-aligned)
   double* part_np;        // [P][K][2]
   unsigned char* part_sk; // [P][K][l*m] places of 8 bytes; a row group's share starts at its first cell's place
@@ -454,6 +454,9 @@ __device__ __forceinline__ double block_all_sum(double v, double* scratch) {
 // [row][bucket][worker].  The loads of the next tile are issued
 // before the current one is consumed.
 //
+// SKETCH: false for LinearFDA alone (a kernel of its own: what the sketch needs further down cost that loop scalar
+// registers, 31 x 34M bf16 427 us a step for 417).
+//
 // KC and LR are compile-time and the loops over them carry no tests: a group with fewer than
 // KC workers re-reads its last worker into the spare slots, whose LDS columns are never
 // flushed; a group with fewer than LR rows sends the spare rows' additions to a small dummy
@@ -529,7 +532,7 @@ __device__ __forceinline__ int round_half_up(float x) {
   return q;
 }
 
-template <typename T, int KC, int LR, int FB, bool SPLIT = false>
+template <typename T, int KC, int LR, int FB, bool SPLIT = false, bool SKETCH = true>
 __global__ void __launch_bounds__(kStateThreads)
 state_kernel(const StateParams prm) {
   constexpr int V = kStateV;
@@ -557,9 +560,12 @@ state_kernel(const StateParams prm) {
     p = (prm.P & ~7) + e / GR;
   }
   const int g = gr / prm.R, r = gr - g * prm.R;
+  // (in the kernels of the sketch a test at run time: folded, the start of a workgroup is ordered differently and
+  // 5 x 61706 takes 18.0 us for 17.5)
+  const bool do_sk = SKETCH && prm.do_sk;
   int kstart, kcnt, rstart = 0, rcnt = 0;
   group_range(prm.K, prm.G, g, &kstart, &kcnt);
-  if (prm.do_sk) group_range(prm.l, prm.R, r, &rstart, &rcnt);
+  if (do_sk) group_range(prm.l, prm.R, r, &rstart, &rcnt);
   const bool scalars = r == 0;
 
   // cells32_* layout, KC words per bucket
@@ -570,7 +576,7 @@ state_kernel(const StateParams prm) {
   const int mrow = SPLIT ? 2 * prm.m : prm.m;          // buckets of one LDS row
   const uint32_t row_words32 = cells32_row_words(mrow, KC);
   const uint32_t dummy_base = (uint32_t)rcnt * row_words32 * 4u;
-  const int lds_quads = prm.do_sk ? ((int)cells32_words(rcnt, mrow, KC) + 3) / 4 : 0;       // 16 bytes each
+  const int lds_quads = do_sk ? ((int)cells32_words(rcnt, mrow, KC) + 3) / 4 : 0;       // 16 bytes each
   double* red = reinterpret_cast<double*>(lds_raw + (size_t)lds_quads * 16);
 
   const int tid = threadIdx.x;
@@ -620,7 +626,7 @@ state_kernel(const StateParams prm) {
   constexpr int kWaveTile = 64 * V, kHalf = kStateThreads / 128;        // kHalf waves of either kind
   const int wave_id = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int full = cend > cbeg && prm.vec_ok ? (int)((cend - cbeg) / kTile) * 2 * kHalf : 0;     // wave tiles
-  const int older = (int)((float)(full / kHalf) * (prm.do_sk ? kOlderShare : 0.5f) + 0.5f), younger = full / kHalf - older;
+  const int older = (int)((float)(full / kHalf) * (do_sk ? kOlderShare : 0.5f) + 0.5f), younger = full / kHalf - older;
   const int mine = wave_id < kHalf ? older : younger;
   // from a wave's it-th tile to its next one: all waves side by side as long as the younger ones have any
   auto stride_after = [&](int it) { return it + 1 <= younger ? (long long)2 * kHalf * kWaveTile : (long long)kHalf * kWaveTile; };
@@ -676,7 +682,7 @@ state_kernel(const StateParams prm) {
   uint32_t seen_or = 0u;            // OR of every cell value this lane's adds returned
   double typical = 0.0;             // mean sampled |u|
   bool sketch = false;
-  if (prm.do_sk) {
+  if (do_sk) {
     if (cend > cbeg) {
       const long long sbeg = sample_begin(cbeg, cend), len = cend - sbeg;
       auto row_of = [&](int i, int) { return wrow[i]; };
@@ -833,7 +839,7 @@ state_kernel(const StateParams prm) {
   };
   if (scalars) {
     if (sketch) run(std::true_type{}, std::true_type{}, std::true_type{});
-    else if (prm.do_sk) run(std::true_type{}, std::false_type{}, std::true_type{});
+    else if (do_sk) run(std::true_type{}, std::false_type{}, std::true_type{});
     else run(std::true_type{}, std::false_type{}, std::false_type{});
   } else if (sketch) {
     run(std::false_type{}, std::true_type{}, std::true_type{});
@@ -841,7 +847,7 @@ state_kernel(const StateParams prm) {
 
   // the 32-bit cells are void: a drift beyond their terms, a cell that left its band, or any drift at all
   // where the sample saw none
-  bool bad = prm.do_sk && (sketch ? (!(amax < kTermBound) || (seen_or & 0x80000000u) != 0u) : (!scalars || amax > 0.0f));
+  bool bad = do_sk && (sketch ? (!(amax < kTermBound) || (seen_or & 0x80000000u) != 0u) : (!scalars || amax > 0.0f));
 
   // ---- workgroup reduction of the scalar components (fixed shape) ---------------------
   const int lane = tid & 63, wave = tid >> 6;
@@ -866,7 +872,7 @@ state_kernel(const StateParams prm) {
     }
   };
   put_scalars(dn, dp, 1.0 / (double)S32);
-  if (!prm.do_sk) return;
+  if (!do_sk) return;
   // ---- flush the LDS sketch to this workgroup's slice of the partial buffer -----------
   const size_t allcells = (size_t)prm.l * prm.m;
   // (worker kstart + k's share begins at place [(p * K + kstart + k) * allcells + rstart * m])

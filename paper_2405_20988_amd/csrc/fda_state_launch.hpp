@@ -29,9 +29,9 @@ FDA_NARROW_LAUNCHER(f32, 6); FDA_NARROW_LAUNCHER(f32, 8);
 FDA_NARROW_LAUNCHER(bf16, 1); FDA_NARROW_LAUNCHER(bf16, 2); FDA_NARROW_LAUNCHER(bf16, 4);
 FDA_NARROW_LAUNCHER(bf16, 6); FDA_NARROW_LAUNCHER(bf16, 8);
 
-template <typename T, int KC, int LR, int FB, bool SPLIT = false>
+template <typename T, int KC, int LR, int FB, bool SPLIT = false, bool SKETCH = true>
 hipError_t launch_state_kernel(const StateParams* prm, size_t lds, hipStream_t st) {
-  auto kern = state_kernel<T, KC, LR, FB, SPLIT>;
+  auto kern = state_kernel<T, KC, LR, FB, SPLIT, SKETCH>;
   if (prm == nullptr)
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
