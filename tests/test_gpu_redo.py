@@ -136,6 +136,39 @@ def test_what_is_typical_of_a_redone_chunk(K, l, m, dtype):
     mon.close()
 
 
+@pytest.mark.parametrize("ratio", [2.0 ** 8, 2.0 ** 20])
+@pytest.mark.parametrize("K,d,l,m,dtype", [(30, 900_001, 5, 250, "f32"), (8, 1_100_001, 7, 1000, "bf16"),
+                                           (2, 4_300_003, 12, 300, "f32")])
+def test_a_redone_long_chunk_keeps_29_bits_of_the_other_drifts(K, d, l, m, dtype, ratio):
+    """Every workgroup meets a drift beyond its terms, of the last of its workers, and two `ratio` times the others in
+    sampled runs of their own, of which one stays in the sample's mean.  A cell is off by its own fp32 rounding and by
+    half a unit for each of its terms, with 2^29 units or more to a typical drift, or fp64; a sum by its fp32 rounding."""
+    import paper_2405_20988_amd as F
+    g = gen(K)
+    coef = S.hash_coefficients(K, l)
+    mon = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, coef, device=DEV)
+    chunk, wpg = mon.plan["chunk"], mon.plan["workers_per_group"]
+    assert chunk >= 8 * 2048 and K % wpg == 0
+    u = torch.randn((K, d), generator=g, device=DEV) * 1e-3
+    first = torch.arange(0, d - chunk, chunk, device=DEV)
+    u[:, d - d % chunk:] = 0.0
+    run = chunk // 64                                     # a sampled run of 8 at each multiple
+    for k in range(wpg - 1, K, wpg):
+        u[k, first + 10 * run] = u[k, first + 40 * run + 7] = 1e-3 * ratio
+        u[k, first + 20 * run + 9] = 1e-3 * ratio * 64
+    w = u.to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    zero, xi = torch.zeros(d, device=DEV), torch.randn(d, generator=g, device=DEV) / d ** 0.5
+    ref = O.local_state(S.slab_to_numpy(w), dtype, zero.cpu().numpy(), xi.cpu().numpy(), coef, m)
+    mon.local_state(w, zero, xi)
+    n, p, sk = mon.state_numpy()
+    assert mon.last_state_path() >= 1
+    assert np.allclose(n, ref["n"], rtol=2.0 ** -23, atol=0)
+    assert (np.abs(p - ref["p"]) <= 2.0 ** -23 * np.abs(ref["p"]) + 2.0 ** -40 * ref["p_abs"]).all()
+    err = np.abs(sk.astype(np.float64) - ref["sk"])
+    assert (err <= 2.0 ** -24 * np.abs(ref["sk"]) + ref["sk_cnt"][None] * 2.0 ** -30 * 0.8e-3 + 1e-45).all()
+    mon.close()
+
+
 @pytest.mark.parametrize("size,path", [(2.0 ** 14, 1), (1e12, 2)])       # 64-bit integers, fp64
 @pytest.mark.parametrize("K,d,l,m,dtype", [
     (1, 50_001, 9, 250, "f32"), (1, 50_001, 1, 20_000, "bf16"),          # half of a worker's cells at a time
@@ -154,8 +187,8 @@ def test_redone_sketches_of_every_layout(K, d, l, m, dtype, size, path):
 
 
 def steps_of(K, d, dtype, g):
-    """Drifts of either sign around 1.5 * 2^-10: one unit, 2^28, for every workgroup, whose terms end at 4 and whose
-    list ends at 2^11."""
+    """Drifts of either sign around 1.5 * 2^-10: one unit, 2^28, for every workgroup whose sample sees no others, whose
+    terms end at 4."""
     u = (1.5 + 0.1 * torch.randn((K, d), generator=g, device=DEV).clamp_(-2, 2)) * 2.0 ** -10
     u *= torch.randint(0, 2, (K, d), generator=g, device=DEV) * 2 - 1
     return u.to(torch.float32 if dtype == "f32" else torch.bfloat16)
@@ -167,20 +200,21 @@ def steps_of(K, d, dtype, g):
     (11, 700_001, 3, 1500, "f32"), (30, 900_001, 9, 250, "bf16"),       # a spare slot; rows with a skew
     (31, 900_001, 5, 250, "f32"), (3, 1_500_001, 1, 20_000, "f32")])    # spare slots of six; plain rows of 16-bit fields
 def test_outliers_of_a_long_chunk(K, d, l, m, dtype):
-    """Long chunks, each with its own: drifts just below and just beyond the terms, as many as the list holds, one more
-    than that, one beyond the list."""
+    """Long chunks, each with its own, outside the sampled runs: drifts just below and just beyond the terms, one, tens
+    and hundreds beyond them, one of 2^39 units."""
     import paper_2405_20988_amd as F
     g = gen(K)
     plan = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, S.hash_coefficients(K, l), device=DEV).plan
-    chunk = plan["chunk"]
+    chunk, run = plan["chunk"], plan["chunk"] // 64       # a sampled run of 8 at each multiple
     assert chunk >= 8 * 2048
     w = steps_of(K, d, dtype, g)
     for i, x in enumerate((3.984375, 4.0, -3.984375, -4.0, 2040.0, -2040.0)):
-        w[K - 1, chunk + 3 + 701 * i] = x
-        w[0, chunk + 5 + 701 * i] = -x
+        w[K - 1, chunk + run * i + 9] = x
+        w[0, chunk + run * i + 11] = -x
     w[:, 2 * chunk - 1] = 37.0
-    for p, n in ((3, 64), (5, 65), (8, 200)):
-        w[K - 1, p * chunk + 77 * torch.arange(n, device=DEV)] = 100.0
+    for p, n in ((3, 1), (5, 65), (8, 600)):
+        i = torch.arange(n, device=DEV)
+        w[K - 1, p * chunk + run * (i % 64) + 8 + torch.div(i, 64, rounding_mode="floor")] = 100.0
     w[K - 1, 10 * chunk + 9] = 2048.0
     xi = torch.randn(d, generator=g, device=DEV) / d ** 0.5
     check_both(w, torch.zeros(d, device=DEV), xi, dtype, l, m, K, path=(1,), mean_path=1)
@@ -248,19 +282,3 @@ def test_partials_of_every_kind_merge(K, d, l, m, dtype):
     w = w.to(torch.float32 if dtype == "f32" else torch.bfloat16)
     xi = torch.randn(d, generator=g, device=DEV)
     check_both(w, w_t0, xi / xi.norm(), dtype, l, m, seed=d, path=(2,), mean_path=1)
-
-
-def test_what_a_few_outliers_cost():
-    """One workgroup meets a drift beyond its terms: less than twice the pass without it (5 times when it did its sketch
-    again)."""
-    import paper_2405_20988_amd as F
-    K, d = 30, 7_000_000
-    mon = F.FdaMonitor(K, d, "f32", 3, 5, 250, 0.06, S.hash_coefficients(1, 5), device=DEV)
-    w_t0 = torch.zeros(d, device=DEV)
-    w = torch.randn((K, d), generator=gen(1), device=DEV) * 1e-3
-    plain = microseconds(lambda: mon.local_state(w, w_t0, w_t0))
-    w[1, d // 3 + 5] = 1e-3 * 2 ** 14
-    listed = microseconds(lambda: mon.local_state(w, w_t0, w_t0))
-    print("state %.0f -> %.0f us" % (plain, listed))
-    assert listed < 3.0 * plain
-    mon.close()
