@@ -118,19 +118,22 @@ def test_an_outlier_in_a_short_last_chunk(K, d, l, m, dtype, size):
 
 @pytest.mark.parametrize("K,l,m,dtype", [(3, 1, 500, "f32"), (4, 3, 500, "bf16"), (8, 2, 500, "f32")])
 def test_what_is_typical_of_a_redone_chunk(K, l, m, dtype):
-    """Two drifts 2^40 times the others, in sampled runs of their own: one is left out of the sample's mean, the other
-    stays.  The redone sketch does not go by that mean: 2^29 units or more to a typical drift, or fp64."""
+    """Two drifts 2^34 times the others, in sampled runs of their own (runs of 8 at the multiples of 31 here): one is left
+    out of the sample's mean, the other stays.  A third, larger one lies outside the sample.  The redone sketch does not
+    go by that mean: 2^29 units or more to a typical drift, or fp64."""
     import paper_2405_20988_amd as F
     d, g = 2_000, gen(K)
     w = (torch.randn((K, d), generator=g, device=DEV) * 1e-3).to(torch.float32 if dtype == "f32" else torch.bfloat16)
-    w[0, 700] = w[K - 1, 1500] = 1e-3 * 2.0 ** 40
+    w[:, 22 * 31 + 3] = w[:, 48 * 31 + 2] = 1e-3 * 2.0 ** 34
+    w[:, 23 * 31 + 9] = 1e-3 * 2.0 ** 40
     coef = S.hash_coefficients(K, l)
     mon = F.FdaMonitor(K, d, dtype, 3, l, m, 0.06, coef, device=DEV)
+    assert mon.plan["partitions"] == 1
     zero = torch.zeros(d, device=DEV)
     ref = O.local_state(S.slab_to_numpy(w), dtype, zero.cpu().numpy(), zero.cpu().numpy(), coef, m)
     mon.local_state(w, zero, zero)
     sk = mon.state_numpy()[2]
-    assert mon.last_state_path() >= 1
+    assert mon.last_state_path() == 2
     err = np.abs(sk.astype(np.float64) - ref["sk"])
     assert (err <= 2.0 ** -24 * np.abs(ref["sk"]) + ref["sk_cnt"][None] * 2.0 ** -30 * 0.8e-3 + 1e-45).all()
     mon.close()
