@@ -182,8 +182,8 @@ int fda_get_plan(const fda_ctx* ctx, fda_plan_info* out);
  * (fda_last_state_path 0 or 1) the state is bit-identical from run to run; the fp64 cells of the last
  * fallback (path 2, and path 1 of fda_mean_state) add in the order the lanes arrive and are not.
  * ||u_k||^2 and <xi,u_k> are summed on drifts scaled by that 2^e; a workgroup that meets drifts beyond 2^30
- * of its units sums them again in fp64, unscaled, together with its sketch: they are infinite only where
- * fp32 cannot hold the result.
+ * of its units, or whose cells leave their range, sums them again in fp64, unscaled, together with its sketch:
+ * they are infinite only where fp32 cannot hold the result.
  * The first call of a context also tabulates the hash into the workspace (one record per coordinate:
  * 11 bits per sketch row, 16 for m > 1024, 13 where the rows are placed -- fda_plan_info.placed_row_group --
  * rounded up to whole 16-bit words; 12 bytes for l = 7, m = 1000).  fda_mean_state tabulates a plain

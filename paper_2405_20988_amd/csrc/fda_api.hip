@@ -44,7 +44,9 @@ int fail(int code, const char* fmt, ...) {
       return fail(FDA_EHIP, "%s failed: %s", #call, hipGetErrorString(e_));            \
   } while (0)
 
-constexpr int64_t kLdsReserve = 1536;      // reduction scratch (8 waves x 8 worker slots x 2 doubles) + slack
+// reduction scratch: the scalar sums (8 waves x 8 worker slots x 2 doubles), a double per wave behind them, and slack
+constexpr int64_t kLdsReserve = 1536;
+static_assert((fda::kRedSums + fda::kStateThreads / 64) * (int64_t)sizeof(double) <= kLdsReserve, "reduction scratch");
 constexpr int kMaxRounds = 4;              // at most this many rounds of resident workgroups per launch
 constexpr int64_t kMaxTermsPlanned = 12000;    // terms per 32-bit cell and workgroup the planner allows for
 constexpr int64_t kMaxTermsPlannedSplit = 3500;   // ... per cell of a sign-split row

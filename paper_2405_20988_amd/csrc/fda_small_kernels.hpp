@@ -380,8 +380,8 @@ __device__ __forceinline__ double sum_partials(const V* q, size_t step, const Ce
 // The same where some workgroups redid their sketch: the kind of each partition says where its sum lies and how wide it
 // is, so the units of a batch are loaded together and then its sums: two latencies for four partitions, where one after
 // the other took two for each.  (One drift 2^14 times the others, us a call, state and average state: 16 x 2.6M fp32
-// 89.8 and 63.1, now 84.5 and 57.3; 7 x 18M bf16 224.5 and 137.7, now 218.5 and 126.4; 8 x 3000001 bf16 81.8 and 61.6, now
-// 76.9 and 51.2.  Batches of 16 are no faster, hold 129 registers where the kernel has 91 otherwise and cost every call
+// 217 and 62.8, now 212 and 57.8; 7 x 18M bf16 669 and 137.7, now 663 and 125.9; 8 x 3000001 bf16 147.7 and 53.7, now
+// 143.0 and 42.7.  Batches of 16 are no faster, hold 129 registers where the kernel has 91 otherwise and cost every call
 // the second workgroup of a CU: 7 x 18M without such a drift 141.4 us a step for 138.0.)
 constexpr int kKindLoads = 4;
 __device__ __forceinline__ double sum_partials_by_kind(const unsigned char* base, size_t cell, size_t step, const CellUnit* un,

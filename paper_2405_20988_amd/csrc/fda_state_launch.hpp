@@ -8,8 +8,8 @@
 #include "fda_kernels.hpp"
 
 namespace fda {
-// Worker slots KC in kKCSet, row slots LR in 1..kMaxLR, KC * LR <= max_slots(KC): what the registers hold (4 x 9 takes 251 of
-// 256, 6 x 6 would spill).  Nine rows in one workgroup instead of groups of five and four with six worker slots:
+// Worker slots KC in kKCSet, row slots LR in 1..kMaxLR, KC * LR <= max_slots(KC): what the registers hold (fp32 slabs, with
+// the library's own compiler options: 4 x 9 and 6 x 5 take 251 of 256, 6 x 6 would spill; 8 x 4 spills 50 to 54).  Nine rows in one workgroup instead of groups of five and four with six worker slots:
 // 9 x 250, 30 x 7M fp32 378 -> 293 us a step, 8 x 40M bf16 553 -> 433.
 // Kernels with sign-split LDS rows exist for the even KC, kernels with plain rows for KC <= 2 (with
 // more slots, half the slots per workgroup and split rows need the same LDS and less work).
