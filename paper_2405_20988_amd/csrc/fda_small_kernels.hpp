@@ -358,7 +358,11 @@ constexpr int kFinishLoads = 16;   // partials per thread the host aims at
 constexpr int kMeanLoads = 8;
 
 // sum over the partitions slice, slice + slices, ... of value times unit.  The loads of a batch of N are issued
-// together (those past the end repeat the first one).
+// together (those past the end repeat the first one).  For the 4-byte sums nothing may move across the end of the
+// loads: beside the shorter batch of the 8-byte ones the compiler waited for the first partition before it issued
+// the other fifteen, a second latency (5 x 61706 fp32 17.35 -> 17.5 us a step; as it is now 17.0, in 65 registers for
+// 76; 16 x 2.6M 57.3, now 56.5).  The 8-byte loads are together without it, and with it 11 x 123457 takes 48.2 us for
+// 47.9.
 template <int N, typename V>
 __device__ __forceinline__ double sum_partials(const V* q, size_t step, const CellUnit* un, int GR, int slice, int slices, int P) {
   double acc = 0.0;
@@ -371,6 +375,7 @@ __device__ __forceinline__ double sum_partials(const V* q, size_t step, const Ce
       x[t] = q[p * step];
       unit[t] = un[(size_t)p * GR].unit;
     }
+    if constexpr (sizeof(V) == 4) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < N; ++t) acc += p0 + t * slices < P ? unit[t] * (double)x[t] : 0.0;
   }
@@ -381,8 +386,8 @@ __device__ __forceinline__ double sum_partials(const V* q, size_t step, const Ce
 // is, so the units of a batch are loaded together and then its sums: two latencies for four partitions, where one after
 // the other took two for each.  (One drift 2^14 times the others, us a call, state and average state: 16 x 2.6M fp32
 // 217 and 62.8, now 212 and 57.8; 7 x 18M bf16 669 and 137.7, now 663 and 125.9; 8 x 3000001 bf16 147.7 and 53.7, now
-// 143.0 and 42.7.  Batches of 16 are no faster, hold 129 registers where the kernel has 91 otherwise and cost every call
-// the second workgroup of a CU: 7 x 18M without such a drift 141.4 us a step for 138.0.)
+// 143.0 and 42.7.  Batches of 16 are no faster, hold 129 registers and cost every call the second
+// workgroup of a CU: 7 x 18M without such a drift 141.4 us a step for 138.0.)
 constexpr int kKindLoads = 4;
 __device__ __forceinline__ double sum_partials_by_kind(const unsigned char* base, size_t cell, size_t step, const CellUnit* un,
                                                        int GR, int slice, int slices, int P) {
